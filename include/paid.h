@@ -118,12 +118,10 @@ typedef struct {
                            the evaluation launch) as HIP graphs and replay
                            them every round */
   int eval_wg_per_cu;   /* workgroups of the region-evaluation launch per
-                           compute unit (0: 16 per workgroup the kernel's
-                           occupancy fits on a compute unit); the work items
-                           of a round are split over them in geometrically
-                           shrinking ranges; grids much shorter than the
-                           default hand the first workgroups more than an
-                           even share (8 per occupancy slot: ~25% slower) */
+                           compute unit (0: as many as the kernel's occupancy
+                           fits on one); they share the work items of a round
+                           out among themselves in shrinking chunks, so more
+                           than fit at once gains nothing */
   int symmetry;         /* 1: integrate over the half zone p_y >= 0 only.  The
                            integrand of both bubbles is even under p -> -p
                            (it swaps the energies eps(l/2 + p) and

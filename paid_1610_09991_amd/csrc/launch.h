@@ -67,7 +67,6 @@ struct Problem {      // everything the round kernels need, passed by value
   int lds_wave_doubles;       // per-wave LDS of the evaluation kernel (set at launch)
   int tab_rows;               // rows of the largest frequency-sum table (the LDS table)
   int lds_limit;              // bytes of LDS a workgroup may use on the device
-  int eval_slots;             // evaluation workgroups resident at once (0: even partition)
   int sym;                    // 1: half zone p_y >= 0 with the parity factors of the pairs
   int eval_layout;            // 0: the fastest evaluation kernel for the basis, 1: one wave per parent
   uint64_t *code;             // [regions], slot s from slot_base(s)
@@ -89,7 +88,7 @@ struct Problem {      // everything the round kernels need, passed by value
   int *st_depth;              // [W]
   // queue and global counters
   int *qhead;                 // next container to admit
-  int *counters;              // [0] done, [1] not converged, [2] total work items
+  int *counters;              // [0] done, [1] not converged, [2] total work items, [3] chunk counter
   long long *gstats;          // [0] rounds [1] splits [2] leaves [3] max depth
   // outputs (device)
   double *out, *err_out;      // [n_ctr][M][M]

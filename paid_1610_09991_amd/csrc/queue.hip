@@ -552,6 +552,7 @@ __global__ void k_worklist(Problem P) {
   if (t == 0) {
     P.woff[P.W] = carry;
     P.counters[2] = carry;
+    P.counters[3] = 0;  // the evaluation's chunk counter
   }
 }
 

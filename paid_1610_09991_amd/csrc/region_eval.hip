@@ -913,31 +913,62 @@ __device__ inline const Problem &kernarg_problem(const Problem &P) {
 #endif
 }
 
-// Work items [i0, i1) of this workgroup.  Guided partition: workgroup b
-// starts at item total (1 - k^b) with k = 1 - 1/S, S the workgroups resident
-// at once, so the ranges shrink geometrically and the workgroups dispatched
-// last (the tail of the launch) are short; k is lowered where the grid would
-// otherwise leave its last workgroup more than four items.
-__device__ inline void item_range(const Problem &P, int &i0, int &i1) {
-  const int total = P.counters[2];
-  if (P.eval_slots > 0) {
-    const double keep = fmin(1.0 - 1.0 / (double)P.eval_slots,
-                             exp(log(4.0 / fmax((double)total, 4.0)) / (double)gridDim.x));
-    auto start = [&](int b) -> int {
-      return b >= (int)gridDim.x ? total : (int)((double)total * (1.0 - pow(keep, (double)b)));
-    };
-    i0 = start(blockIdx.x);
-    i1 = min(start(blockIdx.x + 1), total);
-  } else {
-    const int per = (total + gridDim.x - 1) / gridDim.x;
-    i0 = blockIdx.x * per;
-    i1 = min(i0 + per, total);
+// The round's work items in chunks: the grid is the workgroups resident at
+// once; each takes a first chunk by its index and then further ones from a
+// counter (P.counters[3], zero at the start of a round) until the items are
+// gone.  A chunk is half of an even share of the items that are left, in
+// whole passes of the workgroup's waves, so chunks shrink towards the end and
+// no workgroup is left with a long one; a round of few items is spread over
+// all workgroups, a pass of one wave (`unit` items) at a time.  Which
+// workgroup evaluates an item changes nothing in its result.  (Sixteen
+// generations of workgroups with ranges shrinking by index, before, paid the
+// start of a workgroup - its table, its search for the first slot - sixteen
+// times a round: 80 us a launch for rounds of 300 items.)
+struct Chunk {
+  int i0, i1;
+};
+__device__ inline int chunk_items(int left, int unit) {
+  const int wg = unit * (int)(blockDim.x >> 6), nb = (int)gridDim.x;
+  const int half = left / (2 * nb);
+  if (half >= wg) return half / wg * wg;
+  const int even = (left + nb - 1) / nb;  // spread what is left
+  return max(unit, min(wg, (even + unit - 1) / unit * unit));
+}
+__device__ inline Chunk first_chunk(const Problem &P, int unit) {
+  const int total = P.counters[2], c = chunk_items(total, unit);
+  Chunk k;
+  k.i0 = (int)min((long)blockIdx.x * c, (long)total);
+  k.i1 = min(k.i0 + c, total);
+  return k;
+}
+// the next chunk, the same in every thread (two workgroup barriers)
+__device__ inline Chunk next_chunk(const Problem &P, int unit, int *sh) {
+  __syncthreads();  // every wave is done with the last chunk (and with sh)
+  if (threadIdx.x == 0) {
+    const int total = P.counters[2], c0 = chunk_items(total, unit);
+    const long base = (long)c0 * gridDim.x;
+    int i0 = total, i1 = total;
+    if (base < total) {
+      const int seen = (int)base + __hip_atomic_load(&P.counters[3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (seen < total) {
+        const int c = chunk_items(total - seen, unit);
+        i0 = min((int)base + atomicAdd(&P.counters[3], c), total);
+        i1 = min(i0 + c, total);
+      }
+    }
+    sh[0] = i0;
+    sh[1] = i1;
   }
+  __syncthreads();
+  Chunk k;
+  k.i0 = __builtin_amdgcn_readfirstlane(sh[0]);
+  k.i1 = __builtin_amdgcn_readfirstlane(sh[1]);
+  return k;
 }
 
-// Each workgroup takes a contiguous range of work items; its waves take every
-// nw-th item of it, so at any time they work on neighbouring parents, mostly
-// of one container and parameter row.  The range is cut into segments of
+// Each workgroup takes contiguous chunks of work items; its waves take every
+// nw-th item of one, so at any time they work on neighbouring parents, mostly
+// of one container and parameter row.  A chunk is cut into segments of
 // consecutive slots of one parameter row (usually a single one); at the
 // start of a segment the workgroup stages that row's table in LDS (two
 // barriers), and inside a segment there is no workgroup barrier: each wave
@@ -953,12 +984,16 @@ __global__ void __launch_bounds__(256) k_children(Problem P) {
   const int nw = blockDim.x >> 6, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   WaveLds<L> &S = *reinterpret_cast<WaveLds<L> *>(lds_raw + (size_t)P.tab_rows * kTabStride +
                                                   (size_t)wv * P.lds_wave_doubles);
-  int i0, i1;
-  item_range(P, i0, i1);
-  if (i0 >= i1) return;  // uniform in the workgroup
+  __shared__ int next[2];
+  Chunk k = first_chunk(P, 1);
+  if (k.i0 >= k.i1) return;  // uniform in the workgroup
   build_pidmap<L>(pidmap, podd, threadIdx.x, blockDim.x);
-  int s = item_slot(P, i0), lo = P.woff[s], hi = P.woff[s + 1];  // current slot, its items
-  int w = i0 + wv, seg = i0, loaded = -1;
+  int loaded = -1;
+#pragma unroll 1
+  for (; k.i0 < k.i1; k = next_chunk(P, 1, next)) {
+  const int i1 = k.i1;
+  int s = item_slot(P, k.i0), lo = P.woff[s], hi = P.woff[s + 1];  // current slot, its items
+  int w = k.i0 + wv, seg = k.i0;
 #pragma unroll 1
   while (seg < i1) {
     // segment [seg, seg_hi): slots from s on while they hold items of row e
@@ -996,6 +1031,7 @@ __global__ void __launch_bounds__(256) k_children(Problem P) {
       lo = P.woff[s];
       hi = P.woff[s + 1];
     }
+  }
   }
 }
 
@@ -1403,11 +1439,15 @@ __global__ void __launch_bounds__(512) k_children_lpc(Problem P) {
   double *tabl = lds_raw;
   const int nw = blockDim.x >> 6, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   double *Yw = lds_raw + (size_t)P.tab_rows * kTabStride + (size_t)wv * P.lds_wave_doubles;
-  int i0, i1;
-  item_range(P, i0, i1);
-  if (i0 >= i1) return;  // uniform in the workgroup
-  int s = item_slot(P, i0), hi = P.woff[s + 1];
-  int seg = i0, loaded = -1;
+  __shared__ int next[2];
+  Chunk k = first_chunk(P, lpc::kItems);
+  if (k.i0 >= k.i1) return;  // uniform in the workgroup
+  int loaded = -1;
+#pragma unroll 1
+  for (; k.i0 < k.i1; k = next_chunk(P, lpc::kItems, next)) {
+  const int i1 = k.i1;
+  int s = item_slot(P, k.i0), hi = P.woff[s + 1];
+  int seg = k.i0;
 #pragma unroll 1
   while (seg < i1) {
     const int e = __builtin_amdgcn_readfirstlane(slot_entry(P, s));
@@ -1440,6 +1480,7 @@ __global__ void __launch_bounds__(512) k_children_lpc(Problem P) {
       s = t;
       hi = P.woff[s + 1];
     }
+  }
   }
 }
 
