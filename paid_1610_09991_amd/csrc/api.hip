@@ -52,7 +52,7 @@ struct paid_ctx {
   bool own_stream = false;
   std::string err;
   // workspace
-  DevBuf entries, tab, zeta, svals, ctr, qv, ffc;
+  DevBuf entries, tab, zeta, svals, ctr, qv, ffc, pcoef;
   DevBuf code, key, Q, E;
   DevBuf slot_i, slot_d, sel, dv, de, dep, itau, errp, stl, counters, outs, errs;
   // learned seeding
@@ -63,6 +63,7 @@ struct paid_ctx {
   float *feat_out = nullptr, *lab_out = nullptr;
   const double *pair_w = nullptr;  // weighted mode: caller's [n_ctr][M][M]
   DevBuf pairw;
+  std::vector<double> hcoef;     // pairs over the product integrals (Problem::pcoef)
   // lockstep mode (batch = batch_max = 1): creation index of every leaf
   DevBuf born;
   // leaf output of finished containers
@@ -347,6 +348,33 @@ int carve_act(paid_ctx *c, DevBuf &buf, int n, MlpAct &a, float *&yhat, float *&
   return PAID_OK;
 }
 
+// the form-factor pairs as combinations of the 25 product integrals (general
+// sets over the 9-function box, or over its first function), on the device
+int stage_pair_coefficients(paid_ctx *c, Problem &P, const double *ff) {
+  if (!needs_pair_coefficients(P)) return PAID_OK;
+  std::vector<double> &co = c->hcoef;  // (kept: the copy may read it after this returns)
+  co.assign((size_t)P.MU * kProd, 0.0);
+  double *k = co.data();
+  for (int p = 0; p < P.M; ++p)
+    for (int q = p; q < P.M; ++q, k += kProd)
+      for (int m = 0; m < P.MB; ++m)
+        for (int n = 0; n < P.MB; ++n) {
+          const double w = ff[p * P.MB + m] * ff[q * P.MB + n];
+          if (w == 0.0) continue;
+          const int am = m / 3, bm = m % 3, an = n / 3, bn = n % 3;
+          const Terms x = prod_terms(std::min(am, an), std::max(am, an));
+          const Terms y = prod_terms(std::min(bm, bn), std::max(bm, bn));
+          k[kPhi * x.j0 + y.j0] += w;
+          if (y.n == 2) k[kPhi * x.j0 + y.j1] += w * y.s1;
+          if (x.n == 2) k[kPhi * x.j1 + y.j0] += w * x.s1;
+          if (x.n == 2 && y.n == 2) k[kPhi * x.j1 + y.j1] += w * x.s1 * y.s1;
+        }
+  HIPCHK(c, c->pcoef.ensure(sizeof(double) * co.size()));
+  HIPCHK(c, hipMemcpyAsync(c->pcoef.p, co.data(), sizeof(double) * co.size(), hipMemcpyHostToDevice, c->stream));
+  P.pcoef = c->pcoef.as<double>();
+  return PAID_OK;
+}
+
 struct SlotLayout {  // carving of the small per-slot arrays
   int *cid, *state, *nleaf, *selcnt, *woff, *flags, *depth;
 };
@@ -462,7 +490,7 @@ void paid_destroy(paid_ctx *c) {
                     &c->errp,    &c->stl,  &c->counters, &c->outs, &c->errs,
                     &c->seedw,   &c->sfeat, &c->sfold, &c->sy,  &c->sact,  &c->pyr,
                     &c->seedd,   &c->ifill, &c->labtmp, &c->pairw, &c->born, &c->lcodes,
-                    &c->lq,      &c->rowsz, &c->rperm, &c->movei, &c->upart};
+                    &c->lq,      &c->pcoef, &c->rowsz, &c->rperm, &c->movei, &c->upart};
   for (DevBuf *b : bufs) b->release();
   if (c->host_counters) (void)hipHostFree(c->host_counters);
   for (hipEvent_t ev : {c->ev0, c->ev1, c->ev2, c->ev3, c->evd[0], c->evd[1]})
@@ -520,65 +548,6 @@ int paid_integrate(paid_ctx *c, const paid_params *params, int n_params, const d
   HIPCHK(c, c->ctr.ensure(sizeof(Ctr) * n_ctr));
   HIPCHK(c, launch_container_setup(c->ctr.as<Ctr>(), n_ctr, c->qv.as<double>(), n_q, n_ch, ch_first, c->stream));
 
-  // pool: slots x capacity; with small_regions, large slots (capb) first,
-  // then small ones (cap)
-  const long capb = cfg.max_regions;
-  const bool two = cfg.small_regions > 0 && cfg.small_regions < capb;
-  const long cap = two ? cfg.small_regions : capb;
-  const size_t rec = 16 + 8 * (size_t)MU + (store_E ? 4 * (size_t)MU : 0);
-  size_t pool_bytes, rest_bytes = 0;  // rest: for the per-slot round buffers (0: unchecked)
-  if (cfg.pool_gib > 0) {
-    pool_bytes = (size_t)(cfg.pool_gib * 1073741824.0);
-  } else {
-    size_t fr = 0, tot = 0;
-    HIPCHK(c, hipMemGetInfo(&fr, &tot));
-    const double avail = (double)(fr + c->code.n + c->key.n + c->Q.n + c->E.n + c->dv.n + c->dep.n);
-    pool_bytes = (size_t)(0.55 * avail);
-    rest_bytes = (size_t)(0.35 * avail);
-  }
-  long Wb = 0;
-  if (two) {
-    const double share = cfg.big_share > 0 ? cfg.big_share : 0.25;
-    Wb = (long)(share * (double)pool_bytes / ((double)capb * rec));
-    if (Wb < 1) Wb = 1;
-    if (Wb > n_ctr) Wb = n_ctr;
-  }
-  const size_t big_bytes = (size_t)Wb * capb * rec;
-  long Ws = cfg.max_active > 0 ? cfg.max_active - Wb
-                               : (pool_bytes > big_bytes ? (long)((pool_bytes - big_bytes) / ((size_t)cap * rec)) : 0);
-  if (Ws > n_ctr) Ws = n_ctr;
-  if (Wb + Ws > 65536) Ws = 65536 - Wb;
-  // the round buffers of every slot (deltas, selections) must fit beside the pool
-  const size_t slot_rest = (size_t)cfg.batch_max * (8 * (size_t)MU * (store_E ? 2 : 1) + 16) + 32 * (size_t)MU;
-  if (rest_bytes > 0 && (size_t)(Wb + Ws) * slot_rest > rest_bytes) Ws = (long)(rest_bytes / slot_rest) - Wb;
-  if (Ws < 1) return fail(c, PAID_ENOMEM, "region pool too small for one container of %ld regions", cap);
-  const long W = Wb + Ws;
-  const size_t regions = (size_t)Wb * capb + (size_t)Ws * cap;
-  const int bmax = cfg.batch_max, bmin = cfg.batch;
-  HIPCHK(c, c->code.ensure(sizeof(uint64_t) * regions));
-  HIPCHK(c, c->key.ensure(sizeof(double) * regions));
-  HIPCHK(c, c->Q.ensure(sizeof(double) * regions * MU));
-  if (store_E) HIPCHK(c, c->E.ensure(sizeof(float) * regions * MU));
-  HIPCHK(c, c->movei.ensure(sizeof(int) * (size_t)(W + Wb + 1)));
-  HIPCHK(c, c->upart.ensure(sizeof(double) * update_scratch_doubles((int)W, MU)));
-  HIPCHK(c, c->slot_i.ensure(sizeof(int) * (8 * W + 8)));
-  HIPCHK(c, c->slot_d.ensure(sizeof(double) * (W * (size_t)MU + W)));
-  HIPCHK(c, c->errp.ensure(sizeof(double) * W * (size_t)MU));
-  HIPCHK(c, c->itau.ensure(sizeof(float) * W * (size_t)MU));
-  HIPCHK(c, c->sel.ensure(sizeof(int) * W * (size_t)bmax));
-  HIPCHK(c, c->dv.ensure(sizeof(double) * W * (size_t)bmax * MU));
-  HIPCHK(c, c->de.ensure(sizeof(double) * W * (size_t)bmax));
-  if (store_E) HIPCHK(c, c->dep.ensure(sizeof(double) * W * (size_t)bmax * MU));
-  HIPCHK(c, c->stl.ensure(sizeof(long) * 3 * W));
-  HIPCHK(c, c->ifill.ensure(sizeof(int) * W * (size_t)bmax));
-  const bool lockstep = bmin == 1 && bmax == 1;
-  if (lockstep) HIPCHK(c, c->born.ensure(sizeof(unsigned int) * regions));
-  HIPCHK(c, c->counters.ensure(256));
-  const bool out_dev = is_device_ptr(out), err_dev = err_out && is_device_ptr(err_out);
-  const size_t out_bytes = sizeof(double) * (size_t)n_ctr * M * M;
-  if (!out_dev) HIPCHK(c, c->outs.ensure(out_bytes));
-  if (err_out && !err_dev) HIPCHK(c, c->errs.ensure(out_bytes));
-
   Problem P;
   memset(&P, 0, sizeof P);
   P.entries = c->entries.as<Entry>();
@@ -604,9 +573,73 @@ int paid_integrate(paid_ctx *c, const paid_params *params, int n_params, const d
   P.MU = MU;
   P.ff_identity = identity;
   P.eval_layout = cfg.eval_layout;
+  P.sym = cfg.symmetry;
   if (eval_lds_bytes(P) == 0)
     return fail(c, PAID_EINVAL, "frequency-sum table of %d rows does not fit in LDS (T too small against the band)",
                 P.tab_rows);
+  P.products = leaves_hold_products(P) ? 1 : 0;
+  const int MQ = P.MQ = P.products ? kProd : MU;
+  if ((rc = stage_pair_coefficients(c, P, hff.data())) != PAID_OK) return rc;
+
+  // pool: slots x capacity; with small_regions, large slots (capb) first,
+  // then small ones (cap)
+  const long capb = cfg.max_regions;
+  const bool two = cfg.small_regions > 0 && cfg.small_regions < capb;
+  const long cap = two ? cfg.small_regions : capb;
+  const size_t rec = 16 + 8 * (size_t)MQ + (store_E ? 4 * (size_t)MU : 0);
+  size_t pool_bytes, rest_bytes = 0;  // rest: for the per-slot round buffers (0: unchecked)
+  if (cfg.pool_gib > 0) {
+    pool_bytes = (size_t)(cfg.pool_gib * 1073741824.0);
+  } else {
+    size_t fr = 0, tot = 0;
+    HIPCHK(c, hipMemGetInfo(&fr, &tot));
+    const double avail = (double)(fr + c->code.n + c->key.n + c->Q.n + c->E.n + c->dv.n + c->dep.n);
+    pool_bytes = (size_t)(0.55 * avail);
+    rest_bytes = (size_t)(0.35 * avail);
+  }
+  long Wb = 0;
+  if (two) {
+    const double share = cfg.big_share > 0 ? cfg.big_share : 0.25;
+    Wb = (long)(share * (double)pool_bytes / ((double)capb * rec));
+    if (Wb < 1) Wb = 1;
+    if (Wb > n_ctr) Wb = n_ctr;
+  }
+  const size_t big_bytes = (size_t)Wb * capb * rec;
+  long Ws = cfg.max_active > 0 ? cfg.max_active - Wb
+                               : (pool_bytes > big_bytes ? (long)((pool_bytes - big_bytes) / ((size_t)cap * rec)) : 0);
+  if (Ws > n_ctr) Ws = n_ctr;
+  if (Wb + Ws > 65536) Ws = 65536 - Wb;
+  // the round buffers of every slot (deltas, selections) must fit beside the pool
+  const size_t slot_rest = (size_t)cfg.batch_max * (8 * ((size_t)MQ + (store_E ? MU : 0)) + 16) + 32 * (size_t)MU;
+  if (rest_bytes > 0 && (size_t)(Wb + Ws) * slot_rest > rest_bytes) Ws = (long)(rest_bytes / slot_rest) - Wb;
+  if (Ws < 1) return fail(c, PAID_ENOMEM, "region pool too small for one container of %ld regions", cap);
+  const long W = Wb + Ws;
+  const size_t regions = (size_t)Wb * capb + (size_t)Ws * cap;
+  const int bmax = cfg.batch_max, bmin = cfg.batch;
+  HIPCHK(c, c->code.ensure(sizeof(uint64_t) * regions));
+  HIPCHK(c, c->key.ensure(sizeof(double) * regions));
+  HIPCHK(c, c->Q.ensure(sizeof(double) * regions * MQ));
+  if (store_E) HIPCHK(c, c->E.ensure(sizeof(float) * regions * MU));
+  HIPCHK(c, c->movei.ensure(sizeof(int) * (size_t)(W + Wb + 1)));
+  HIPCHK(c, c->upart.ensure(sizeof(double) * update_scratch_doubles((int)W, MQ, MU)));
+  HIPCHK(c, c->slot_i.ensure(sizeof(int) * (8 * W + 8)));
+  HIPCHK(c, c->slot_d.ensure(sizeof(double) * (W * (size_t)MQ + W)));
+  HIPCHK(c, c->errp.ensure(sizeof(double) * W * (size_t)MU));
+  HIPCHK(c, c->itau.ensure(sizeof(float) * W * (size_t)MU));
+  HIPCHK(c, c->sel.ensure(sizeof(int) * W * (size_t)bmax));
+  HIPCHK(c, c->dv.ensure(sizeof(double) * W * (size_t)bmax * MQ));
+  HIPCHK(c, c->de.ensure(sizeof(double) * W * (size_t)bmax));
+  if (store_E) HIPCHK(c, c->dep.ensure(sizeof(double) * W * (size_t)bmax * MU));
+  HIPCHK(c, c->stl.ensure(sizeof(long) * 3 * W));
+  HIPCHK(c, c->ifill.ensure(sizeof(int) * W * (size_t)bmax));
+  const bool lockstep = bmin == 1 && bmax == 1;
+  if (lockstep) HIPCHK(c, c->born.ensure(sizeof(unsigned int) * regions));
+  HIPCHK(c, c->counters.ensure(256));
+  const bool out_dev = is_device_ptr(out), err_dev = err_out && is_device_ptr(err_out);
+  const size_t out_bytes = sizeof(double) * (size_t)n_ctr * M * M;
+  if (!out_dev) HIPCHK(c, c->outs.ensure(out_bytes));
+  if (err_out && !err_dev) HIPCHK(c, c->errs.ensure(out_bytes));
+
   P.ffc = c->ffc.as<double>();
   P.W = (int)W;
   P.cap = cap;
@@ -631,7 +664,7 @@ int paid_integrate(paid_ctx *c, const paid_params *params, int n_params, const d
   P.woff = si + 6 * W;  // W + 1 entries
   P.sel = c->sel.as<int>();
   P.val = c->slot_d.as<double>();
-  P.err = c->slot_d.as<double>() + W * (size_t)MU;
+  P.err = c->slot_d.as<double>() + W * (size_t)MQ;
   P.errp = store_E ? c->errp.as<double>() : nullptr;
   P.itau = c->itau.as<float>();
   P.dv = c->dv.as<double>();
@@ -681,7 +714,6 @@ int paid_integrate(paid_ctx *c, const paid_params *params, int n_params, const d
   const bool want_labels = c->lab_out != nullptr || c->feat_out != nullptr;
   if (cfg.symmetry && (c->seed_on || want_labels))
     return fail(c, PAID_EINVAL, "the half-zone mode takes neither a seed model nor tree labels");
-  P.sym = cfg.symmetry;
   double seed_s = 0.0;
   if (c->seed_on || want_labels) {
     auto ts = std::chrono::steady_clock::now();
@@ -954,34 +986,6 @@ int paid_children_eval(paid_ctx *c, const paid_params *p, const double *l, unsig
                                    channel == PAID_PH ? 1 : 0, c->stream));
   const int M = n_ff, MU = M * (M + 1) / 2;
   const long cap = 4L * n;
-  DevBuf code, key, Q, si, dv, de, itau, cnt, ctrid, ifl;
-  HIPCHK(c, code.ensure(sizeof(uint64_t) * cap));
-  HIPCHK(c, key.ensure(sizeof(double) * cap));
-  HIPCHK(c, Q.ensure(sizeof(double) * cap * MU));
-  HIPCHK(c, si.ensure(sizeof(int) * (8 + (size_t)n)));
-  HIPCHK(c, dv.ensure(sizeof(double) * (size_t)n * MU));
-  HIPCHK(c, de.ensure(sizeof(double) * (size_t)n));
-  HIPCHK(c, itau.ensure(sizeof(float) * MU));
-  HIPCHK(c, cnt.ensure(256));
-  HIPCHK(c, ifl.ensure(sizeof(int) * (size_t)n));
-  HIPCHK(c, hipMemsetAsync(Q.p, 0, sizeof(double) * cap * MU, c->stream));
-  HIPCHK(c, hipMemsetAsync(key.p, 0, sizeof(double) * cap, c->stream));
-  HIPCHK(c, hipMemcpyAsync(code.p, pc.data(), sizeof(uint64_t) * n, hipMemcpyHostToDevice, c->stream));
-  // slot state: cid 0, state active, nleaf n, selcnt n, woff {0, n}, flags, depth; sel = 0..n-1
-  std::vector<int> hs(8 + (size_t)n, 0);
-  hs[0] = 0;      // cid
-  hs[1] = SLOT_ACTIVE;
-  hs[2] = n;      // nleaf
-  hs[3] = n;      // selcnt
-  hs[4] = 0;      // flags
-  hs[5] = 0;      // depth
-  hs[6] = 0;      // woff[0]
-  hs[7] = n;      // woff[1]
-  for (int i = 0; i < n; ++i) hs[8 + i] = i;
-  HIPCHK(c, hipMemcpyAsync(si.p, hs.data(), sizeof(int) * hs.size(), hipMemcpyHostToDevice, c->stream));
-  int hcnt[64] = {0};
-  hcnt[4 + 2] = n;  // counters[2]: work items
-  HIPCHK(c, hipMemcpyAsync(cnt.p, hcnt, sizeof hcnt, hipMemcpyHostToDevice, c->stream));
   Problem P;
   memset(&P, 0, sizeof P);
   P.entries = c->entries.as<Entry>();
@@ -1007,6 +1011,37 @@ int paid_children_eval(paid_ctx *c, const paid_params *p, const double *l, unsig
   if (eval_lds_bytes(P) == 0)
     return fail(c, PAID_EINVAL, "frequency-sum table of %d rows does not fit in LDS (T too small against the band)",
                 P.tab_rows);
+  P.products = leaves_hold_products(P) ? 1 : 0;
+  const int MQ = P.MQ = P.products ? kProd : MU;
+  if ((rc = stage_pair_coefficients(c, P, hff.data())) != PAID_OK) return rc;
+  DevBuf code, key, Q, si, dv, de, itau, cnt, ctrid, ifl;
+  HIPCHK(c, code.ensure(sizeof(uint64_t) * cap));
+  HIPCHK(c, key.ensure(sizeof(double) * cap));
+  HIPCHK(c, Q.ensure(sizeof(double) * cap * MQ));
+  HIPCHK(c, si.ensure(sizeof(int) * (8 + (size_t)n)));
+  HIPCHK(c, dv.ensure(sizeof(double) * (size_t)n * MQ));
+  HIPCHK(c, de.ensure(sizeof(double) * (size_t)n));
+  HIPCHK(c, itau.ensure(sizeof(float) * MU));
+  HIPCHK(c, cnt.ensure(256));
+  HIPCHK(c, ifl.ensure(sizeof(int) * (size_t)n));
+  HIPCHK(c, hipMemsetAsync(Q.p, 0, sizeof(double) * cap * MQ, c->stream));
+  HIPCHK(c, hipMemsetAsync(key.p, 0, sizeof(double) * cap, c->stream));
+  HIPCHK(c, hipMemcpyAsync(code.p, pc.data(), sizeof(uint64_t) * n, hipMemcpyHostToDevice, c->stream));
+  // slot state: cid 0, state active, nleaf n, selcnt n, woff {0, n}, flags, depth; sel = 0..n-1
+  std::vector<int> hs(8 + (size_t)n, 0);
+  hs[0] = 0;      // cid
+  hs[1] = SLOT_ACTIVE;
+  hs[2] = n;      // nleaf
+  hs[3] = n;      // selcnt
+  hs[4] = 0;      // flags
+  hs[5] = 0;      // depth
+  hs[6] = 0;      // woff[0]
+  hs[7] = n;      // woff[1]
+  for (int i = 0; i < n; ++i) hs[8 + i] = i;
+  HIPCHK(c, hipMemcpyAsync(si.p, hs.data(), sizeof(int) * hs.size(), hipMemcpyHostToDevice, c->stream));
+  int hcnt[64] = {0};
+  hcnt[4 + 2] = n;  // counters[2]: work items
+  HIPCHK(c, hipMemcpyAsync(cnt.p, hcnt, sizeof hcnt, hipMemcpyHostToDevice, c->stream));
   P.ffc = c->ffc.as<double>();
   P.W = 1;
   P.cap = cap;
@@ -1030,15 +1065,23 @@ int paid_children_eval(paid_ctx *c, const paid_params *p, const double *l, unsig
   P.counters = cnt.as<int>() + 4;
   P.ifill = ifl.as<int>();
   HIPCHK(c, launch_eval(P, n < 4096 ? n : 4096, c->stream));
-  std::vector<double> hQ((size_t)cap * MU), hk(cap);
-  HIPCHK(c, hipMemcpyAsync(hQ.data(), Q.p, sizeof(double) * cap * MU, hipMemcpyDeviceToHost, c->stream));
+  std::vector<double> hQ((size_t)cap * MQ), hk(cap);
+  HIPCHK(c, hipMemcpyAsync(hQ.data(), Q.p, sizeof(double) * cap * MQ, hipMemcpyDeviceToHost, c->stream));
   HIPCHK(c, hipMemcpyAsync(hk.data(), key.p, sizeof(double) * cap, hipMemcpyDeviceToHost, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
   std::vector<double> oq((size_t)n * 4 * MU), oe((size_t)n * 4);
   for (int r = 0; r < n; ++r)
     for (int ch = 0; ch < 4; ++ch) {
       long ri = ch == 0 ? r : n + 3L * r + (ch - 1);
-      memcpy(&oq[((size_t)r * 4 + ch) * MU], &hQ[ri * MU], sizeof(double) * MU);
+      double *dst = &oq[((size_t)r * 4 + ch) * MU];
+      const double *src = &hQ[ri * MQ];
+      if (P.products) {
+        int k = 0;
+        for (int m = 0; m < 9; ++m)
+          for (int n2 = m; n2 < 9; ++n2) dst[k++] = pair_of_products(src, m, n2);
+      } else {
+        memcpy(dst, src, sizeof(double) * MU);
+      }
       oe[(size_t)r * 4 + ch] = hk[ri];
     }
   HIPCHK(c, hipMemcpy(q2n, oq.data(), sizeof(double) * oq.size(), hipMemcpyDefault));

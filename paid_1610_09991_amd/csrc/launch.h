@@ -56,6 +56,11 @@ struct Problem {      // everything the round kernels need, passed by value
   int L, nb, MB, M, MU;       // box order, harmonics per axis, box size, n_ff, pairs
   int ff_identity;            // 1: form factors are the box basis itself
   const double *ffc;          // [M][MB]
+  // values of a leaf: MQ doubles, the MU form-factor pairs, or (products = 1)
+  // the 25 product integrals of the 9-function box, from which a pair is formed
+  // where it is needed (slot_pair)
+  int MQ, products;
+  const double *pcoef;        // [MU][25] pairs over the product integrals (general sets, L <= 1)
   // pool
   int W;                      // slots
   long cap;                   // regions per slot (per small slot when Wb > 0)
@@ -71,19 +76,19 @@ struct Problem {      // everything the round kernels need, passed by value
   int eval_layout;            // 0: the fastest evaluation kernel for the basis, 1: one wave per parent
   uint64_t *code;             // [regions], slot s from slot_base(s)
   double *key;                // [regions]
-  double *Q;                  // [regions*MU]
+  double *Q;                  // [regions*MQ]
   float *E;                   // [regions*MU] or NULL
   // slot state
   int *cid, *state, *nleaf, *selcnt, *sel, *woff;  // sel: [W*bmax], woff: [W+1]
   int *flags;                 // [W]: bit0 = converged, bit1 = budget hit
-  double *val;                // [W*MU]
+  double *val;                // [W*MQ]
   double *err;                // [W]   (sum of keys)
   double *errp;               // [W*MU] per pair (when E != NULL)
   float *itau;                // [W*MU] key weights (per-integral mode)
-  double *dv;                 // [W*bmax*MU]
+  double *dv;                 // [W*bmax*MQ]
   double *de;                 // [W*bmax]
   double *dep;                // [W*bmax*MU] (when E != NULL)
-  double *upart;              // [W][chunks][2*MU + 2] chunk sums of the deltas
+  double *upart;              // [W][chunks][MQ + MU + 2] chunk sums of the deltas
   long *st_rounds, *st_splits;  // [W]
   int *st_depth;              // [W]
   // queue and global counters
@@ -125,6 +130,15 @@ __host__ __device__ inline long slot_base(const Problem &P, int s) {
 }
 __host__ __device__ inline long slot_cap(const Problem &P, int s) { return s < P.Wb ? P.capb : P.cap; }
 
+// running value of pair pid (p <= q) of slot s
+__device__ inline double slot_pair(const Problem &P, int s, int pid) {
+  const double *v = P.val + (long)s * P.MQ;
+  if (!P.products) return v[pid];
+  int m = 0, k = pid;
+  while (k >= 9 - m) { k -= 9 - m; ++m; }
+  return pair_of_products(v, m, m + k);
+}
+
 constexpr int kSeedG = 16;                    // cells per axis of the density grid
 constexpr int kPyr = 1 + 4 + 16 + 64 + 256;   // pyramid levels 0..4
 constexpr int kFlagSeed = 4;                  // slot flag: seed phase
@@ -164,7 +178,7 @@ __device__ inline bool seed_split(const Problem &P, int s, uint64_t code) {
 
 hipError_t launch_admit(const Problem &p, hipStream_t s);
 // doubles of the chunk sums of the per-parent deltas (Problem::upart)
-size_t update_scratch_doubles(int W, int MU);
+size_t update_scratch_doubles(int W, int MQ, int MU);
 // moves of waiting containers from small to large slots (p.Wb > 0)
 hipError_t launch_move(const Problem &p, hipStream_t s);
 // predicted leaves of every parameter row (sum over its containers and cells
@@ -173,6 +187,11 @@ hipError_t launch_seed_rowsize(const float *y, int n_rows, int per_row, double *
 hipError_t launch_root(const Problem &p, hipStream_t s);
 hipError_t launch_select(const Problem &p, hipStream_t s);
 hipError_t launch_worklist(const Problem &p, hipStream_t s);
+// whether leaves hold the 25 product integrals instead of the pairs (by the
+// static description alone)
+bool leaves_hold_products(const Problem &p);
+// whether the evaluation reads Problem::pcoef
+bool needs_pair_coefficients(const Problem &p);
 // dynamic LDS bytes of the evaluation kernel for p (0: the table does not fit)
 size_t eval_lds_bytes(const Problem &p);
 // evaluation workgroups that fit on one compute unit at once for p

@@ -89,6 +89,70 @@ struct Ctr {          // one container (parameter row, transfer momentum, channe
 };
 
 // ---------------------------------------------------------------------------
+// Products of the 9-function box basis.  The products of two box harmonics
+// u_a u_c (u_0 = 1, u_1 = sqrt2 cos, u_2 = sqrt2 sin) lie in the span of five
+// functions phi = {1, sqrt2 cos, sqrt2 sin, cos 2x, sin 2x} (2 cos^2 = 1 +
+// cos 2x, 2 cos sin = sin 2x, 2 sin^2 = 1 - cos 2x), so every pair of box
+// functions of a rectangle is a signed sum of one to four of the 25 integrals
+// I_jk = int g phi_j(x) phi_k(y), and every pair of form factors over the
+// 9-function box (or its first function) a combination of them.
+constexpr int kPhi = 5, kProd = kPhi * kPhi;
+constexpr int kPairs9 = 45;  // pairs of the 9 box functions
+
+// phi index and sign of the terms of the product u_a u_c (a <= c)
+struct Terms {
+  int n, j0, s0, j1, s1;
+};
+__host__ __device__ constexpr Terms prod_terms(int a, int c) {
+  return (a == 0 && c == 0) ? Terms{1, 0, 1, 0, 0}
+       : (a == 0 && c == 1) ? Terms{1, 1, 1, 0, 0}
+       : (a == 0 && c == 2) ? Terms{1, 2, 1, 0, 0}
+       : (a == 1 && c == 1) ? Terms{2, 0, 1, 3, 1}
+       : (a == 1 && c == 2) ? Terms{1, 4, 1, 0, 0}
+                            : Terms{2, 0, 1, 3, -1};  // (2, 2)
+}
+
+// the 45 box pairs (m, n), m <= n, m = 3 a + b: x terms of u_am u_an
+// (phi index j0, optional j1 with sign) and y terms of u_bm u_bn; -1 = none
+struct PairTab {
+  signed char t[kPairs9][6];  // jx0, jx1, sx1, ky0, ky1, sy1
+};
+__host__ __device__ constexpr PairTab make_pair_tab() {
+  PairTab T{};
+  int p = 0;
+  for (int m = 0; m < 9; ++m)
+    for (int n = m; n < 9; ++n) {
+      const int am = m / 3, bm = m % 3, an = n / 3, bn = n % 3;
+      const Terms tx = prod_terms(am < an ? am : an, am < an ? an : am);
+      const Terms ty = prod_terms(bm < bn ? bm : bn, bm < bn ? bn : bm);
+      T.t[p][0] = (signed char)tx.j0;
+      T.t[p][1] = (signed char)(tx.n == 2 ? tx.j1 : -1);
+      T.t[p][2] = (signed char)tx.s1;
+      T.t[p][3] = (signed char)ty.j0;
+      T.t[p][4] = (signed char)(ty.n == 2 ? ty.j1 : -1);
+      T.t[p][5] = (signed char)ty.s1;
+      ++p;
+    }
+  return T;
+}
+
+// box pair (m, n) from the 25 product integrals
+template <class T>
+__host__ __device__ inline double pair_of_products(const T &I, int m, int n) {
+  const int am = m / 3, bm = m % 3, an = n / 3, bn = n % 3;
+  const Terms tx = prod_terms(am < an ? am : an, am < an ? an : am);
+  const Terms ty = prod_terms(bm < bn ? bm : bn, bm < bn ? bn : bm);
+  double v = I[kPhi * tx.j0 + ty.j0];
+  if (ty.n == 2) v += ty.s1 * I[kPhi * tx.j0 + ty.j1];
+  if (tx.n == 2) {
+    double u = I[kPhi * tx.j1 + ty.j0];
+    if (ty.n == 2) u += ty.s1 * I[kPhi * tx.j1 + ty.j1];
+    v += tx.s1 * u;
+  }
+  return v;
+}
+
+// ---------------------------------------------------------------------------
 // Region codes: depth in bits 56..63, ix in 28..55, iy in 0..27.
 __host__ __device__ inline uint64_t make_code(int d, uint64_t ix, uint64_t iy) {
   return ((uint64_t)d << 56) | (ix << 28) | iy;

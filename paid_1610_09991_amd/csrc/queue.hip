@@ -176,7 +176,7 @@ __device__ int tolerance_test(const Problem &P, int s, double *shd, double &eps,
   const int t = threadIdx.x;
   double a = 0.0, mx = 0.0;
   for (int pid = t; pid < P.MU; pid += blockDim.x) {
-    double v = fabs(P.val[(long)s * P.MU + pid]);
+    double v = fabs(slot_pair(P, s, pid));
     a += v;
     mx = fmax(mx, v);
   }
@@ -187,7 +187,7 @@ __device__ int tolerance_test(const Problem &P, int s, double *shd, double &eps,
     } else {  // weighted sums (the keys carry the same weights)
       double aw = 0.0;
       for (int pid = t; pid < P.MU; pid += blockDim.x)
-        aw += (double)P.itau[(long)s * P.MU + pid] * fabs(P.val[(long)s * P.MU + pid]);
+        aw += (double)P.itau[(long)s * P.MU + pid] * fabs(slot_pair(P, s, pid));
       eps = fmax(P.atol, P.rtol * block_sum(aw, shd));
     }
     const double E = P.err[s];
@@ -198,7 +198,7 @@ __device__ int tolerance_test(const Problem &P, int s, double *shd, double &eps,
   double ex = 0.0;
   int bad = 0, near = 0;
   for (int pid = t; pid < P.MU; pid += blockDim.x) {
-    double v = fabs(P.val[(long)s * P.MU + pid]);
+    double v = fabs(slot_pair(P, s, pid));
     double tau = fmax(P.atol, P.rtol * fmax(v, P.nu * vmax));
     double e = P.errp[(long)s * P.MU + pid];
     if (!(e <= tau)) {  // a NaN error fails the test
@@ -593,7 +593,7 @@ __device__ inline int upd_chunks(int k) {
   return c < kUpdChunks ? c : kUpdChunks;
 }
 
-// one chunk's sums: [MU] values, [MU] per-pair errors, key delta, filled items
+// one chunk's sums: [MQ] values, [MU] per-pair errors, key delta, filled items
 __global__ void __launch_bounds__(kSelThreads) k_update_part(Problem P) {
   __shared__ double shd[2 * kSelThreads];
   const int s = blockIdx.x, c = blockIdx.y, t = threadIdx.x;
@@ -602,10 +602,10 @@ __global__ void __launch_bounds__(kSelThreads) k_update_part(Problem P) {
   if (c >= nch) return;
   const int per = (k + nch - 1) / nch, r0 = c * per, r1 = r0 + per < k ? r0 + per : k;
   const long it0 = (long)s * P.bmax + r0;
-  const long MU = P.MU;
-  double *part = P.upart + ((long)s * kUpdChunks + c) * (2 * MU + 2);
-  column_sums(P.dv + it0 * MU, r1 - r0, P.MU, part, shd);
-  if (P.dep) column_sums(P.dep + it0 * MU, r1 - r0, P.MU, part + MU, shd);
+  const long MU = P.MU, MQ = P.MQ;
+  double *part = P.upart + ((long)s * kUpdChunks + c) * (MQ + MU + 2);
+  column_sums(P.dv + it0 * MQ, r1 - r0, P.MQ, part, shd);
+  if (P.dep) column_sums(P.dep + it0 * MU, r1 - r0, P.MU, part + MQ, shd);
   double de = 0.0, nf = 0.0;
   for (int r = t; r < r1 - r0; r += blockDim.x) {
     de += P.de[it0 + r];
@@ -614,8 +614,8 @@ __global__ void __launch_bounds__(kSelThreads) k_update_part(Problem P) {
   const double d = block_sum(de, shd);
   const double fills = block_sum(nf, shd);
   if (t == 0) {
-    part[2 * MU] = d;
-    part[2 * MU + 1] = fills;
+    part[MQ + MU] = d;
+    part[MQ + MU + 1] = fills;
   }
 }
 
@@ -625,23 +625,24 @@ __global__ void __launch_bounds__(kSelThreads) k_update(Problem P) {
   const int k = P.selcnt[s];
   if (k == 0) return;
   const int nch = upd_chunks(k);
-  const long MU = P.MU;
-  const double *part = P.upart + (long)s * kUpdChunks * (2 * MU + 2);
-  for (long pid = t; pid < MU; pid += blockDim.x) {
-    double v = part[pid];
-    for (int c = 1; c < nch; ++c) v += part[c * (2 * MU + 2) + pid];
-    P.val[(long)s * MU + pid] += v;
-    if (P.dep) {  // per-pair error sums are kept where the deltas carry them
-      double e = part[MU + pid];
-      for (int c = 1; c < nch; ++c) e += part[c * (2 * MU + 2) + MU + pid];
+  const long MU = P.MU, MQ = P.MQ, len = MQ + MU + 2;
+  const double *part = P.upart + (long)s * kUpdChunks * len;
+  for (long i = t; i < MQ; i += blockDim.x) {
+    double v = part[i];
+    for (int c = 1; c < nch; ++c) v += part[c * len + i];
+    P.val[(long)s * MQ + i] += v;
+  }
+  if (P.dep)  // per-pair error sums are kept where the deltas carry them
+    for (long pid = t; pid < MU; pid += blockDim.x) {
+      double e = part[MQ + pid];
+      for (int c = 1; c < nch; ++c) e += part[c * len + MQ + pid];
       P.errp[(long)s * MU + pid] += e;
     }
-  }
   if (t == 0) {
-    double d = part[2 * MU], fills = part[2 * MU + 1];
+    double d = part[MQ + MU], fills = part[MQ + MU + 1];
     for (int c = 1; c < nch; ++c) {
-      d += part[c * (2 * MU + 2) + 2 * MU];
-      fills += part[c * (2 * MU + 2) + 2 * MU + 1];
+      d += part[c * len + MQ + MU];
+      fills += part[c * len + MQ + MU + 1];
     }
     P.err[s] += d;
     P.st_evals[s] += (long)fills * (kNX * kNX);
@@ -694,8 +695,15 @@ __global__ void __launch_bounds__(kSelThreads) k_finalize(Problem P) {
         cd[0] = code_depth(code);
         cd[1] = (int)code_ix(code);
         cd[2] = (int)code_iy(code);
-        for (int k = 0; k < P.MU; ++k)
-          P.leaf_q[(c * P.leaf_cap + i) * P.MU + k] = P.Q[(base + i) * P.MU + k];
+        double *lq = P.leaf_q + (c * P.leaf_cap + i) * P.MU;
+        const double *v = P.Q + (base + i) * P.MQ;
+        if (P.products) {
+          int k = 0;
+          for (int m = 0; m < 9; ++m)
+            for (int n2 = m; n2 < 9; ++n2) lq[k++] = pair_of_products(v, m, n2);
+        } else {
+          for (int k = 0; k < P.MU; ++k) lq[k] = v[k];
+        }
       } else {
         cd[0] = cd[1] = cd[2] = -1;
       }
@@ -706,7 +714,7 @@ __global__ void __launch_bounds__(kSelThreads) k_finalize(Problem P) {
     int p = 0, k = pid;
     while (k >= M - p) { k -= M - p; ++p; }
     int q = p + k;
-    double v = P.val[(long)s * P.MU + pid];
+    double v = slot_pair(P, s, pid);
     P.out[c * M * M + p * M + q] = v;
     P.out[c * M * M + q * M + p] = v;
     if (P.err_out) {
@@ -769,11 +777,10 @@ __global__ void k_move_copy(Problem P) {
     P.key[db + i] = P.key[sb + i];
     if (P.born) P.born[db + i] = P.born[sb + i];
   }
-  const long MU = P.MU;
-  for (long e = i0 * MU + threadIdx.x; e < i1 * MU; e += blockDim.x) {
-    P.Q[db * MU + e] = P.Q[sb * MU + e];
-    if (P.E) P.E[db * MU + e] = P.E[sb * MU + e];
-  }
+  const long MU = P.MU, MQ = P.MQ;
+  for (long e = i0 * MQ + threadIdx.x; e < i1 * MQ; e += blockDim.x) P.Q[db * MQ + e] = P.Q[sb * MQ + e];
+  if (P.E)
+    for (long e = i0 * MU + threadIdx.x; e < i1 * MU; e += blockDim.x) P.E[db * MU + e] = P.E[sb * MU + e];
 }
 
 // the moving containers' sums and bookkeeping; the large slot becomes active
@@ -781,9 +788,9 @@ __global__ void k_move_copy(Problem P) {
 __global__ void k_move_finish(Problem P) {
   const int b = blockIdx.x, src = P.promo[b], t = threadIdx.x;
   if (src < 0) return;
-  const long MU = P.MU;
+  const long MU = P.MU, MQ = P.MQ;
+  for (long i = t; i < MQ; i += blockDim.x) P.val[(long)b * MQ + i] = P.val[(long)src * MQ + i];
   for (long pid = t; pid < MU; pid += blockDim.x) {
-    P.val[(long)b * MU + pid] = P.val[(long)src * MU + pid];
     P.itau[(long)b * MU + pid] = P.itau[(long)src * MU + pid];
     if (P.errp) P.errp[(long)b * MU + pid] = P.errp[(long)src * MU + pid];
   }
@@ -854,7 +861,7 @@ hipError_t launch_update(const Problem &p, hipStream_t s) {
   return hipGetLastError();
 }
 
-size_t update_scratch_doubles(int W, int MU) { return (size_t)W * kUpdChunks * (2 * (size_t)MU + 2); }
+size_t update_scratch_doubles(int W, int MQ, int MU) { return (size_t)W * kUpdChunks * ((size_t)MQ + MU + 2); }
 hipError_t launch_finalize(const Problem &p, hipStream_t s) {
   hipLaunchKernelGGL(k_finalize, dim3(p.W), dim3(kSelThreads), 0, s, p);
   return hipGetLastError();

@@ -20,6 +20,8 @@
 // workgroup and shared by its waves.
 #include <math.h>
 
+#include <type_traits>
+
 #include "launch.h"
 
 namespace paid {
@@ -570,7 +572,7 @@ __device__ double store_region(WaveLds<L> &S, const Problem &P, int s, long ri, 
   double part = 0.0;
   for (int pid = lane; pid < P.MU; pid += 64) {
     double q = S.cq[pid], e = fabs(S.ce[pid]);
-    P.Q[base * P.MU + pid] = q;
+    if (!P.products) P.Q[base * P.MQ + pid] = q;
     if (P.E) P.E[base * P.MU + pid] = err_f32(e);
     part += (P.err_mode != 0) ? e * (double)P.itau[(long)s * P.MU + pid] : e;
   }
@@ -621,10 +623,9 @@ template <int L>
 __device__ void store_zero(const Problem &P, int s, long ri, uint64_t code) {
   const int lane = lane_id();
   const long base = slot_base(P, s) + ri;
-  for (int pid = lane; pid < P.MU; pid += 64) {
-    P.Q[base * P.MU + pid] = 0.0;
-    if (P.E) P.E[base * P.MU + pid] = 0.0f;
-  }
+  for (int i = lane; i < P.MQ; i += 64) P.Q[base * P.MQ + i] = 0.0;
+  if (P.E)
+    for (int pid = lane; pid < P.MU; pid += 64) P.E[base * P.MU + pid] = 0.0f;
   if (lane == 0) {
     P.key[base] = 0.0;
     P.code[base] = code;
@@ -727,10 +728,9 @@ __global__ void __launch_bounds__(64) k_root(Problem P) {
   const int nroot = P.sym ? 2 : 1;  // leaves the container starts from
   if (placeholder) {
     store_zero<L>(P, s, 0, make_code(0, 0, 0));
-    for (int pid = threadIdx.x; pid < P.MU; pid += 64) {
-      P.val[(long)s * P.MU + pid] = 0.0;
-      if (P.errp) P.errp[(long)s * P.MU + pid] = 0.0;
-    }
+    for (int i = threadIdx.x; i < P.MQ; i += 64) P.val[(long)s * P.MQ + i] = 0.0;
+    if (P.errp)
+      for (int pid = threadIdx.x; pid < P.MU; pid += 64) P.errp[(long)s * P.MU + pid] = 0.0;
   } else {
     const Ctr C = P.ctr[c];
     const Entry E = P.entries[C.entry];
@@ -745,9 +745,19 @@ __global__ void __launch_bounds__(64) k_root(Problem P) {
       for (int pid = threadIdx.x; pid < P.MU; pid += 64) {
         const long o = (long)s * P.MU + pid;
         const double e = (double)err_f32(fabs(S.ce[pid]));
-        P.val[o] = h ? P.val[o] + S.cq[pid] : S.cq[pid];
+        if (!P.products) P.val[(long)s * P.MQ + pid] = h ? P.val[(long)s * P.MQ + pid] + S.cq[pid] : S.cq[pid];
         if (P.errp) P.errp[o] = h ? P.errp[o] + e : e;
       }
+      if constexpr (L == 1 && GRAM == kSep)
+        if (P.products && threadIdx.x < kProd) {
+          // the product integrals from the x-sums over the harmonics' products
+          // (phi_3 = u_1 u_1 - u_0 u_0; the others are products themselves)
+          const int j = threadIdx.x / kPhi, k = threadIdx.x % kPhi;
+          auto sum_y = [&](int x) { return k == 3 ? S.g2[x * 6 + 3] - S.g2[x * 6] : S.g2[x * 6 + k]; };
+          const double v = ((0.5 * wr) * (0.5 * wr) / (4.0 * kPi * kPi)) * (j == 3 ? sum_y(3) - sum_y(0) : sum_y(j));
+          P.Q[(slot_base(P, s) + h) * P.MQ + threadIdx.x] = v;
+          P.val[(long)s * P.MQ + threadIdx.x] = v;
+        }
       wave_sync();
     }
   }
@@ -1036,16 +1046,12 @@ __global__ void __launch_bounds__(256) k_children(Problem P) {
 }
 
 // ---------------------------------------------------------------- two lanes per child
-// Region evaluation for the 9-function box basis (L = 1) with the separable
-// FP64 projection, arranged so that every sum stays in registers: a wave
-// holds 8 work items (parents); lane 8 it + 2 ch + h evaluates child ch of
-// item it together with its partner lane (h = 0, 1).  The products of two
-// box harmonics u_a u_c (u_0 = 1, u_1 = sqrt2 cos, u_2 = sqrt2 sin) lie in
-// the span of five functions phi = {1, sqrt2 cos, sqrt2 sin, cos 2x,
-// sin 2x} (2 cos^2 = 1 + cos 2x, 2 cos sin = sin 2x, 2 sin^2 = 1 - cos 2x),
-// so every pair of box functions of a rectangle is a signed sum of the 25
-// integrals I_jk = int g phi_j(x) phi_k(y).  Lane h = 0 accumulates I for
-// the fine rule (Q_2N); lane h = 1 accumulates the same sums with the weight
+// Region evaluation for form factors over the 9-function box (L <= 1) with the
+// separable FP64 projection, arranged so that every sum stays in registers: a
+// wave holds 8 work items (parents); lane 8 it + 2 ch + h evaluates child ch of
+// item it together with its partner lane (h = 0, 1).  Every pair of form
+// factors of a rectangle is a combination of the 25 product integrals I_jk =
+// int g phi_j(x) phi_k(y).  Lane h = 0 accumulates I for the fine rule (Q_2N); lane h = 1 accumulates the same sums with the weight
 // difference of the two rules (E = Q_2N - Q_N, the error estimate), so the
 // key of the child (sum over pairs of |E|) needs no lanes but its own.
 // The two lanes of a child share its 81 nodes column by column: lane 0
@@ -1062,50 +1068,22 @@ constexpr int kYRow = 6;               // doubles per node row: C, D, phi_1..phi
 // that the blocks the lanes of a wave read at one time fall on distinct banks
 constexpr int kYBlock = kNF * kYRow + 1;
 constexpr int kYDoubles = kItems * 2 * kYBlock;  // per-wave LDS: rows of both child rows
-constexpr int kPairs = 45;             // pairs of the 9 box functions
-// per-wave LDS: the node rows while the sums run, then (in the same space)
-// per item the parent's Q, E and key weights for the records
-__host__ __device__ constexpr int wave_doubles(bool with_e, bool with_w) {
-  const int par = kItems * kPairs * (1 + (with_e ? 1 : 0) + (with_w ? 1 : 0));
-  return par > kYDoubles ? par : kYDoubles;
+// records are staged in LDS, kStage values of each of the wave's 32 children at
+// a time (an odd stride: the children's lanes write to distinct banks)
+constexpr int kChildren = 4 * kItems;
+constexpr int kStage = kProd;
+static_assert(kStage & 1, "bank spread of the staged records");
+// per-wave LDS: the node rows while the sums run, then in the same space the
+// staged records (errors of the box basis after its values; of a general set
+// beside them); behind it the children's and items' places and the key weights
+__host__ __device__ constexpr int area_doubles(bool with_e, bool general) {
+  const int rec = kChildren * kStage + (with_e && general ? kChildren * kStage / 2 : 0);
+  return rec > kYDoubles ? rec : kYDoubles;
 }
-
-// phi index and sign of the terms of the product u_a u_c (a <= c)
-struct Terms {
-  int n, j0, s0, j1, s1;
-};
-__host__ __device__ constexpr Terms prod_terms(int a, int c) {
-  return (a == 0 && c == 0) ? Terms{1, 0, 1, 0, 0}
-       : (a == 0 && c == 1) ? Terms{1, 1, 1, 0, 0}
-       : (a == 0 && c == 2) ? Terms{1, 2, 1, 0, 0}
-       : (a == 1 && c == 1) ? Terms{2, 0, 1, 3, 1}
-       : (a == 1 && c == 2) ? Terms{1, 4, 1, 0, 0}
-                            : Terms{2, 0, 1, 3, -1};  // (2, 2)
+__host__ __device__ constexpr int wave_doubles(bool with_e, bool with_w, bool general) {
+  return area_doubles(with_e, general) + kChildren + kItems + (with_w ? kItems * kPairs9 / 2 : 0);
 }
-
-// the 45 box pairs (m, n), m <= n, m = 3 a + b: x terms of u_am u_an
-// (phi index j0, optional j1 with sign) and y terms of u_bm u_bn; -1 = none
-struct PairTab {
-  signed char t[45][6];  // jx0, jx1, sx1, ky0, ky1, sy1
-};
-__host__ __device__ constexpr PairTab make_pair_tab() {
-  PairTab T{};
-  int p = 0;
-  for (int m = 0; m < 9; ++m)
-    for (int n = m; n < 9; ++n) {
-      const int am = m / 3, bm = m % 3, an = n / 3, bn = n % 3;
-      const Terms tx = prod_terms(am < an ? am : an, am < an ? an : am);
-      const Terms ty = prod_terms(bm < bn ? bm : bn, bm < bn ? bn : bm);
-      T.t[p][0] = (signed char)tx.j0;
-      T.t[p][1] = (signed char)(tx.n == 2 ? tx.j1 : -1);
-      T.t[p][2] = (signed char)tx.s1;
-      T.t[p][3] = (signed char)ty.j0;
-      T.t[p][4] = (signed char)(ty.n == 2 ? ty.j1 : -1);
-      T.t[p][5] = (signed char)ty.s1;
-      ++p;
-    }
-  return T;
-}
+static_assert(kChildren * kPairs9 / 2 <= kYDoubles, "the box basis' errors fit in the area");
 
 // sum of v over the four children of the item, the same in all lanes of the
 // item with the same h: ((c0 + c1) + (c2 + c3)) with a + b = b + a exactly
@@ -1162,7 +1140,9 @@ __device__ inline double wave_uniform(double v) {
 // integrand.  WE: per-pair errors are stored (FP32 records and deltas);
 // otherwise the children's errors only form their keys.  WW: the keys weigh
 // the pairs (per-integral and weighted modes); otherwise they are plain sums.
-template <bool BUB, bool WE, bool WW>
+// GEN: general form factors (pairs from P.pcoef); otherwise the box basis
+// itself, whose leaves hold the product integrals.
+template <bool BUB, bool WE, bool WW, bool GEN>
 __device__ void lpc_group(const Problem &P, int erow, const double *tab, double *Yw, int g0,
                           int gend, int s0) {
   using namespace lpc;
@@ -1353,21 +1333,13 @@ __device__ void lpc_group(const Problem &P, int erow, const double *tab, double 
   // registers across the loops above
   asm volatile("" ::: "memory");
 
-  // ---- records: lane 0 writes the child's Q_2N, lane 1 its |E| and key;
-  // the lanes of child 0 write the item's deltas (children minus parent, the
-  // parent's values from LDS), summed over the four children
+  // ---- records.  Lane 0 of a child holds its Q_2N, lane 1 its E.  Values pass
+  // through LDS, so that consecutive lanes store consecutive doubles of a
+  // record (children of neighbouring items are neighbours in the pool) and the
+  // items' deltas (children minus parent) are sums over the staged values.
+  // Stored straight from the lanes, each value is a write of its own in L2 (32
+  // lanes, 32 records): 236 requests a parent kept L2 busy 95% of the time.
   const LpcItem q = lpc_item(P, w, s0);
-  // the parents' values (their records are overwritten by child 0 below):
-  // Q, and E and the key weights where the mode uses them, in the LDS that
-  // held the node rows
-  double *PQ = Yw, *PE = PQ + kItems * lpc::kPairs;
-  double *PW = PE + (P.E ? kItems * lpc::kPairs : 0);
-  for (int k = lane & 7; k < MU; k += 8) {
-    PQ[it * lpc::kPairs + k] = P.Q[q.pbase * MU + k];
-    if (P.E) PE[it * lpc::kPairs + k] = (double)P.E[q.pbase * MU + k];
-    if (P.err_mode != 0) PW[it * lpc::kPairs + k] = (double)P.itau[(long)q.s * MU + k];
-  }
-  wave_sync();
   const bool valid = g0 + it < gend;
   const int dd = code_depth(q.pc);
   const uint64_t ix = code_ix(q.pc), iy = code_iy(q.pc);
@@ -1382,39 +1354,123 @@ __device__ void lpc_group(const Problem &P, int erow, const double *tab, double 
   const long base = slot_base(P, q.s) + ri;
   const long itm = (long)q.s * P.bmax + q.r;
   const bool head = valid && ch == 0;
-  const double *par = (h ? PE : PQ) + it * lpc::kPairs;
-  [[maybe_unused]] const double *wgt = P.err_mode != 0 ? PW + it * lpc::kPairs : nullptr;
-  double *dst = h ? P.dep : P.dv;
+  const int child = lane >> 1;
+  const long MQ = P.MQ;
+  double *rec = Yw;  // [32][kStage]
+  long *cbase = reinterpret_cast<long *>(Yw + lpc::area_doubles(WE, GEN));  // [32] region, -1: inactive
+  long *ibase = cbase + kChildren;                                          // [8] item of the deltas
+  [[maybe_unused]] float *wgt = reinterpret_cast<float *>(ibase + kItems);  // [8][45] key weights
+  if (h == 0) cbase[child] = valid ? base : -1;
+  if ((lane & 7) == 0) ibase[it] = valid ? itm : -1;
+  if constexpr (WW)
+    for (int k = lane & 7; k < MU; k += 8) wgt[it * kPairs9 + k] = P.itau[(long)q.s * MU + k];
+  // staged values [32][n] of columns p0.. of the value records: deltas, then
+  // the records (child 0's takes its parent's place, whose values the deltas
+  // have read by then)
+  auto put_values = [&](auto n_, int p0) {
+    const int n = n_;
+#pragma unroll 4
+    for (int e = lane; e < kItems * n; e += 64) {
+      const int i = e / n, k = e - i * n;
+      const long m = ibase[i];
+      if (m >= 0) {
+        const double *c = rec + i * 4 * kStage + k;
+        const double sum = (c[0] + c[kStage]) + (c[2 * kStage] + c[3 * kStage]);
+        P.dv[m * MQ + p0 + k] = sum - P.Q[cbase[4 * i] * MQ + p0 + k];
+      }
+    }
+    wave_sync();
+#pragma unroll 4
+    for (int e = lane; e < kChildren * n; e += 64) {
+      const int c = e / n, k = e - c * n;
+      const long b = cbase[c];
+      if (b >= 0) P.Q[b * MQ + p0 + k] = rec[c * kStage + k];
+    }
+  };
+  // the same for errors, staged as float [32][ld]; the deltas carry the
+  // float-rounded errors that are stored and later subtracted
+  [[maybe_unused]] auto put_errors = [&](const float *re, int ld, int n, int p0) {
+    for (int e = lane; e < kItems * n; e += 64) {
+      const int i = e / n, k = e - i * n;
+      const long m = ibase[i];
+      if (m >= 0) {
+        const float *c = re + i * 4 * ld + k;
+        const double sum = ((double)c[0] + (double)c[ld]) + ((double)c[2 * ld] + (double)c[3 * ld]);
+        P.dep[m * MU + p0 + k] = sum - (double)P.E[cbase[4 * i] * MU + p0 + k];
+      }
+    }
+    wave_sync();
+    for (int e = lane; e < kChildren * n; e += 64) {
+      const int c = e / n, k = e - c * n;
+      const long b = cbase[c];
+      if (b >= 0) P.E[b * MU + p0 + k] = re[c * ld + k];
+    }
+  };
   double key = 0.0;
-  constexpr lpc::PairTab PT = lpc::make_pair_tab();
+  if constexpr (!GEN) {
+    if (h == 0) {
 #pragma unroll
-  for (int p = 0; p < lpc::kPairs; ++p) {
-    const signed char *tp = PT.t[p];
-    double v = I[tp[0]][tp[3]];
-    if (tp[4] >= 0) v = tp[5] > 0 ? v + I[tp[0]][tp[4]] : v - I[tp[0]][tp[4]];
-    if (tp[1] >= 0) {
-      double u = I[tp[1]][tp[3]];
-      if (tp[4] >= 0) u = tp[5] > 0 ? u + I[tp[1]][tp[4]] : u - I[tp[1]][tp[4]];
-      v = tp[2] > 0 ? v + u : v - u;
+      for (int j = 0; j < kPhi; ++j)
+#pragma unroll
+        for (int k = 0; k < kPhi; ++k) rec[child * kStage + kPhi * j + k] = fx * I[j][k];
     }
-    const double x = fx * v;  // lane 0: Q_2N of the pair, lane 1: E
-    const double e = fabs(x);
-    if constexpr (WW)
-      key += wgt ? e * wgt[p] : e;  // (the test keeps the weights' loads where they are used)
-    else
-      key += e;
-    // lane 1's term of the children's sum: the same float-rounded error
-    // that is stored and later subtracted (without stored errors lane 1's
-    // sum is not used)
-    double term = x;
+    wave_sync();
+    put_values(std::integral_constant<int, kProd>{}, 0);
+    if constexpr (WE) wave_sync();  // the errors take the values' place
+    float *re = reinterpret_cast<float *>(rec);
+    constexpr PairTab PT = make_pair_tab();
+#pragma unroll
+    for (int p = 0; p < kPairs9; ++p) {
+      const signed char *tp = PT.t[p];
+      double v = I[tp[0]][tp[3]];
+      if (tp[4] >= 0) v = tp[5] > 0 ? v + I[tp[0]][tp[4]] : v - I[tp[0]][tp[4]];
+      if (tp[1] >= 0) {
+        double u = I[tp[1]][tp[3]];
+        if (tp[4] >= 0) u = tp[5] > 0 ? u + I[tp[1]][tp[4]] : u - I[tp[1]][tp[4]];
+        v = tp[2] > 0 ? v + u : v - u;
+      }
+      const double e = fabs(fx * v);  // lane 1: |E| of the pair
+      if constexpr (WW)
+        key += e * (double)wgt[it * kPairs9 + p];
+      else
+        key += e;
+      if constexpr (WE)
+        if (h == 1) re[child * kPairs9 + p] = err_f32(e);
+    }
     if constexpr (WE) {
-      const float ef = err_f32(e);
-      if (h == 1 && valid) P.E[base * MU + p] = ef;
-      if (h) term = (double)ef;
+      wave_sync();
+      put_errors(re, kPairs9, kPairs9, 0);
     }
-    if (h == 0 && valid) P.Q[base * MU + p] = x;
-    const double sum = lpc::child_sum(term);
-    if (head && dst) dst[itm * MU + p] = sum - par[p];
+  } else {
+    // pairs from the product integrals, kStage at a time (the coefficients
+    // are the same for every lane: scalar loads)
+    [[maybe_unused]] float *re = reinterpret_cast<float *>(rec + kChildren * kStage);
+    typedef const __attribute__((address_space(4))) double CD;
+    CD *co = (CD *)P.pcoef;
+#pragma unroll 1
+    for (int p0 = 0; p0 < MU; p0 += kStage) {
+      const int n = min(kStage, MU - p0);
+#pragma unroll 1
+      for (int j = 0; j < n; ++j, co += kProd) {
+        double v = 0.0;
+#pragma unroll
+        for (int a = 0; a < kPhi; ++a)
+#pragma unroll
+          for (int b = 0; b < kPhi; ++b) v = fma(co[kPhi * a + b], I[a][b], v);
+        const double x = fx * v, e = fabs(x);
+        if constexpr (WW)
+          key += e * (double)wgt[it * kPairs9 + p0 + j];
+        else
+          key += e;
+        if (h == 0) rec[child * kStage + j] = x;
+        if constexpr (WE)
+          if (h == 1) re[child * kStage + j] = err_f32(e);
+      }
+      wave_sync();
+      put_values(n, p0);
+      if constexpr (WE) put_errors(re, kStage, n, p0);
+      wave_sync();
+    }
   }
   // child keys (lane 1) and the item's key delta
   const double kk = lpc::child_sum(h ? key : 0.0);
@@ -1428,12 +1484,13 @@ __device__ void lpc_group(const Problem &P, int erow, const double *tab, double 
     if (P.ifill) P.ifill[itm] = !item_skip;
     if (dd + 1 > P.st_depth[q.s]) atomicMax(&P.st_depth[q.s], dd + 1);
   }
+  wave_sync();  // the next group's node rows take the records' place
 }
 
 // The same work partition and table staging as k_children; inside a segment
 // (items of one parameter row) wave wv takes the groups of 8 items that
 // start at seg + 8 (wv + nw k).
-template <bool BUB, bool WE, bool WW>
+template <bool BUB, bool WE, bool WW, bool GEN>
 __global__ void __launch_bounds__(512) k_children_lpc(Problem P) {
   extern __shared__ double lds_raw[];
   double *tabl = lds_raw;
@@ -1473,7 +1530,7 @@ __global__ void __launch_bounds__(512) k_children_lpc(Problem P) {
         s = a;
         hi = P.woff[s + 1];
       }
-      lpc_group<BUB, WE, WW>(kernarg_problem(P), e, tabl, Yw, g, seg_hi, s);
+      lpc_group<BUB, WE, WW, GEN>(kernarg_problem(P), e, tabl, Yw, g, seg_hi, s);
     }
     seg = seg_hi;
     if (seg < i1) {
@@ -1542,29 +1599,29 @@ hipError_t launch_eval_t(Problem p, int grid, hipStream_t s) {
 
 // per-wave LDS of the two-lanes-per-child kernel (doubles)
 int lpc_wave_doubles(const Problem &p) {
-  return lpc::wave_doubles(p.E != nullptr, p.err_mode != 0);
+  return lpc::wave_doubles(p.E != nullptr, p.err_mode != 0, needs_pair_coefficients(p));
+}
+
+// the two-lanes-per-child kernel for the problem's integrand and form factors
+template <bool BUB, bool GEN>
+const void *lpc_kernel_t(bool we, bool ww) {
+  return we ? (ww ? reinterpret_cast<const void *>(&k_children_lpc<BUB, true, true, GEN>)
+                  : reinterpret_cast<const void *>(&k_children_lpc<BUB, true, false, GEN>))
+            : (ww ? reinterpret_cast<const void *>(&k_children_lpc<BUB, false, true, GEN>)
+                  : reinterpret_cast<const void *>(&k_children_lpc<BUB, false, false, GEN>));
+}
+const void *lpc_kernel(const Problem &p) {
+  const bool we = p.E != nullptr, ww = p.err_mode != 0, gen = needs_pair_coefficients(p);
+  if (p.kind <= 1) return gen ? lpc_kernel_t<true, true>(we, ww) : lpc_kernel_t<true, false>(we, ww);
+  return gen ? lpc_kernel_t<false, true>(we, ww) : lpc_kernel_t<false, false>(we, ww);
 }
 
 // Dynamic LDS of the two-lanes-per-child kernel: the table and each wave's
-// node rows and parent values.  The table is staged once per workgroup, so
-// the number of waves per workgroup (4, 6 or 8; fewer only if nothing else
-// fits the device's per-workgroup limit) is the one that keeps the most
-// waves resident per CU, by the runtime's occupancy calculator; the choice
-// is remembered per table and wave size.
-// the two-lanes-per-child kernel for the problem's integrand
-const void *lpc_kernel(const Problem &p) {
-  static const void *const k[8] = {
-      reinterpret_cast<const void *>(&k_children_lpc<false, false, false>),
-      reinterpret_cast<const void *>(&k_children_lpc<false, false, true>),
-      reinterpret_cast<const void *>(&k_children_lpc<false, true, false>),
-      reinterpret_cast<const void *>(&k_children_lpc<false, true, true>),
-      reinterpret_cast<const void *>(&k_children_lpc<true, false, false>),
-      reinterpret_cast<const void *>(&k_children_lpc<true, false, true>),
-      reinterpret_cast<const void *>(&k_children_lpc<true, true, false>),
-      reinterpret_cast<const void *>(&k_children_lpc<true, true, true>)};
-  return k[(p.kind <= 1 ? 4 : 0) + (p.E ? 2 : 0) + (p.err_mode != 0 ? 1 : 0)];
-}
-
+// node rows and records.  The table is staged once per workgroup, so the
+// number of waves per workgroup (4, 6 or 8; fewer only if nothing else fits the
+// device's per-workgroup limit) is the one that keeps the most waves resident
+// per CU, by the runtime's occupancy calculator; the choice is remembered per
+// table and wave size.
 size_t lpc_lds(const Problem &p, int *waves_out) {
   const size_t wave_b = sizeof(double) * lpc_wave_doubles(p);
   const size_t tab_b = sizeof(double) * (size_t)p.tab_rows * kTabStride;
@@ -1605,11 +1662,11 @@ namespace {
 // in the requested precision
 int gram_mode(const Problem &p) { return p.gram == PAID_GRAM_SEPARABLE ? kSep : p.precision; }
 
-// the two-lanes-per-child kernel serves the 9-function box basis itself with
-// the separable FP64 projection over the full zone (bubble and unit integrands)
+// the two-lanes-per-child kernel serves form factors over the 9-function box
+// (or its first function) with the separable FP64 projection over the full
+// zone (bubble and unit integrands)
 bool use_lpc(const Problem &p) {
-  return p.eval_layout == 0 && p.L == 1 && p.ff_identity && !p.sym && gram_mode(p) == kSep &&
-         p.kind != PAID_GAUSS;
+  return p.eval_layout == 0 && p.L <= 1 && !p.sym && gram_mode(p) == kSep && p.kind != PAID_GAUSS;
 }
 
 template <int L>
@@ -1642,6 +1699,9 @@ hipError_t launch_eval_l(const Problem &p, int grid, hipStream_t s) {
   }
 }
 }  // namespace
+
+bool leaves_hold_products(const Problem &p) { return use_lpc(p) && p.L == 1 && p.ff_identity; }
+bool needs_pair_coefficients(const Problem &p) { return use_lpc(p) && !(p.L == 1 && p.ff_identity); }
 
 hipError_t launch_root(const Problem &p, hipStream_t s) {
   switch (p.L) {
