@@ -361,6 +361,7 @@ def main():
     mpath = args.seed_model or SM.DEFAULT_MODEL
     if not args.no_seed and os.path.exists(mpath):
         w_seed, meta = SM.load(mpath)
+        w_seed = SM.even(w_seed)  # the density is even: seeded calls keep mirror images together
         model = {"file": os.path.relpath(mpath, ROOT), "kappa": meta["kappa"],
                  "trees": meta["trees"], "train_seconds": meta["train_seconds"],
                  "mse_held_out": meta["mse_held_out"]}

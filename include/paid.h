@@ -164,7 +164,9 @@ typedef struct {
   long not_converged;   /* containers that hit max_regions */
   long regions;         /* leaves at exit, summed over containers */
   long splits;          /* rectangles subdivided, summed */
-  long kernel_evals;    /* evaluations of the scalar integrand g */
+  long kernel_evals;    /* values of the scalar integrand g in the rule sums (a
+                           rectangle evaluated together with its mirror image
+                           under p -> -p counts both, as do regions and splits) */
   long rounds;          /* bulk-extraction rounds, summed over containers */
   long launch_rounds;   /* device rounds of the whole call */
   int max_depth;        /* deepest subdivision level */

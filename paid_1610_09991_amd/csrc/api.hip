@@ -58,6 +58,7 @@ struct paid_ctx {
   // learned seeding
   DevBuf seedw, sfeat, sfold, sy, sact, pyr, seedd, ifill, labtmp, rowsz, rperm, movei, upart;
   bool seed_on = false;
+  bool seed_even = false;        // the model predicts the same for a cell and its mirror image
   int seed_dmax = 8;
   double seed_kappa = 2.0;
   float *feat_out = nullptr, *lab_out = nullptr;
@@ -580,12 +581,21 @@ int paid_integrate(paid_ctx *c, const paid_params *params, int n_params, const d
   P.products = leaves_hold_products(P) ? 1 : 0;
   const int MQ = P.MQ = P.products ? kProd : MU;
   if ((rc = stage_pair_coefficients(c, P, hff.data())) != PAID_OK) return rc;
+  // Mirror images together, except where the tree is asked for leaf by leaf
+  // (the serial order, which takes one of two equal keys after the other, and
+  // the leaf output) or started from a density that is not even itself.  Half
+  // the rectangles are evaluated and kept: 2x on every workload.
+  const bool lockstep = cfg.batch == 1 && cfg.batch_max == 1;
+  P.mirror = can_mirror(P) && !lockstep && !c->leaf_codes && (!c->seed_on || c->seed_even) ? 1 : 0;
+  const int img = images(P);
 
   // pool: slots x capacity; with small_regions, large slots (capb) first,
   // then small ones (cap)
-  const long capb = cfg.max_regions;
-  const bool two = cfg.small_regions > 0 && cfg.small_regions < capb;
-  const long cap = two ? cfg.small_regions : capb;
+  const long capb = cfg.max_regions / img;
+  const bool two = cfg.small_regions > 0 && cfg.small_regions < cfg.max_regions;
+  const long cap = two ? cfg.small_regions / img : capb;
+  // splits per container and round, in stored leaves
+  const int bmax = cfg.batch_max / img > 1 ? cfg.batch_max / img : 1, bmin = (cfg.batch + img - 1) / img;
   const size_t rec = 16 + 8 * (size_t)MQ + (store_E ? 4 * (size_t)MU : 0);
   size_t pool_bytes, rest_bytes = 0;  // rest: for the per-slot round buffers (0: unchecked)
   if (cfg.pool_gib > 0) {
@@ -610,12 +620,11 @@ int paid_integrate(paid_ctx *c, const paid_params *params, int n_params, const d
   if (Ws > n_ctr) Ws = n_ctr;
   if (Wb + Ws > 65536) Ws = 65536 - Wb;
   // the round buffers of every slot (deltas, selections) must fit beside the pool
-  const size_t slot_rest = (size_t)cfg.batch_max * (8 * ((size_t)MQ + (store_E ? MU : 0)) + 16) + 32 * (size_t)MU;
+  const size_t slot_rest = (size_t)bmax * (8 * ((size_t)MQ + (store_E ? MU : 0)) + 16) + 32 * (size_t)MU;
   if (rest_bytes > 0 && (size_t)(Wb + Ws) * slot_rest > rest_bytes) Ws = (long)(rest_bytes / slot_rest) - Wb;
   if (Ws < 1) return fail(c, PAID_ENOMEM, "region pool too small for one container of %ld regions", cap);
   const long W = Wb + Ws;
   const size_t regions = (size_t)Wb * capb + (size_t)Ws * cap;
-  const int bmax = cfg.batch_max, bmin = cfg.batch;
   HIPCHK(c, c->code.ensure(sizeof(uint64_t) * regions));
   HIPCHK(c, c->key.ensure(sizeof(double) * regions));
   HIPCHK(c, c->Q.ensure(sizeof(double) * regions * MQ));
@@ -632,7 +641,6 @@ int paid_integrate(paid_ctx *c, const paid_params *params, int n_params, const d
   if (store_E) HIPCHK(c, c->dep.ensure(sizeof(double) * W * (size_t)bmax * MU));
   HIPCHK(c, c->stl.ensure(sizeof(long) * 3 * W));
   HIPCHK(c, c->ifill.ensure(sizeof(int) * W * (size_t)bmax));
-  const bool lockstep = bmin == 1 && bmax == 1;
   if (lockstep) HIPCHK(c, c->born.ensure(sizeof(unsigned int) * regions));
   HIPCHK(c, c->counters.ensure(256));
   const bool out_dev = is_device_ptr(out), err_dev = err_out && is_device_ptr(err_out);
@@ -743,7 +751,7 @@ int paid_integrate(paid_ctx *c, const paid_params *params, int n_params, const d
       P.seed_d = c->seedd.as<int>();
       P.seed_dmax = c->seed_dmax;
       P.seed_thresh = 4.0 * c->seed_kappa;
-      P.seed_limit = cap / 4;  // a seed tree fits a small slot
+      P.seed_limit = cap * img / 4;  // a seed tree fits a small slot
       // admission order: the parameter rows by predicted leaves, largest
       // first (ties by row), so that the deepest trees start early and the
       // call does not end on a few of them; each row's containers stay
@@ -867,7 +875,7 @@ int paid_integrate(paid_ctx *c, const paid_params *params, int n_params, const d
       eval_ms += ms;
     }
     if (hc[0] >= n_ctr) break;
-    if (rounds > 4L * capb + 64L * (n_ctr / Ws + 1)) {
+    if (rounds > 4L * cfg.max_regions + 64L * (n_ctr / Ws + 1)) {
       (void)hipStreamSynchronize(c->stream);
       return fail(c, PAID_EINTERNAL, "round loop did not finish (%ld rounds)", rounds);
     }
@@ -1115,6 +1123,14 @@ int paid_set_seed_model(paid_ctx *c, const float *w, int dmax, double kappa) {
       c->seed_on = false;
       return fail(c, PAID_EINVAL, "model weight %ld is not finite", i);
     }
+  // an even density: output 255 - o is the cell of p -> -p of output o's cell
+  const MlpLayout L = mlp_layout();
+  const int ni = L.ni[3];
+  c->seed_even = true;
+  for (int o = 0; o < kMlpOut / 2 && c->seed_even; ++o)
+    c->seed_even = chk[L.b[3] + o] == chk[L.b[3] + kMlpOut - 1 - o] &&
+                   std::equal(&chk[L.w[3] + (long)o * ni], &chk[L.w[3] + (long)o * ni] + ni,
+                              &chk[L.w[3] + (long)(kMlpOut - 1 - o) * ni]);
   c->seed_on = true;
   return PAID_OK;
 }

@@ -73,6 +73,15 @@ struct Problem {      // everything the round kernels need, passed by value
   int tab_rows;               // rows of the largest frequency-sum table (the LDS table)
   int lds_limit;              // bytes of LDS a workgroup may use on the device
   int sym;                    // 1: half zone p_y >= 0 with the parity factors of the pairs
+  // 1: a leaf stands for itself and its mirror image under p -> -p.  Both
+  // bubbles are even (the inversion swaps the two energies, in which K_j is
+  // symmetric), so the tree of a container and every rectangle's values are
+  // mirror images of themselves: Q of a pair of odd joint parity cancels
+  // between the two, any other doubles, and the errors and keys double.  Leaves
+  // with p_y >= 0 are kept and evaluated (the root as its two upper quadrants);
+  // capacities and batch sizes here count them, results and statistics count
+  // both images.
+  int mirror;
   int eval_layout;            // 0: the fastest evaluation kernel for the basis, 1: one wave per parent
   uint64_t *code;             // [regions], slot s from slot_base(s)
   double *key;                // [regions]
@@ -129,6 +138,9 @@ __host__ __device__ inline long slot_base(const Problem &P, int s) {
   return s < P.Wb ? (long)s * P.capb : (long)P.Wb * P.capb + (long)(s - P.Wb) * P.cap;
 }
 __host__ __device__ inline long slot_cap(const Problem &P, int s) { return s < P.Wb ? P.capb : P.cap; }
+
+// leaves of the tree that a stored leaf stands for
+__host__ __device__ inline int images(const Problem &P) { return P.mirror ? 2 : 1; }
 
 // running value of pair pid (p <= q) of slot s
 __device__ inline double slot_pair(const Problem &P, int s, int pid) {
@@ -190,6 +202,8 @@ hipError_t launch_worklist(const Problem &p, hipStream_t s);
 // whether leaves hold the 25 product integrals instead of the pairs (by the
 // static description alone)
 bool leaves_hold_products(const Problem &p);
+// whether the evaluation kernels for p can keep mirror images together
+bool can_mirror(const Problem &p);
 // whether the evaluation reads Problem::pcoef
 bool needs_pair_coefficients(const Problem &p);
 // dynamic LDS bytes of the evaluation kernel for p (0: the table does not fit)

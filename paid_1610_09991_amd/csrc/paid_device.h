@@ -99,6 +99,12 @@ struct Ctr {          // one container (parameter row, transfer momentum, channe
 constexpr int kPhi = 5, kProd = kPhi * kPhi;
 constexpr int kPairs9 = 45;  // pairs of the 9 box functions
 
+// product integral kPhi j + k: whether phi_j(x) phi_k(y) is odd under p -> -p
+// (phi_2 and phi_4 are sines)
+__host__ __device__ constexpr bool product_odd(int i) {
+  return ((i / kPhi) == 2 || (i / kPhi) == 4) != ((i % kPhi) == 2 || (i % kPhi) == 4);
+}
+
 // phi index and sign of the terms of the product u_a u_c (a <= c)
 struct Terms {
   int n, j0, s0, j1, s1;

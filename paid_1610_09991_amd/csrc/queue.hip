@@ -423,8 +423,10 @@ __global__ void __launch_bounds__(kSelThreads) k_select(Problem P) {
     unsigned long long sex = sinc - s8;
     double dd = ldexp(deficit, -ke) * scale;
     unsigned long long dfix = dd >= 4.0e18 ? 4000000000000000000ull : (unsigned long long)(dd > 0 ? dd : 0.0);
-    int beps = (P.err_mode != 1) ? key_bin(ldexp(eps, -ke), eb) : 0;
-    if (P.err_mode != 1 && eps >= maxkey) beps = -1;  // no single leaf exceeds eps
+    // (a stored key is that of all its images; eps is compared with one leaf's)
+    const double epsl = eps * images(P);
+    int beps = (P.err_mode != 1) ? key_bin(ldexp(epsl, -ke), eb) : 0;
+    if (P.err_mode != 1 && epsl >= maxkey) beps = -1;  // no single leaf exceeds eps
     // first bin b (in this lane's 8) meeting all conditions
     int found = kBins, fcnt = 0;
     unsigned int cc = cex;
@@ -645,10 +647,10 @@ __global__ void __launch_bounds__(kSelThreads) k_update(Problem P) {
       fills += part[c * len + MQ + MU + 1];
     }
     P.err[s] += d;
-    P.st_evals[s] += (long)fills * (kNX * kNX);
+    P.st_evals[s] += (long)fills * (kNX * kNX) * images(P);
     P.nleaf[s] += 3 * k;
     P.st_rounds[s] += 1;
-    P.st_splits[s] += k;
+    P.st_splits[s] += (long)k * images(P);
   }
 }
 
@@ -665,12 +667,18 @@ __device__ void tree_labels(const Problem &P, int s, long c, double *cnt) {
     const uint64_t code = P.code[base + i];
     const int d = code_depth(code), ix = (int)code_ix(code), iy = (int)code_iy(code);
     if (d >= 4) {
-      atomicAdd(&cnt[((iy >> (d - 4)) << 4) + (ix >> (d - 4))], 1.0);
+      const int cell = ((iy >> (d - 4)) << 4) + (ix >> (d - 4));
+      atomicAdd(&cnt[cell], 1.0);
+      if (P.mirror) atomicAdd(&cnt[kSeedG * kSeedG - 1 - cell], 1.0);
     } else {
       const int span = 1 << (4 - d);
       const double f = ldexp(1.0, -2 * (4 - d));
       for (int b = 0; b < span; ++b)
-        for (int a = 0; a < span; ++a) atomicAdd(&cnt[((iy * span + b) << 4) + ix * span + a], f);
+        for (int a = 0; a < span; ++a) {
+          const int cell = ((iy * span + b) << 4) + ix * span + a;
+          atomicAdd(&cnt[cell], f);
+          if (P.mirror) atomicAdd(&cnt[kSeedG * kSeedG - 1 - cell], f);
+        }
     }
   }
   __syncthreads();
@@ -729,7 +737,7 @@ __global__ void __launch_bounds__(kSelThreads) k_finalize(Problem P) {
     if (P.flags[s] & 2) atomicAdd(&P.counters[1], 1);
     atomicAdd((unsigned long long *)&P.gstats[0], (unsigned long long)P.st_rounds[s]);
     atomicAdd((unsigned long long *)&P.gstats[1], (unsigned long long)P.st_splits[s]);
-    atomicAdd((unsigned long long *)&P.gstats[2], (unsigned long long)P.nleaf[s]);
+    atomicAdd((unsigned long long *)&P.gstats[2], (unsigned long long)P.nleaf[s] * images(P));
     atomicMax((unsigned long long *)&P.gstats[3], (unsigned long long)P.st_depth[s]);
     atomicAdd((unsigned long long *)&P.gstats[4], (unsigned long long)P.st_evals[s]);
     P.state[s] = SLOT_EMPTY;

@@ -299,19 +299,21 @@ __device__ void sep_stage2(WaveLds<L> &S, const Problem &P, const int *pidmap, c
   if (P.ff_identity) {
     for (int pid = lane; pid < MU; pid += 64) {
       int jk = pidmap[pid];
-      double q2 = G2[jk], f = fa;
-      if (P.sym) f = podd[pid] ? 0.0 : 2.0 * fa;
+      double q2 = G2[jk], f = fa, fe = fa;
+      if (P.sym || P.mirror) f = podd[pid] ? 0.0 : 2.0 * fa;
+      if (P.sym || P.mirror) fe = P.mirror ? 2.0 * fa : f;
       S.cq[pid] = f * q2;
-      S.ce[pid] = f * (q2 - G1[jk]);
+      S.ce[pid] = fe * (q2 - G1[jk]);
     }
   } else {
     for (int idx = lane; idx < MB * MB; idx += 64) {
       int m = idx / MB, n = idx - m * MB;
       int jk = prod_index<NB>(m / NB, n / NB) * NP + prod_index<NB>(m % NB, n % NB);
-      double q2 = G2[jk], f = fa;
-      if (P.sym) f = half_zone_factor<NB>(m, n) * fa;
+      double q2 = G2[jk], f = fa, fe = fa;
+      if (P.sym || P.mirror) f = half_zone_factor<NB>(m, n) * fa;
+      if (P.sym || P.mirror) fe = P.mirror ? 2.0 * fa : f;
       S.tq[idx] = f * q2;
-      S.ts[idx] = f * (q2 - G1[jk]);
+      S.ts[idx] = fe * (q2 - G1[jk]);
     }
   }
   wave_sync();
@@ -725,8 +727,11 @@ __global__ void __launch_bounds__(64) k_root(Problem P) {
     placeholder = D > 0 && spyr[0] >= P.seed_thresh;
   }
   double key = 0.0;
-  const int nroot = P.sym ? 2 : 1;  // leaves the container starts from
-  if (placeholder) {
+  // leaves the container starts from: the zone, or its two quadrants with p_y >= 0
+  const bool half = P.sym || P.mirror;
+  const int nroot = half ? 2 : 1;
+  int filled = 0;
+  if (placeholder && !half) {
     store_zero<L>(P, s, 0, make_code(0, 0, 0));
     for (int i = threadIdx.x; i < P.MQ; i += 64) P.val[(long)s * P.MQ + i] = 0.0;
     if (P.errp)
@@ -735,18 +740,28 @@ __global__ void __launch_bounds__(64) k_root(Problem P) {
     const Ctr C = P.ctr[c];
     const Entry E = P.entries[C.entry];
     const double *tab = P.tab + E.tab_off;
-    // the zone, or in the half-zone mode its two quadrants with p_y >= 0
-    const double wr = P.sym ? kPi : kTwoPi;
+    const double wr = half ? kPi : kTwoPi;
+    if (half) {  // the sums below add up the quadrants
+      for (int i = threadIdx.x; i < P.MQ; i += 64) P.val[(long)s * P.MQ + i] = 0.0;
+      if (P.errp)
+        for (int pid = threadIdx.x; pid < P.MU; pid += 64) P.errp[(long)s * P.MU + pid] = 0.0;
+    }
     for (int h = 0; h < nroot; ++h) {
-      fill_nodes<L>(S, P, C, E, tab, kNF, -kPi + h * wr, P.sym ? 0.0 : -kPi, wr);
+      // a quadrant that the seed tree splits again (the root is split then)
+      if (placeholder && D > 1 && spyr[pyr_off(1) + 2 + h] >= P.seed_thresh) {
+        store_zero<L>(P, s, h, make_code(1, h, 1));
+        continue;
+      }
+      ++filled;
+      fill_nodes<L>(S, P, C, E, tab, kNF, -kPi + h * wr, half ? 0.0 : -kPi, wr);
       if (GRAM == kSep) sep_stage1<L>(S, kNF, 1);
       eval_rect<L, GRAM>(S, P, pidmap, podd, kNF, 0, 0, (0.5 * wr) * (0.5 * wr) / (4.0 * kPi * kPi));
-      key += store_region<L>(S, P, s, h, P.sym ? make_code(1, h, 1) : make_code(0, 0, 0));
+      key += store_region<L>(S, P, s, h, half ? make_code(1, h, 1) : make_code(0, 0, 0));
       for (int pid = threadIdx.x; pid < P.MU; pid += 64) {
         const long o = (long)s * P.MU + pid;
         const double e = (double)err_f32(fabs(S.ce[pid]));
-        if (!P.products) P.val[(long)s * P.MQ + pid] = h ? P.val[(long)s * P.MQ + pid] + S.cq[pid] : S.cq[pid];
-        if (P.errp) P.errp[o] = h ? P.errp[o] + e : e;
+        if (!P.products) P.val[(long)s * P.MQ + pid] = half ? P.val[(long)s * P.MQ + pid] + S.cq[pid] : S.cq[pid];
+        if (P.errp) P.errp[o] = half ? P.errp[o] + e : e;
       }
       if constexpr (L == 1 && GRAM == kSep)
         if (P.products && threadIdx.x < kProd) {
@@ -754,19 +769,20 @@ __global__ void __launch_bounds__(64) k_root(Problem P) {
           // (phi_3 = u_1 u_1 - u_0 u_0; the others are products themselves)
           const int j = threadIdx.x / kPhi, k = threadIdx.x % kPhi;
           auto sum_y = [&](int x) { return k == 3 ? S.g2[x * 6 + 3] - S.g2[x * 6] : S.g2[x * 6 + k]; };
-          const double v = ((0.5 * wr) * (0.5 * wr) / (4.0 * kPi * kPi)) * (j == 3 ? sum_y(3) - sum_y(0) : sum_y(j));
+          double v = ((0.5 * wr) * (0.5 * wr) / (4.0 * kPi * kPi)) * (j == 3 ? sum_y(3) - sum_y(0) : sum_y(j));
+          if (P.mirror) v *= product_odd(threadIdx.x) ? 0.0 : 2.0;
           P.Q[(slot_base(P, s) + h) * P.MQ + threadIdx.x] = v;
-          P.val[(long)s * P.MQ + threadIdx.x] = v;
+          P.val[(long)s * P.MQ + threadIdx.x] = half ? P.val[(long)s * P.MQ + threadIdx.x] + v : v;
         }
       wave_sync();
     }
   }
   if (threadIdx.x == 0) {
     P.err[s] = key;
-    P.nleaf[s] = placeholder ? 1 : nroot;
+    P.nleaf[s] = nroot;
     P.st_rounds[s] = 0;
-    P.st_splits[s] = 0;
-    P.st_evals[s] = placeholder ? 0 : nroot * kNF * kNF;
+    P.st_splits[s] = P.mirror ? 1 : 0;  // (the root's)
+    P.st_evals[s] = (long)filled * images(P) * kNF * kNF;
     P.st_depth[s] = nroot - 1;
     if (P.born)
       for (int h = 0; h < nroot; ++h) P.born[slot_base(P, s) + h] = h;
@@ -853,9 +869,10 @@ __device__ void do_item(WaveLds<L> &S, const Problem &P, const int *pidmap, cons
           const int pid = lane + 64 * k;
           if (pid < MU) {
             const int jk = pidmap[pid];
-            double f = fa;
-            if (P.sym) f = podd[pid] ? 0.0 : 2.0 * fa;
-            const double q2 = G2[jk], q = f * q2, e = fabs(f * (q2 - G1[jk]));
+            double f = fa, fe = fa;
+            if (P.sym || P.mirror) f = podd[pid] ? 0.0 : 2.0 * fa;
+            if (P.sym || P.mirror) fe = P.mirror ? 2.0 * fa : f;
+            const double q2 = G2[jk], q = f * q2, e = fabs(fe * (q2 - G1[jk]));
             P.Q[base * MU + pid] = q;
             if (P.E) P.E[base * MU + pid] = err_f32(e);
             part += (P.err_mode != 0) ? e * (double)P.itau[(long)s * MU + pid] : e;
@@ -1349,7 +1366,15 @@ __device__ void lpc_group(const Problem &P, int erow, const double *tab, double 
   const double pkey = P.key[q.pbase];
   const double wdt = kTwoPi * ldexp(1.0, -dd);
   const double fa = (0.25 * wdt) * (0.25 * wdt) / (4.0 * kPi * kPi);
-  const double fx = phc ? 0.0 : fa;  // placeholders store zeros
+  const double fm = P.mirror ? 2.0 * fa : fa;  // the child and its mirror image
+  const double fx = phc ? 0.0 : fm;            // placeholders store zeros
+  if (P.mirror && h == 0) {  // odd product integrals cancel between the images
+#pragma unroll
+    for (int j = 0; j < kPhi; ++j)
+#pragma unroll
+      for (int k = 0; k < kPhi; ++k)
+        if (product_odd(kPhi * j + k)) I[j][k] = 0.0;
+  }
   const long ri = (ch == 0) ? q.leaf : (long)P.nleaf[q.s] + 3L * q.r + (ch - 1);
   const long base = slot_base(P, q.s) + ri;
   const long itm = (long)q.s * P.bmax + q.r;
@@ -1700,6 +1725,7 @@ hipError_t launch_eval_l(const Problem &p, int grid, hipStream_t s) {
 }
 }  // namespace
 
+bool can_mirror(const Problem &p) { return !p.sym && gram_mode(p) == kSep && p.kind != PAID_GAUSS; }
 bool leaves_hold_products(const Problem &p) { return use_lpc(p) && p.L == 1 && p.ff_identity; }
 bool needs_pair_coefficients(const Problem &p) { return use_lpc(p) && !(p.L == 1 && p.ff_identity); }
 

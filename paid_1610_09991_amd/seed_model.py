@@ -69,6 +69,19 @@ def sweep_kappa(ctx, w, prm, q, ff, L, kappas=(0.5, 1.0, 2.0, 4.0), rtol=1e-6, r
     return res
 
 
+def even(w):
+    """The model whose prediction is the average of w's over each cell and its
+    mirror image under p -> -p (output 255 - o for output o).  The density is
+    even, so this loses nothing, and the library then integrates a seeded
+    container and its mirror images together, as it does without a model."""
+    w = np.array(w, dtype=np.float32, copy=True)
+    no, ni = 256, 128
+    W4, b4 = w[-(no * ni + no):-no].reshape(no, ni), w[-no:]
+    W4[:] = 0.5 * (W4 + W4[::-1])
+    b4[:] = 0.5 * (b4 + b4[::-1])
+    return w
+
+
 def save(path, w, meta):
     np.savez(path, w=np.asarray(w, dtype=np.float32), meta=np.array(json.dumps(meta)))
 
