@@ -4,124 +4,144 @@
 // V^P(l), V^C(l), V^D(l) (M x M over form factors),
 //   dP = V^P chi^pp V^P,
 //   dC = - V^C chi^ph V^C,
-//   dD = 2 V^D chi^ph V^D - V^C chi^ph V^D - V^D chi^ph V^C.
-// One wave per l.  Matrices are staged in LDS zero-padded to 32 x 32 and
-// multiplied on the FP64 matrix cores (16 x 16 x 4 tiles); dD is formed as
-// (2 V^D - V^C) (chi^ph V^D) - V^D (chi^ph V^C), reusing chi^ph V^C from dC.
+//   dD = 2 V^D chi^ph V^D - V^C chi^ph V^D - V^D chi^ph V^C,
+// the last as (2 V^D - V^C) (chi^ph V^D) - V^D (chi^ph V^C), reusing chi^ph V^C.
+//
+// FP64 matrix cores, everything in registers.  A wave owns one l and one
+// column tile (16 columns; M <= 16 has one, M <= 32 two): the columns of all
+// products are independent.  In the 16 x 16 x 4 tiles, lane (kk, m) = (lane >> 4,
+// lane & 15) holds A[m][4 kb + kk] and B[4 kb + kk][m] of k-step kb, and result
+// register r of row tile t is row 16 t + 4 r + kk, column m: that is B of k-step
+// 4 t + r, so chi V feeds the second product as it stands, with no exchange and
+// no LDS.  The bound is memory (every matrix read and written once) and, at M
+// > 16, the matrix cores; the operands come straight from global memory, a
+// whole matrix's loads issued together, and many waves hide them.  Staging six
+// zero-padded 32 x 32 matrices per wave in LDS (50.7 KB, three waves a compute
+// unit) instead took 210 us for 11,520 momenta of order 9 and 77 us for 1,024
+// of order 25; this takes 18 and 20 us (35 and 37 us a call with its synchronisation, 244 and 89 before).
 #include "launch.h"
 
 namespace paid {
 
 namespace {
 
-constexpr int kCM = 32;                 // padded order
-constexpr int kCLd = kCM + 1;           // leading dimension in LDS (bank spread)
-constexpr int kCMat = kCM * kCLd;       // doubles per staged matrix
-constexpr int kCBufs = 6;               // staged matrices per wave
-
 typedef double c4 __attribute__((ext_vector_type(4)));
 
-__device__ inline void cwave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// X (LDS, padded) <- src [M][M] (global), zero outside M x M
-__device__ inline void stage(double *X, const double *src, int M) {
-  const int lane = threadIdx.x & 63;
-  for (int e = lane; e < kCM * kCM; e += 64) {
-    const int i = e / kCM, j = e % kCM;
-    X[i * kCLd + j] = (i < M && j < M) ? src[i * M + j] : 0.0;
-  }
-}
-
-// C = alpha A B + beta C on padded 32 x 32 LDS matrices; tiles beyond the
-// order M (nt = 1 or 2 tiles per side) are skipped.
-__device__ void mm(const double *A, const double *B, double *C, int nt, double alpha, double beta) {
+// A[16 t + m][4 kb + kk] of X [M][M], zero outside
+template <int NT>
+__device__ inline void load_a(const double *X, int M, double (&a)[NT][4 * NT]) {
   const int lane = threadIdx.x & 63, m = lane & 15, kk = lane >> 4;
-  c4 acc[4];
 #pragma unroll
-  for (int t = 0; t < 4; ++t) acc[t] = c4{0.0, 0.0, 0.0, 0.0};
-  const int nk = 4 * nt;  // k-steps of 4 over 16 nt
-  for (int kb = 0; kb < nk; ++kb) {
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int kb = 0; kb < 4 * NT; ++kb) {
+      const int i = 16 * t + m, k = 4 * kb + kk;
+      a[t][kb] = (i < M && k < M) ? X[i * M + k] : 0.0;
+    }
+}
+
+// B[4 kb + kk][16 tc + m] of X, zero outside
+template <int NT>
+__device__ inline void load_b(const double *X, int M, int tc, double (&b)[4 * NT]) {
+  const int lane = threadIdx.x & 63, j = 16 * tc + (lane & 15), kk = lane >> 4;
+#pragma unroll
+  for (int kb = 0; kb < 4 * NT; ++kb) {
     const int k = 4 * kb + kk;
-#pragma unroll
-    for (int tr = 0; tr < 2; ++tr) {
-      if (tr >= nt) continue;
-      const double a = A[(16 * tr + m) * kCLd + k];
-#pragma unroll
-      for (int tc = 0; tc < 2; ++tc) {
-        if (tc >= nt) continue;
-        const double b = B[k * kCLd + 16 * tc + m];
-        acc[2 * tr + tc] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc[2 * tr + tc], 0, 0, 0);
-      }
-    }
+    b[kb] = (k < M && j < M) ? X[k * M + j] : 0.0;
   }
-  cwave_sync();
-  // f64 16x16x4 result: row = 4 r + lane >> 4, col = lane & 15
+}
+
+// acc += A B over the k-steps that hold rows below M
+template <int NT>
+__device__ inline void mul(const double (&a)[NT][4 * NT], const double (&b)[4 * NT], int nk, c4 (&acc)[NT]) {
 #pragma unroll
-  for (int tr = 0; tr < 2; ++tr)
+  for (int kb = 0; kb < 4 * NT; ++kb)
+    if (kb < nk) {
 #pragma unroll
-    for (int tc = 0; tc < 2; ++tc) {
-      if (tr >= nt || tc >= nt) continue;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        double *c = &C[(16 * tr + 4 * r + kk) * kCLd + 16 * tc + m];
-        *c = alpha * acc[2 * tr + tc][r] + (beta != 0.0 ? beta * *c : 0.0);
-      }
+      for (int t = 0; t < NT; ++t)
+        acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t][kb], b[kb], acc[t], 0, 0, 0);
     }
-  cwave_sync();
 }
 
-__device__ inline void unstage(double *dst, const double *X, int M) {
-  const int lane = threadIdx.x & 63;
-  for (int e = lane; e < M * M; e += 64) dst[e] = X[(e / M) * kCLd + e % M];
+// a result as the right operand of the next product
+template <int NT>
+__device__ inline void as_b(const c4 (&acc)[NT], double (&b)[4 * NT]) {
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) b[4 * t + r] = acc[t][r];
 }
 
-__global__ void __launch_bounds__(256) k_contract(int n_l, int M, const double *chi,
-                                                 const double *VP, const double *VC,
-                                                 const double *VD, double *dP, double *dC,
-                                                 double *dD) {
-  extern __shared__ double craw[];
-  const int wv = threadIdx.x >> 6;
-  const long l = (long)blockIdx.x * (blockDim.x >> 6) + wv;
+template <int NT>
+__device__ inline void zero(c4 (&acc)[NT]) {
+#pragma unroll
+  for (int t = 0; t < NT; ++t) acc[t] = c4{0.0, 0.0, 0.0, 0.0};
+}
+
+template <int NT>
+__device__ inline void store(double *X, int M, int tc, const c4 (&acc)[NT], double f) {
+  const int lane = threadIdx.x & 63, j = 16 * tc + (lane & 15), kk = lane >> 4;
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int i = 16 * t + 4 * r + kk;
+      if (i < M && j < M) X[i * M + j] = f * acc[t][r];
+    }
+}
+
+template <int NT>
+__global__ void __launch_bounds__(256) k_contract(int n_l, int M, const double *__restrict__ chi,
+                                                  const double *__restrict__ VP, const double *__restrict__ VC,
+                                                  const double *__restrict__ VD, double *__restrict__ dP,
+                                                  double *__restrict__ dC, double *__restrict__ dD) {
+  const long unit = (long)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+  const long l = unit / NT;
+  const int tc = (int)(unit % NT);
   if (l >= n_l) return;  // whole waves only: nothing below synchronises the workgroup
-  double *X = craw + (size_t)wv * kCBufs * kCMat;
-  double *Vp = X, *Ch = X + kCMat, *Vc = X + 2 * kCMat, *T1 = X + 3 * kCMat,
-         *T2 = X + 4 * kCMat, *T3 = X + 5 * kCMat;
-  const int nt = M > 16 ? 2 : 1;
+  const int nk = (M + 3) >> 2;
   const long mm2 = (long)M * M;
   const double *cpp = chi + (2 * l) * mm2, *cph = chi + (2 * l + 1) * mm2;
+  double a[NT][4 * NT], v[NT][4 * NT], b[4 * NT], t1[4 * NT];
+  c4 acc[NT];
   // dP = V^P (chi^pp V^P)
-  stage(Vp, VP + l * mm2, M);
-  stage(Ch, cpp, M);
-  cwave_sync();
-  mm(Ch, Vp, T1, nt, 1.0, 0.0);
-  mm(Vp, T1, T3, nt, 1.0, 0.0);
-  unstage(dP + l * mm2, T3, M);
-  // dC = -V^C (chi^ph V^C); keep T2 = chi^ph V^C
-  stage(Vc, VC + l * mm2, M);
-  stage(Ch, cph, M);
-  cwave_sync();
-  mm(Ch, Vc, T2, nt, 1.0, 0.0);
-  mm(Vc, T2, T3, nt, -1.0, 0.0);
-  unstage(dC + l * mm2, T3, M);
+  load_a<NT>(cpp, M, a);
+  load_b<NT>(VP + l * mm2, M, tc, b);
+  load_a<NT>(VP + l * mm2, M, v);
+  zero<NT>(acc);
+  mul<NT>(a, b, nk, acc);
+  as_b<NT>(acc, t1);
+  zero<NT>(acc);
+  mul<NT>(v, t1, nk, acc);
+  store<NT>(dP + l * mm2, M, tc, acc, 1.0);
+  // t1 = chi^ph V^D, b = chi^ph V^C
+  load_a<NT>(cph, M, a);
+  load_b<NT>(VD + l * mm2, M, tc, t1);
+  load_b<NT>(VC + l * mm2, M, tc, b);
+  load_a<NT>(VC + l * mm2, M, v);
+  zero<NT>(acc);
+  mul<NT>(a, t1, nk, acc);
+  as_b<NT>(acc, t1);
+  zero<NT>(acc);
+  mul<NT>(a, b, nk, acc);
+  as_b<NT>(acc, b);
+  // dC = -V^C (chi^ph V^C)
+  load_a<NT>(VD + l * mm2, M, a);
+  zero<NT>(acc);
+  mul<NT>(v, b, nk, acc);
+  store<NT>(dC + l * mm2, M, tc, acc, -1.0);
   // dD = (2 V^D - V^C) (chi^ph V^D) - V^D (chi^ph V^C)
-  stage(Vp, VD + l * mm2, M);  // Vp now holds V^D
-  cwave_sync();
-  mm(Ch, Vp, T1, nt, 1.0, 0.0);  // T1 = chi^ph V^D
-  {
-    const int lane = threadIdx.x & 63;
-    for (int e = lane; e < kCM * kCM; e += 64) {
-      const int i = e / kCM, j = e % kCM;
-      Vc[i * kCLd + j] = 2.0 * Vp[i * kCLd + j] - Vc[i * kCLd + j];
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int kb = 0; kb < 4 * NT; ++kb) {
+      v[t][kb] = 2.0 * a[t][kb] - v[t][kb];
+      a[t][kb] = -a[t][kb];
     }
-  }
-  cwave_sync();
-  mm(Vc, T1, T3, nt, 1.0, 0.0);
-  mm(Vp, T2, T3, nt, -1.0, 1.0);
-  unstage(dD + l * mm2, T3, M);
+  zero<NT>(acc);
+  mul<NT>(v, t1, nk, acc);
+  mul<NT>(a, b, nk, acc);
+  store<NT>(dD + l * mm2, M, tc, acc, 1.0);
 }
 
 }  // namespace
@@ -129,10 +149,13 @@ __global__ void __launch_bounds__(256) k_contract(int n_l, int M, const double *
 hipError_t launch_contract(int n_l, int M, const double *chi, const double *VP, const double *VC,
                            const double *VD, double *dP, double *dC, double *dD, hipStream_t s) {
   if (n_l <= 0) return hipSuccess;
-  const int waves = 1;  // 6 staged matrices = 50.7 KB of LDS per workgroup
-  const size_t sh = sizeof(double) * (size_t)waves * kCBufs * kCMat;
-  hipLaunchKernelGGL(k_contract, dim3((n_l + waves - 1) / waves), dim3(64 * waves), sh, s, n_l, M,
-                     chi, VP, VC, VD, dP, dC, dD);
+  const int waves = 4, nt = M > 16 ? 2 : 1;
+  const long units = (long)n_l * nt;
+  const dim3 grid((unsigned)((units + waves - 1) / waves)), block(64 * waves);
+  if (nt == 1)
+    hipLaunchKernelGGL(k_contract<1>, grid, block, 0, s, n_l, M, chi, VP, VC, VD, dP, dC, dD);
+  else
+    hipLaunchKernelGGL(k_contract<2>, grid, block, 0, s, n_l, M, chi, VP, VC, VD, dP, dC, dD);
   return hipGetLastError();
 }
 
