@@ -305,7 +305,7 @@ int paid_mlp_loss_grad(struct paid_ctx *ctx, const float *w, const float *x, con
  * training loops, harnesses that forbid allocation.  Same kernels, same
  * results (bit for bit) as paid_mlp_loss_grad, but no call allocates or
  * frees memory: the working memory (per-sample activations and deltas of up
- * to PAID_NOALLOC_MAX_N samples, and the loss; 13.6 MB) is a fixed array of
+ * to PAID_NOALLOC_MAX_N samples, and the loss; 8.4 MB) is a fixed array of
  * the library on each device, held until the process ends, and the loss is
  * read back through the context's pinned buffer.
  *   w [nparams], x [n][7], y [n][256], grad [nparams]: device memory only

@@ -56,7 +56,7 @@ struct paid_ctx {
   DevBuf code, key, Q, E;
   DevBuf slot_i, slot_d, sel, dv, de, dep, itau, errp, stl, counters, outs, errs;
   // learned seeding
-  DevBuf seedw, sfeat, sfold, sy, sact, pyr, seedd, ifill, labtmp, rowsz, rperm, movei, upart;
+  DevBuf seedw, sfeat, sfold, sy, pyr, seedd, ifill, labtmp, rowsz, rperm, movei, upart;
   bool seed_on = false;
   bool seed_even = false;        // the model predicts the same for a cell and its mirror image
   int seed_dmax = 8;
@@ -333,22 +333,6 @@ int finish_out(paid_ctx *c, T *p, const T *d, size_t n) {
   return PAID_OK;
 }
 
-// the full set of per-sample training buffers for n samples, carved from buf
-int carve_act(paid_ctx *c, DevBuf &buf, int n, MlpAct &a, float *&yhat, float *&dY) {
-  const size_t h = (size_t)kMlpHid * n, o = (size_t)kMlpOut * n;
-  HIPCHK(c, buf.ensure(sizeof(float) * (9 * h + 2 * o)));
-  float *p = buf.as<float>();
-  for (int l = 0; l < 3; ++l) {
-    a.Z[l] = p + (size_t)l * h;
-    a.A[l] = p + (size_t)(3 + l) * h;
-    a.D[l] = p + (size_t)(6 + l) * h;
-  }
-  a.Z[3] = nullptr;
-  yhat = p + 9 * h;
-  dY = yhat + o;
-  return PAID_OK;
-}
-
 // the form-factor pairs as combinations of the 25 product integrals (general
 // sets over the 9-function box, or over its first function), on the device
 int stage_pair_coefficients(paid_ctx *c, Problem &P, const double *ff) {
@@ -489,7 +473,7 @@ void paid_destroy(paid_ctx *c) {
                     &c->ffc,     &c->code, &c->key,   &c->Q,     &c->E,     &c->slot_i,
                     &c->slot_d,  &c->sel,  &c->dv,    &c->de,    &c->dep,   &c->itau,
                     &c->errp,    &c->stl,  &c->counters, &c->outs, &c->errs,
-                    &c->seedw,   &c->sfeat, &c->sfold, &c->sy,  &c->sact,  &c->pyr,
+                    &c->seedw,   &c->sfeat, &c->sfold, &c->sy,  &c->pyr,
                     &c->seedd,   &c->ifill, &c->labtmp, &c->pairw, &c->born, &c->lcodes,
                     &c->lq,      &c->pcoef, &c->rowsz, &c->rperm, &c->movei, &c->upart};
   for (DevBuf *b : bufs) b->release();
@@ -732,18 +716,7 @@ int paid_integrate(paid_ctx *c, const paid_params *params, int n_params, const d
     P.seed_fold = c->sfold.as<int>();
     if (c->seed_on) {
       HIPCHK(c, c->sy.ensure(sizeof(float) * kMlpOut * (size_t)n_ctr));
-      const int chunk = n_ctr < 65536 ? n_ctr : 65536;
-      HIPCHK(c, c->sact.ensure(sizeof(float) * 2 * kMlpHid * (size_t)chunk));
-      MlpAct a;
-      memset(&a, 0, sizeof a);
-      a.A[0] = c->sact.as<float>();
-      a.A[1] = a.A[0] + (size_t)kMlpHid * chunk;
-      a.A[2] = a.A[0];
-      for (int o = 0; o < n_ctr; o += chunk) {
-        int nn = n_ctr - o < chunk ? n_ctr - o : chunk;
-        HIPCHK(c, mlp_forward(c->seedw.as<float>(), c->sfeat.as<float>() + (size_t)o * kMlpIn, nn, a,
-                              c->sy.as<float>() + (size_t)o * kMlpOut, c->stream));
-      }
+      HIPCHK(c, mlp_forward(c->seedw.as<float>(), c->sfeat.as<float>(), n_ctr, c->sy.as<float>(), c->stream));
       HIPCHK(c, c->pyr.ensure(sizeof(double) * kPyr * (size_t)W));
       HIPCHK(c, c->seedd.ensure(sizeof(int) * (size_t)W));
       P.seed_y = c->sy.as<float>();
@@ -1169,35 +1142,17 @@ int paid_mlp_forward(paid_ctx *c, const float *w, const float *x, int n, float *
   if (n > (1 << 24)) return fail(c, PAID_EINVAL, "n must be <= 2^24");
   HIPCHK(c, hipSetDevice(c->cfg.device));
   const long np = mlp_layout().total;
-  DevBuf tw, tx, ty, act;
+  DevBuf tw, tx, ty;
   const float *dw, *dx;
   float *dy;
   int rc;
   if ((rc = stage_in(c, w, np, tw, dw)) != PAID_OK) return rc;
   if ((rc = stage_in(c, x, (size_t)n * kMlpIn, tx, dx)) != PAID_OK) return rc;
   if ((rc = stage_out(c, y, (size_t)n * kMlpOut, ty, dy)) != PAID_OK) return rc;
-  HIPCHK(c, act.ensure(sizeof(float) * 2 * kMlpHid * (size_t)n));
-  MlpAct a;
-  memset(&a, 0, sizeof a);
-  a.A[0] = act.as<float>();
-  a.A[1] = a.A[0] + (size_t)kMlpHid * n;
-  a.A[2] = a.A[0];
-  HIPCHK(c, mlp_forward(dw, dx, n, a, dy, c->stream));
+  HIPCHK(c, mlp_forward(dw, dx, n, dy, c->stream));
   if ((rc = finish_out(c, y, dy, (size_t)n * kMlpOut)) != PAID_OK) return rc;
   HIPCHK(c, hipStreamSynchronize(c->stream));
   return PAID_OK;
-}
-
-// forward pass, mean squared error and backward pass on device arrays with
-// the per-sample buffers of a and the loss in dloss (shared by both entry
-// points)
-static hipError_t loss_grad_launch(paid_ctx *c, const float *dw, const float *dx, const float *dyl,
-                                   int n, MlpAct &a, float *yhat, float *dY, float *dg,
-                                   double *dloss) {
-  hipError_t e;
-  if ((e = mlp_forward(dw, dx, n, a, yhat, c->stream)) != hipSuccess) return e;
-  if ((e = mlp_mse(yhat, dyl, (long)n * kMlpOut, dY, dloss, nullptr, c->stream)) != hipSuccess) return e;
-  return mlp_backward(dw, dx, n, a, dY, dg, c->stream);
 }
 
 int paid_mlp_loss_grad_noalloc(paid_ctx *c, const float *w, const float *x, const float *y, int n,
@@ -1212,19 +1167,8 @@ int paid_mlp_loss_grad_noalloc(paid_ctx *c, const float *w, const float *x, cons
     return fail(c, PAID_EINVAL, "paid_mlp_loss_grad_noalloc takes device arrays only");
   if (!c->noalloc) return fail(c, PAID_EINTERNAL, "fixed working memory not set up");
   HIPCHK(c, hipSetDevice(c->cfg.device));
-  // carve the per-sample buffers of n samples and the loss from the array
-  const size_t h = (size_t)kMlpHid * n, o = (size_t)kMlpOut * n;
-  float *p = c->noalloc;
-  MlpAct a;
-  for (int l = 0; l < 3; ++l) {
-    a.Z[l] = p + (size_t)l * h;
-    a.A[l] = p + (size_t)(3 + l) * h;
-    a.D[l] = p + (size_t)(6 + l) * h;
-  }
-  a.Z[3] = nullptr;
-  float *yhat = p + 9 * h, *dY = yhat + o;
-  double *dloss = reinterpret_cast<double *>(p + kNoAllocActFloats);
-  HIPCHK(c, loss_grad_launch(c, w, x, y, n, a, yhat, dY, grad, dloss));
+  double *dloss = reinterpret_cast<double *>(c->noalloc + kNoAllocActFloats);
+  HIPCHK(c, mlp_loss_grad(w, x, y, n, mlp_carve(c->noalloc, n), grad, dloss, nullptr, c->stream));
   // the loss goes through the context's pinned buffer (bytes 32..39)
   double *hl = reinterpret_cast<double *>(reinterpret_cast<char *>(c->host_counters) + 32);
   HIPCHK(c, hipMemcpyAsync(hl, dloss, sizeof(double), hipMemcpyDeviceToHost, c->stream));
@@ -1248,11 +1192,9 @@ int paid_mlp_loss_grad(paid_ctx *c, const float *w, const float *x, const float 
   if ((rc = stage_in(c, x, (size_t)n * kMlpIn, tx, dx)) != PAID_OK) return rc;
   if ((rc = stage_in(c, y, (size_t)n * kMlpOut, ty, dyl)) != PAID_OK) return rc;
   if ((rc = stage_out(c, grad, np, tg, dg)) != PAID_OK) return rc;
-  MlpAct a;
-  float *yhat, *dY;
-  if ((rc = carve_act(c, act, n, a, yhat, dY)) != PAID_OK) return rc;
+  HIPCHK(c, act.ensure(sizeof(float) * mlp_act_floats(n)));
   HIPCHK(c, tl.ensure(sizeof(double)));
-  HIPCHK(c, loss_grad_launch(c, dw, dx, dyl, n, a, yhat, dY, dg, tl.as<double>()));
+  HIPCHK(c, mlp_loss_grad(dw, dx, dyl, n, mlp_carve(act.as<float>(), n), dg, tl.as<double>(), nullptr, c->stream));
   if ((rc = finish_out(c, grad, dg, np)) != PAID_OK) return rc;
   double hl = 0.0;
   HIPCHK(c, hipMemcpyAsync(&hl, tl.p, sizeof(double), hipMemcpyDeviceToHost, c->stream));
@@ -1342,9 +1284,8 @@ int paid_seed_train(paid_ctx *c, const float *x, const float *y, int n, const pa
   HIPCHK(c, hist.ensure(sizeof(double) * o.steps));
   HIPCHK(c, xb.ensure(sizeof(float) * (size_t)bs * (kMlpIn + kMlpOut)));
   HIPCHK(c, gr.ensure(sizeof(float) * np));
-  MlpAct a;
-  float *yhat, *dY;
-  if ((rc = carve_act(c, act, bs, a, yhat, dY)) != PAID_OK) return rc;
+  HIPCHK(c, act.ensure(sizeof(float) * mlp_act_floats(bs)));
+  const MlpAct a = mlp_carve(act.as<float>(), bs);
   float *Xb = xb.as<float>(), *Yb = Xb + (size_t)bs * kMlpIn;
   float *W = wd.as<float>(), *M = mv.as<float>(), *V = M + np, *G = gr.as<float>();
   int *step = ctr.as<int>();
@@ -1352,9 +1293,7 @@ int paid_seed_train(paid_ctx *c, const float *x, const float *y, int n, const pa
   auto one_step = [&](hipStream_t st) -> hipError_t {
     hipError_t e;
     if ((e = mlp_gather(dx, dy, idx.as<int>(), step, bs, Xb, Yb, st)) != hipSuccess) return e;
-    if ((e = mlp_forward(W, Xb, bs, a, yhat, st)) != hipSuccess) return e;
-    if ((e = mlp_mse(yhat, Yb, (long)bs * kMlpOut, dY, lh, step, st)) != hipSuccess) return e;
-    if ((e = mlp_backward(W, Xb, bs, a, dY, G, st)) != hipSuccess) return e;
+    if ((e = mlp_loss_grad(W, Xb, Yb, bs, a, G, lh, step, st)) != hipSuccess) return e;
     if ((e = mlp_adam(W, G, M, V, np, 0, step, o.lr, o.lr_final, o.steps, st)) != hipSuccess) return e;
     return mlp_count(step, st);
   };

@@ -227,30 +227,44 @@ struct MlpLayout {
   long w[4], b[4];   // offsets of W_l [out][in] and b_l [out]
   long total;
 };
-struct MlpAct {        // per-sample buffers: Z pre-activations, A activations, D deltas
-  float *Z[4];         // Z[0..2] [n][128] (Z[3] unused)
-  float *A[3];         // [n][128]
-  float *D[3];         // [n][128]
+struct MlpAct {        // buffers of a training pass over n samples
+  float *A[3];         // [n][128] activations
+  float *D[3];         // [n][128] deltas (d loss / d pre-activation)
+  float *dY;           // [n][256] deltas of the outputs
+  double *part;        // [ceil(n / 16)] workgroups' sums of squares
 };
+// floats of an MlpAct's buffers for n samples (part first)
+constexpr long mlp_act_floats(long n) { return 2 * ((n + 15) / 16) + 64 + n * (6 * kMlpHid + kMlpOut); }
+// the buffers, carved from p (8-byte aligned)
+inline MlpAct mlp_carve(float *p, long n) {
+  MlpAct a;
+  a.part = reinterpret_cast<double *>(p);
+  p += 2 * ((n + 15) / 16);
+  for (int l = 0; l < 3; ++l) {
+    a.A[l] = p + (long)l * kMlpHid * n;
+    a.D[l] = p + (long)(3 + l) * kMlpHid * n;
+  }
+  a.dY = p + 6 * kMlpHid * n;
+  return a;
+}
 MlpLayout mlp_layout();
 hipError_t launch_seed_features(const Entry *entries, const double *q, int n_ctr, int n_q, int n_ch,
                                 int ch_first, float *X, int *fold, hipStream_t s);
-hipError_t mlp_forward(const float *w, const float *x, int n, MlpAct &a, float *y, hipStream_t s);
-hipError_t mlp_backward(const float *w, const float *x, int n, MlpAct &a, float *dY, float *grad,
-                        hipStream_t s);
-hipError_t mlp_mse(const float *yhat, const float *y, long ne, float *dY, double *loss,
-                   const int *step, hipStream_t s);
+hipError_t mlp_forward(const float *w, const float *x, int n, float *y, hipStream_t s);
+// loss (at loss[*step] where a history is kept) and gradient
+hipError_t mlp_loss_grad(const float *w, const float *x, const float *y, int n, const MlpAct &a, float *grad,
+                         double *loss, const int *step, hipStream_t s);
 hipError_t mlp_adam(float *w, const float *g, float *m, float *v, long np, int t, const int *tdev,
                     float lr0, float lr1, int steps, hipStream_t s);
 hipError_t mlp_gather(const float *X, const float *Y, const int *idx, const int *step, int bs,
                       float *Xb, float *Yb, hipStream_t s);
 hipError_t mlp_count(int *c, hipStream_t s);
 
-// fixed working memory of paid_mlp_loss_grad_noalloc: per-sample buffers of
-// at most kNoAllocMaxN samples (9 x 128 + 2 x 256 floats each) and the loss
-// (two floats' room for one double, 256-byte aligned after the buffers)
+// fixed working memory of paid_mlp_loss_grad_noalloc: the buffers of at most
+// kNoAllocMaxN samples and the loss (two floats' room for one double, 256-byte
+// aligned after the buffers)
 constexpr int kNoAllocMaxN = PAID_NOALLOC_MAX_N;
-constexpr long kNoAllocActFloats = (long)kNoAllocMaxN * (9 * kMlpHid + 2 * kMlpOut);
+constexpr long kNoAllocActFloats = (mlp_act_floats(kNoAllocMaxN) + 63) / 64 * 64;
 constexpr long kNoAllocFloats = kNoAllocActFloats + 64;
 // device address of this device's copy of the array (call with the device current)
 hipError_t noalloc_scratch_address(float **ptr);

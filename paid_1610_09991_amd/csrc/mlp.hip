@@ -1,7 +1,7 @@
 // mlp.hip -- the subdivision-density model of the learned seeding: model
 // features of each container, and the FP32 kernels of a 7 -> 128 -> 128 ->
-// 128 -> 256 perceptron (GELU on the hidden layers): forward, backward, mean
-// squared error, Adam.  Training and inference share the same kernels.
+// 128 -> 256 perceptron (GELU on the hidden layers): forward, backward with the
+// mean squared error, Adam.  Training and inference share the same kernels.
 //
 // The model predicts, per cell of a 16 x 16 grid over the zone, log2(1 + n)
 // with n the number of leaves the converged adaptive tree has in that cell.
@@ -20,131 +20,291 @@ namespace paid {
 
 namespace {
 
-constexpr int kBM = 64, kBN = 64, kBK = 16;
-
 __device__ inline float gelu(float z) { return 0.5f * z * (1.0f + erff(z * 0.70710678118654752f)); }
 __device__ inline float gelu_d(float z) {
   return 0.5f * (1.0f + erff(z * 0.70710678118654752f)) +
          z * expf(-0.5f * z * z) * 0.39894228040143268f;
 }
 
-// Tiled FP32 product C[m][n] = sum_k A(m,k) B(k,n), A(m,k) = A[m*sam + k*sak],
-// B(k,n) = B[k*sbk + n*sbn]; each of 256 threads owns a 4 x 4 block of a
-// 64 x 64 tile, k runs in chunks of 16 staged through LDS and in a fixed
-// order, so results do not depend on the launch.
-// Epilogues: kFwd: z = C + bias[n] -> Z (if non-null), Y = act ? gelu(z) : z
-//            kBwdData: Y = C * gelu'(Zp[m][n])
-//            kPlain: Y = C
-enum { kFwd = 0, kBwdData = 1, kPlain = 2 };
+// ------------------------------------------------------------------ matrix-core pieces
+// FP32 products on the matrix cores (16 x 16 x 4, FP32 in, FP32 accumulation).
+// Lane (kk, m) = (lane >> 4, lane & 15) holds A[m][k] and B[k][m] of the step's
+// four k, and result register i is row 4 kk + i, column m.  The order of k is
+// free: quarter kk takes k = kk K/4 + s at step s, so that a lane's operands of
+// consecutive steps are consecutive in memory (16-byte loads).  Fixed orders
+// throughout: results do not depend on the launch.
+//
+// A workgroup of eight waves takes 16 RT samples through all layers, with the
+// activations in LDS: one launch for the whole pass, no activations in global
+// memory.  Each wave owns 16 of the 128 columns of a layer (32 of the 256
+// outputs), reads their weights once from L2 into registers and uses them for
+// RT row tiles.  One product kernel per layer instead (64 x 64 tiles, scalar
+// FMAs, activations through memory and a device allocation per call) took 108
+// us of kernels and 168 us a call for 23,040 samples (now 64 and 74), and a
+// training step of 256 samples 17 launches of 8-16 workgroups each, 516 us a
+// call with its Adam step (now three launches, 62 us).
+typedef float f4 __attribute__((ext_vector_type(4)));
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));  // caller's arrays: 4-byte aligned
 
-template <int EPI>
-__global__ void __launch_bounds__(256)
-    k_gemm(int Mr, int Nc, int K, const float *__restrict__ A, long sam, long sak,
-           const float *__restrict__ B, long sbk, long sbn, const float *__restrict__ bias,
-           const float *__restrict__ Zp, float *__restrict__ Z, float *__restrict__ Y, int act) {
-  __shared__ float As[kBK][kBM + 4];
-  __shared__ float Bs[kBK][kBN + 4];
-  const int t = threadIdx.x, tx = t & 15, ty = t >> 4;
-  const int m0 = blockIdx.x * kBM, n0 = blockIdx.y * kBN;
-  float acc[4][4];
+constexpr int kWaves = 8, kThreads = 64 * kWaves;
+constexpr int kHidLd = kMlpHid + 4, kOutLd = kMlpOut + 4;  // LDS leading dimensions (bank spread)
+static_assert(kMlpHid == 16 * kWaves, "a wave owns 16 hidden columns");
+
+__device__ inline f4 mfma4(float a, float b, f4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+
+// acc[t] = X W^T for the wave's 16 columns n0.. : X [16 RT][K] in LDS (leading
+// dimension ld), W [..][K] row-major, K a multiple of 16
+template <int RT, int K>
+__device__ inline void mul_wt(const float *X, int ld, const float *W, int n0, f4 (&acc)[RT]) {
+  const int lane = threadIdx.x & 63, m = lane & 15, kk = lane >> 4;
+  constexpr int Q = K / 16;  // float4 per quarter
+  f4 b[Q];
+  const f4u *w = reinterpret_cast<const f4u *>(W + (long)(n0 + m) * K + kk * (K / 4));
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int s = 0; s < Q; ++s) b[s] = w[s];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = 0.0f;
-  for (int k0 = 0; k0 < K; k0 += kBK) {
+  for (int t = 0; t < RT; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      int e = t + 256 * r;
-      // A tile: 64 rows x 16 k; B tile: 16 k x 64 cols
-      int am = e / kBK, ak = e % kBK;
-      int gm = m0 + am, gk = k0 + ak;
-      As[ak][am] = (gm < Mr && gk < K) ? A[(long)gm * sam + (long)gk * sak] : 0.0f;
-      int bk = e / kBN, bn = e % kBN;
-      int gk2 = k0 + bk, gn = n0 + bn;
-      Bs[bk][bn] = (gk2 < K && gn < Nc) ? B[(long)gk2 * sbk + (long)gn * sbn] : 0.0f;
+  for (int s = 0; s < Q; ++s)
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+      const f4 x = *reinterpret_cast<const f4 *>(X + (16 * t + m) * ld + kk * (K / 4) + 4 * s);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc[t] = mfma4(x[i], b[s][i], acc[t]);
     }
-    __syncthreads();
+}
+
+// acc[t] = X W for the wave's 16 columns n0.. : X [16 RT][K] in LDS, W [K][128]
+template <int RT, int K>
+__device__ inline void mul_w(const float *X, int ld, const float *W, int n0, f4 (&acc)[RT]) {
+  const int lane = threadIdx.x & 63, m = lane & 15, kk = lane >> 4;
+  constexpr int C = 8;  // float4 of X a chunk: 32 weights in flight
+  const float *w = W + (long)kk * (K / 4) * kMlpHid + n0 + m;
 #pragma unroll
-    for (int kk = 0; kk < kBK; ++kk) {
-      float a[4], b[4];
+  for (int t = 0; t < RT; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+  for (int s0 = 0; s0 < K / 16; s0 += C) {
+    float b[4 * C];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[kk][ty * 4 + i];
+    for (int s = 0; s < 4 * C; ++s) b[s] = w[(long)(4 * s0 + s) * kMlpHid];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tx * 4 + j];
+    for (int s = 0; s < C; ++s)
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int t = 0; t < RT; ++t) {
+        const f4 x = *reinterpret_cast<const f4 *>(X + (16 * t + m) * ld + kk * (K / 4) + 4 * (s0 + s));
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    int gm = m0 + ty * 4 + i;
-    if (gm >= Mr) continue;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      int gn = n0 + tx * 4 + j;
-      if (gn >= Nc) continue;
-      long o = (long)gm * Nc + gn;
-      float v = acc[i][j];
-      if (EPI == kFwd) {
-        v += bias[gn];
-        if (Z) Z[o] = v;
-        Y[o] = act ? gelu(v) : v;
-      } else if (EPI == kBwdData) {
-        Y[o] = v * gelu_d(Zp[o]);
-      } else {
-        Y[o] = v;
+        for (int i = 0; i < 4; ++i) acc[t] = mfma4(x[i], b[4 * s + i], acc[t]);
       }
+  }
+}
+
+// The hidden layers of 16 RT samples from r0 on: the last hidden activations
+// end in X[0] (LDS, [16 RT][kHidLd] each of two buffers).  TRAIN: also gelu' of
+// the pre-activations into G[l] (LDS) and the activations into a.A[l] (global).
+template <int RT, bool TRAIN>
+__device__ void hidden_layers(const MlpLayout &L, const float *w, const float *x, int n, long r0, float *X0,
+                              float *X1, float *G, const MlpAct &a) {
+  constexpr int R = 16 * RT;
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6, m = lane & 15, kk = lane >> 4, n0 = 16 * wv;
+  auto put = [&](int l, float *Y, int row, int col, float z) {
+    const float y = gelu(z);
+    Y[row * kHidLd + col] = y;
+    if (TRAIN) {
+      G[(l * R + row) * kHidLd + col] = gelu_d(z);
+      if (r0 + row < n) a.A[l][(r0 + row) * kMlpHid + col] = y;
+    }
+  };
+  // 7 inputs: scalar FMAs, a column per thread, every fourth row (their
+  // samples through X1, which nothing uses yet)
+  for (int e = t; e < R * kMlpIn; e += kThreads) X1[e] = r0 * kMlpIn + e < (long)n * kMlpIn ? x[r0 * kMlpIn + e] : 0.f;
+  __syncthreads();
+  {
+    const int col = t & (kMlpHid - 1);
+    float wr[kMlpIn];
+#pragma unroll
+    for (int k = 0; k < kMlpIn; ++k) wr[k] = w[L.w[0] + (long)col * kMlpIn + k];
+    const float b = w[L.b[0] + col];
+    for (int row = t / kMlpHid; row < R; row += kThreads / kMlpHid) {
+      float z = 0.f;
+#pragma unroll
+      for (int k = 0; k < kMlpIn; ++k) z = fmaf(X1[row * kMlpIn + k], wr[k], z);
+      put(0, X0, row, col, z + b);
     }
   }
-}
-
-template <int EPI>
-void gemm(hipStream_t s, int Mr, int Nc, int K, const float *A, long sam, long sak, const float *B,
-          long sbk, long sbn, const float *bias, const float *Zp, float *Z, float *Y, int act) {
-  dim3 grid((Mr + kBM - 1) / kBM, (Nc + kBN - 1) / kBN);
-  hipLaunchKernelGGL((k_gemm<EPI>), grid, dim3(256), 0, s, Mr, Nc, K, A, sam, sak, B, sbk, sbn,
-                     bias, Zp, Z, Y, act);
-}
-
-// gb[o] = sum_n dZ[n][o], rows in order
-__global__ void k_bias_grad(const float *dZ, int n, int no, float *gb) {
-  int o = blockIdx.x * blockDim.x + threadIdx.x;
-  if (o >= no) return;
-  float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
-  int r = 0;
-  for (; r + 3 < n; r += 4) {
-    a0 += dZ[(long)r * no + o];
-    a1 += dZ[(long)(r + 1) * no + o];
-    a2 += dZ[(long)(r + 2) * no + o];
-    a3 += dZ[(long)(r + 3) * no + o];
-  }
-  for (; r < n; ++r) a0 += dZ[(long)r * no + o];
-  gb[o] = (a0 + a1) + (a2 + a3);
-}
-
-// dZ = 2 (yhat - y) / (n * 256); loss = mean of squares (FP64, one block,
-// fixed order), written to loss[*step] when a history is kept
-__global__ void __launch_bounds__(1024) k_mse(const float *yhat, const float *y, long ne,
-                                              float *dZ, double *loss, const int *step) {
-  __shared__ double sh[1024];
-  const int t = threadIdx.x;
-  const float sc = (float)(2.0 / (double)ne);
-  double a = 0.0;
-  for (long e = t; e < ne; e += 1024) {
-    float r = yhat[e] - y[e];
-    dZ[e] = sc * r;
-    a += (double)r * (double)r;
-  }
-  sh[t] = a;
   __syncthreads();
-  for (int o = 512; o > 0; o >>= 1) {
-    if (t < o) sh[t] += sh[t + o];
+#pragma unroll
+  for (int l = 1; l < 3; ++l) {
+    const float *X = (l == 1) ? X0 : X1;
+    float *Y = (l == 1) ? X1 : X0;
+    f4 acc[RT];
+    mul_wt<RT, kMlpHid>(X, kHidLd, w + L.w[l], n0, acc);
+    const float b = w[L.b[l] + n0 + m];
+#pragma unroll
+    for (int q = 0; q < RT; ++q)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) put(l, Y, 16 * q + 4 * kk + i, n0 + m, acc[q][i] + b);
     __syncthreads();
   }
-  if (t == 0 && loss) loss[step ? *step : 0] = sh[0] / (double)ne;
+}
+
+template <int RT>
+__global__ void __launch_bounds__(kThreads) k_forward(MlpLayout L, const float *__restrict__ w,
+                                                      const float *__restrict__ x, int n, float *__restrict__ y) {
+  constexpr int R = 16 * RT;
+  __shared__ __align__(16) float X[2][R * kHidLd];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, m = lane & 15, kk = lane >> 4;
+  const long r0 = (long)blockIdx.x * R;
+  hidden_layers<RT, false>(L, w, x, n, r0, X[0], X[1], nullptr, MlpAct{});
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    const int n0 = 32 * wv + 16 * c;
+    f4 acc[RT];
+    mul_wt<RT, kMlpHid>(X[0], kHidLd, w + L.w[3], n0, acc);
+    const float b = w[L.b[3] + n0 + m];
+#pragma unroll
+    for (int q = 0; q < RT; ++q)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const long row = r0 + 16 * q + 4 * kk + i;
+        if (row < n) y[row * kMlpOut + n0 + m] = acc[q][i] + b;
+      }
+  }
+}
+
+// Forward pass, squared error and the backward pass down to every layer's
+// delta, of 16 samples a workgroup: activations, deltas (global, for the
+// weight gradients) and the workgroup's sum of squares (FP64, fixed order).
+__global__ void __launch_bounds__(kThreads) k_deltas(MlpLayout L, const float *__restrict__ w,
+                                                     const float *__restrict__ x, const float *__restrict__ y, int n,
+                                                     MlpAct a) {
+  constexpr int R = 16;
+  __shared__ __align__(16) float X[2][R * kHidLd];
+  __shared__ __align__(16) float G[3 * R * kHidLd];
+  __shared__ __align__(16) float O[R * kOutLd];
+  __shared__ double sq[kThreads];
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6, m = lane & 15, kk = lane >> 4;
+  const long r0 = (long)blockIdx.x * R;
+  hidden_layers<1, true>(L, w, x, n, r0, X[0], X[1], G, a);
+  // outputs: dY = 2 (yhat - y) / (n 256)
+  const float sc = (float)(2.0 / ((double)n * kMlpOut));
+  double s = 0.0;
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    const int n0 = 32 * wv + 16 * c;
+    f4 acc[1];
+    mul_wt<1, kMlpHid>(X[0], kHidLd, w + L.w[3], n0, acc);
+    const float b = w[L.b[3] + n0 + m];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int row = 4 * kk + i;
+      float d = 0.f;
+      if (r0 + row < n) {
+        const float e = (acc[0][i] + b) - y[(r0 + row) * kMlpOut + n0 + m];
+        d = sc * e;
+        s += (double)e * (double)e;
+        a.dY[(r0 + row) * kMlpOut + n0 + m] = d;
+      }
+      O[row * kOutLd + n0 + m] = d;
+    }
+  }
+  sq[t] = s;
+  __syncthreads();
+  for (int o = kThreads / 2; o > 0; o >>= 1) {
+    if (t < o) sq[t] += sq[t + o];
+    __syncthreads();
+  }
+  if (t == 0) a.part[blockIdx.x] = sq[0];
+  // deltas of the hidden layers: D_l = (D_{l+1} W_{l+1}) gelu'(Z_l)
+#pragma unroll
+  for (int l = 2; l >= 0; --l) {
+    f4 acc[1];
+    if (l == 2)
+      mul_w<1, kMlpOut>(O, kOutLd, w + L.w[3], 16 * wv, acc);
+    else
+      mul_w<1, kMlpHid>(l == 1 ? X[0] : X[1], kHidLd, w + L.w[l + 1], 16 * wv, acc);
+    float *D = l == 1 ? X[1] : X[0];
+    if (l == 2) __syncthreads();  // (X[0] held the forward pass's last activations)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int row = 4 * kk + i, col = 16 * wv + m;
+      const float d = acc[0][i] * G[(l * R + row) * kHidLd + col];
+      D[row * kHidLd + col] = d;
+      if (r0 + row < n) a.D[l][(r0 + row) * kMlpHid + col] = d;
+    }
+    __syncthreads();
+  }
+}
+
+// Weight and bias gradients gW[o][i] = sum_r d[r][o] X[r][i], gb[o] = sum_r
+// d[r][o]: a workgroup per 32 x 32 tile of one layer's weights, its eight waves
+// take an eighth of the samples each, and the parts are added in wave order.
+// The first workgroup also adds up the loss.
+constexpr int kGradTiles[4] = {4, 16, 16, 32};  // tiles of each layer: (out / 32) (in / 32)
+constexpr int kGradBlocks = 4 + 16 + 16 + 32;
+
+__global__ void __launch_bounds__(kThreads) k_grads(MlpLayout L, const float *__restrict__ x, int n, MlpAct a,
+                                                    float *__restrict__ grad, int parts, double *loss,
+                                                    const int *step) {
+  __shared__ float S[kWaves][32 * 33 + 32];
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6, m = lane & 15, kk = lane >> 4;
+  int l = 0, tile = blockIdx.x;
+  while (tile >= kGradTiles[l]) tile -= kGradTiles[l++];
+  const int ni = L.ni[l], no = L.no[l], it = (ni + 31) / 32;
+  const int o0 = 32 * (tile / it), i0 = 32 * (tile % it);
+  const float *d = l == 3 ? a.dY : a.D[l], *X = l == 0 ? x : a.A[l - 1];
+  const int per = ((n + kWaves - 1) / kWaves + 3) & ~3;
+  const int ra = wv * per, rb = ra + per < n ? ra + per : n;
+  f4 acc[2][2];
+  float bs[2] = {0.f, 0.f};
+#pragma unroll
+  for (int p = 0; p < 2; ++p)
+#pragma unroll
+    for (int q = 0; q < 2; ++q) acc[p][q] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+  for (int r = ra; r < rb; r += 4) {
+    const long row = r + kk;
+    const bool in = row < rb;
+    float da[2], xb[2];
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      da[p] = in ? d[row * no + o0 + 16 * p + m] : 0.f;
+      xb[p] = (in && i0 + 16 * p + m < ni) ? X[row * ni + i0 + 16 * p + m] : 0.f;
+      bs[p] += da[p];
+    }
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+      for (int q = 0; q < 2; ++q) acc[p][q] = mfma4(da[p], xb[q], acc[p][q]);
+  }
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) S[wv][(16 * p + 4 * kk + i) * 33 + 16 * q + m] = acc[p][q][i];
+    float b = bs[p];  // over the four rows of a step: lanes m, m + 16, m + 32, m + 48
+    b += __shfl_xor(b, 16, 64);
+    b += __shfl_xor(b, 32, 64);
+    if (kk == 0) S[wv][32 * 33 + 16 * p + m] = b;
+  }
+  __syncthreads();
+  for (int e = t; e < 32 * 32; e += kThreads) {
+    const int o = e >> 5, i = e & 31;
+    float s = S[0][o * 33 + i];
+    for (int v = 1; v < kWaves; ++v) s += S[v][o * 33 + i];
+    if (i0 + i < ni) grad[L.w[l] + (long)(o0 + o) * ni + i0 + i] = s;
+  }
+  if (i0 == 0 && t < 32) {
+    float s = S[0][32 * 33 + t];
+    for (int v = 1; v < kWaves; ++v) s += S[v][32 * 33 + t];
+    grad[L.b[l] + o0 + t] = s;
+  }
+  if (blockIdx.x == 0 && wv == kWaves - 1 && loss) {
+    double s = 0.0;
+    for (int p = lane; p < parts; p += 64) s += a.part[p];
+    for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o, 64);
+    if (lane == 0) loss[step ? *step : 0] = s / ((double)n * kMlpOut);
+  }
 }
 
 // Adam (beta1 0.9, beta2 0.999, eps 1e-8) with cosine decay of the rate from
@@ -232,43 +392,23 @@ MlpLayout mlp_layout() {
   return L;
 }
 
-hipError_t mlp_forward(const float *w, const float *x, int n, MlpAct &a, float *y, hipStream_t s) {
+// 16 samples a workgroup fill the chip up to 4,096 samples; above that 32,
+// which read the weights (268 KB from L2) half as often
+hipError_t mlp_forward(const float *w, const float *x, int n, float *y, hipStream_t s) {
   const MlpLayout L = mlp_layout();
-  const float *in = x;
-  for (int l = 0; l < 4; ++l) {
-    const int ni = L.ni[l], no = L.no[l];
-    float *Z = a.Z[l], *Y = (l == 3) ? y : a.A[l];
-    gemm<kFwd>(s, n, no, ni, in, ni, 1, w + L.w[l], 1, ni, w + L.b[l], nullptr, Z, Y, l < 3);
-    in = Y;
-  }
+  if (n <= 4096)
+    hipLaunchKernelGGL(k_forward<1>, dim3((n + 15) / 16), dim3(kThreads), 0, s, L, w, x, n, y);
+  else
+    hipLaunchKernelGGL(k_forward<2>, dim3((n + 31) / 32), dim3(kThreads), 0, s, L, w, x, n, y);
   return hipGetLastError();
 }
 
-hipError_t mlp_backward(const float *w, const float *x, int n, MlpAct &a, float *dY, float *grad,
-                        hipStream_t s) {
+hipError_t mlp_loss_grad(const float *w, const float *x, const float *y, int n, const MlpAct &a, float *grad,
+                         double *loss, const int *step, hipStream_t s) {
   const MlpLayout L = mlp_layout();
-  // dY holds dLoss/dz of the output layer; walk the layers down
-  float *d = dY;
-  for (int l = 3; l >= 0; --l) {
-    const int ni = L.ni[l], no = L.no[l];
-    const float *Ain = (l == 0) ? x : a.A[l - 1];
-    // gW[o][i] = sum_r d[r][o] Ain[r][i]
-    gemm<kPlain>(s, no, ni, n, d, 1, no, Ain, ni, 1, nullptr, nullptr, nullptr, grad + L.w[l], 0);
-    hipLaunchKernelGGL(k_bias_grad, dim3((no + 255) / 256), dim3(256), 0, s, d, n, no,
-                       grad + L.b[l]);
-    if (l > 0) {
-      // d_prev[r][i] = (sum_o d[r][o] W[o][i]) * gelu'(Z_{l-1}[r][i])
-      float *dn = a.D[l - 1];
-      gemm<kBwdData>(s, n, ni, no, d, no, 1, w + L.w[l], ni, 1, nullptr, a.Z[l - 1], nullptr, dn, 0);
-      d = dn;
-    }
-  }
-  return hipGetLastError();
-}
-
-hipError_t mlp_mse(const float *yhat, const float *y, long ne, float *dY, double *loss,
-                   const int *step, hipStream_t s) {
-  hipLaunchKernelGGL(k_mse, dim3(1), dim3(1024), 0, s, yhat, y, ne, dY, loss, step);
+  const int blocks = (n + 15) / 16;
+  hipLaunchKernelGGL(k_deltas, dim3(blocks), dim3(kThreads), 0, s, L, w, x, y, n, a);
+  hipLaunchKernelGGL(k_grads, dim3(kGradBlocks), dim3(kThreads), 0, s, L, x, n, a, grad, blocks, loss, step);
   return hipGetLastError();
 }
 
@@ -292,8 +432,8 @@ hipError_t mlp_count(int *c, hipStream_t s) {
 
 // ------------------------------------------------------------------ fixed working memory
 // Working memory of the loss-and-gradient entry point that allocates
-// nothing: the per-sample buffers of kNoAllocMaxN samples (pre-activations,
-// activations, deltas, outputs, output deltas) and the FP64 loss.  Every
+// nothing: the per-sample buffers of kNoAllocMaxN samples (activations, deltas,
+// output deltas), the workgroups' sums of squares and the FP64 loss.  Every
 // element a call reads is written earlier in the same call, so nothing has
 // to start at zero.  Each device holds its own copy of the array at its own
 // address; host code must use that address (from hipGetSymbolAddress), never
