@@ -54,7 +54,7 @@ struct paid_ctx {
   // workspace
   DevBuf entries, tab, zeta, svals, ctr, qv, ffc, pcoef;
   DevBuf code, key, Q, E;
-  DevBuf slot_i, slot_d, sel, dv, de, dep, itau, errp, stl, counters, outs, errs;
+  DevBuf slot_i, slot_d, sel, selc, sctr, dv, de, dep, itau, errp, stl, counters, outs, errs;
   // learned seeding
   DevBuf seedw, sfeat, sfold, sy, pyr, seedd, ifill, labtmp, rowsz, rperm, movei, upart;
   bool seed_on = false;
@@ -73,7 +73,7 @@ struct paid_ctx {
   long leaf_cap = 0;
   DevBuf lcodes, lq;
   int *host_counters = nullptr;  // pinned
-  int max_J = 1;                 // rows of the largest table of the last build
+  int max_tab = 1, max_close = 1;  // doubles of the largest tables of the last build, and of their close rows
   int lds_limit = 0;             // LDS bytes per workgroup (device attribute)
   float *noalloc = nullptr;      // this device's fixed working memory (paid_mlp_loss_grad_noalloc)
   // profile: around the evaluation launch of the two rounds in flight
@@ -180,6 +180,12 @@ int ensure_rule(paid_ctx *c) {
       rc.cdel[d][a] = cos(del);
       rc.sdel[d][a] = sin(del);
     }
+  double f = 1.0;  // factorials: sin_c[7 - i] = (-1)^(i+1) / (2 i + 3)!, cos_c[8 - i] = (-1)^i / (2 i + 2)!
+  for (int n = 1; n <= 18; ++n) {
+    f *= n;
+    if (n >= 3 && (n & 1)) rc.sin_c[7 - (n - 3) / 2] = (((n - 3) / 2) & 1 ? 1.0 : -1.0) / f;
+    if (n >= 2 && !(n & 1)) rc.cos_c[8 - (n - 2) / 2] = (((n - 2) / 2) & 1 ? -1.0 : 1.0) / f;
+  }
   HIPCHK(c, set_rule_constants(rc));
   if (dev >= 0 && dev < 64) g_rule_ready[dev] = 1;
   return PAID_OK;
@@ -187,7 +193,7 @@ int ensure_rule(paid_ctx *c) {
 
 // host bookkeeping of one parameter row's table (sizes only; the table
 // itself is computed on the device)
-Entry make_entry(const paid_params &p, int kind, int &off) {
+Entry make_entry(const paid_params &p, int kind, long &off) {
   Entry e;
   memset(&e, 0, sizeof e);
   e.t = p.t;
@@ -202,6 +208,7 @@ Entry make_entry(const paid_params &p, int kind, int &off) {
     e.inv_w = 1.0 / e.w;
     double top = e.emax * 1.01 + 1e-3 * e.w;
     e.J = tab_rows(top, e.w);
+    e.JV = val_rows(top, e.w);
     double cJ, hJ;
     tab_interval(e.J - 1, e.w, cJ, hJ);
     double xJ = cJ + hJ;  // top of the last interval
@@ -212,10 +219,11 @@ Entry make_entry(const paid_params &p, int kind, int &off) {
     e.w = 1.0;
     e.inv_w = 1.0;
     e.J = 1;
+    e.JV = 1;
     e.nmats = 0;
   }
   e.tab_off = off;
-  off += e.J * kTabStride;
+  off += tab_doubles(e);
   return e;
 }
 
@@ -233,23 +241,28 @@ int lds_limit(paid_ctx *c) {
 
 int build_tables(paid_ctx *c, const paid_params *params, int n, int kind) {
   std::vector<Entry> es(n);
-  int off = 0, maxJ = 1;
+  int max_rows = 1, max_tab = 1, max_close = 1;
+  long off = 0, max_points = 1;
   for (int i = 0; i < n; ++i) {
     es[i] = make_entry(params[i], kind, off);
-    if (es[i].J > maxJ) maxJ = es[i].J;
+    max_rows = std::max(max_rows, es[i].JV + es[i].J);
+    max_tab = std::max(max_tab, tab_doubles(es[i]));
+    max_close = std::max(max_close, close_doubles(es[i]));
+    max_points = std::max(max_points, (long)es[i].JV * kValHalf + (long)es[i].J * kTabHalf);
   }
   HIPCHK(c, c->entries.ensure(sizeof(Entry) * n));
   HIPCHK(c, c->tab.ensure(sizeof(double) * (size_t)off));
   HIPCHK(c, c->zeta.ensure(sizeof(double) * (size_t)n * (kTabKTail + 1)));
-  HIPCHK(c, c->svals.ensure(sizeof(double2) * (size_t)n * maxJ * kTabPts));
+  HIPCHK(c, c->svals.ensure(sizeof(double2) * (size_t)n * max_points));
   HIPCHK(c, hipMemcpyAsync(c->entries.p, es.data(), sizeof(Entry) * n, hipMemcpyHostToDevice,
                            c->stream));
-  HIPCHK(c, hipMemsetAsync(c->tab.p, 0, sizeof(double) * (size_t)off, c->stream));
   TabArgs a;
   a.entries = c->entries.as<Entry>();
   a.n_entries = n;
-  a.max_J = maxJ;
-  c->max_J = maxJ;
+  a.max_rows = max_rows;
+  a.max_points = max_points;
+  c->max_tab = (max_tab + 1) / 2 * 2;  // (what lies behind it in LDS stays 16-byte aligned)
+  c->max_close = max_close;
   a.tab = c->tab.as<double>();
   a.zeta = c->zeta.as<double>();
   a.svals = c->svals.as<double2>();
@@ -471,7 +484,7 @@ void paid_destroy(paid_ctx *c) {
   if (c->stream) (void)hipStreamSynchronize(c->stream);
   DevBuf *bufs[] = {&c->entries, &c->tab,  &c->zeta,  &c->svals, &c->ctr,   &c->qv,
                     &c->ffc,     &c->code, &c->key,   &c->Q,     &c->E,     &c->slot_i,
-                    &c->slot_d,  &c->sel,  &c->dv,    &c->de,    &c->dep,   &c->itau,
+                    &c->slot_d,  &c->sel,  &c->selc,  &c->sctr,  &c->dv,    &c->de,    &c->dep,   &c->itau,
                     &c->errp,    &c->stl,  &c->counters, &c->outs, &c->errs,
                     &c->seedw,   &c->sfeat, &c->sfold, &c->sy,  &c->pyr,
                     &c->seedd,   &c->ifill, &c->labtmp, &c->pairw, &c->born, &c->lcodes,
@@ -537,7 +550,8 @@ int paid_integrate(paid_ctx *c, const paid_params *params, int n_params, const d
   memset(&P, 0, sizeof P);
   P.entries = c->entries.as<Entry>();
   P.tab = c->tab.as<double>();
-  P.tab_rows = c->max_J;
+  P.tab_doubles = c->max_tab;
+  P.close_doubles = c->max_close;
   P.lds_limit = lds_limit(c);
   P.ctr = c->ctr.as<Ctr>();
   P.n_ctr = n_ctr;
@@ -560,8 +574,8 @@ int paid_integrate(paid_ctx *c, const paid_params *params, int n_params, const d
   P.eval_layout = cfg.eval_layout;
   P.sym = cfg.symmetry;
   if (eval_lds_bytes(P) == 0)
-    return fail(c, PAID_EINVAL, "frequency-sum table of %d rows does not fit in LDS (T too small against the band)",
-                P.tab_rows);
+    return fail(c, PAID_EINVAL, "frequency-sum table of %d doubles does not fit in LDS (T too small against the band)",
+                P.tab_doubles);
   P.products = leaves_hold_products(P) ? 1 : 0;
   const int MQ = P.MQ = P.products ? kProd : MU;
   if ((rc = stage_pair_coefficients(c, P, hff.data())) != PAID_OK) return rc;
@@ -620,13 +634,15 @@ int paid_integrate(paid_ctx *c, const paid_params *params, int n_params, const d
   HIPCHK(c, c->errp.ensure(sizeof(double) * W * (size_t)MU));
   HIPCHK(c, c->itau.ensure(sizeof(float) * W * (size_t)MU));
   HIPCHK(c, c->sel.ensure(sizeof(int) * W * (size_t)bmax));
+  HIPCHK(c, c->selc.ensure(sizeof(uint64_t) * W * (size_t)bmax));
+  HIPCHK(c, c->sctr.ensure(sizeof(Ctr) * W));
   HIPCHK(c, c->dv.ensure(sizeof(double) * W * (size_t)bmax * MQ));
   HIPCHK(c, c->de.ensure(sizeof(double) * W * (size_t)bmax));
   if (store_E) HIPCHK(c, c->dep.ensure(sizeof(double) * W * (size_t)bmax * MU));
   HIPCHK(c, c->stl.ensure(sizeof(long) * 3 * W));
   HIPCHK(c, c->ifill.ensure(sizeof(int) * W * (size_t)bmax));
   if (lockstep) HIPCHK(c, c->born.ensure(sizeof(unsigned int) * regions));
-  HIPCHK(c, c->counters.ensure(256));
+  HIPCHK(c, c->counters.ensure(256 + sizeof(int) * kXcds * kXcdStride));
   const bool out_dev = is_device_ptr(out), err_dev = err_out && is_device_ptr(err_out);
   const size_t out_bytes = sizeof(double) * (size_t)n_ctr * M * M;
   if (!out_dev) HIPCHK(c, c->outs.ensure(out_bytes));
@@ -655,6 +671,9 @@ int paid_integrate(paid_ctx *c, const paid_params *params, int n_params, const d
   P.st_depth = si + 5 * W;
   P.woff = si + 6 * W;  // W + 1 entries
   P.sel = c->sel.as<int>();
+  P.selc = c->selc.as<uint64_t>();
+  P.sctr = c->sctr.as<Ctr>();
+  P.one_row = n_params == 1;
   P.val = c->slot_d.as<double>();
   P.err = c->slot_d.as<double>() + W * (size_t)MQ;
   P.errp = store_E ? c->errp.as<double>() : nullptr;
@@ -669,7 +688,8 @@ int paid_integrate(paid_ctx *c, const paid_params *params, int n_params, const d
   int *cnt = c->counters.as<int>();
   P.qhead = cnt;            // [0]
   P.counters = cnt + 4;     // [4..7]: done, not converged, work items
-  P.gstats = reinterpret_cast<long long *>(cnt + 16);  // [16..23]
+  P.gstats = reinterpret_cast<long long *>(cnt + 16);  // [16..25]
+  P.xcount = cnt + 64;
   P.out = out_dev ? out : c->outs.as<double>();
   P.born = lockstep ? c->born.as<unsigned int>() : nullptr;
   int *lcodes_dev = nullptr;
@@ -971,7 +991,8 @@ int paid_children_eval(paid_ctx *c, const paid_params *p, const double *l, unsig
   memset(&P, 0, sizeof P);
   P.entries = c->entries.as<Entry>();
   P.tab = c->tab.as<double>();
-  P.tab_rows = c->max_J;
+  P.tab_doubles = c->max_tab;
+  P.close_doubles = c->max_close;
   P.lds_limit = lds_limit(c);
   P.ctr = c->ctr.as<Ctr>();
   P.n_ctr = 1;
@@ -990,12 +1011,12 @@ int paid_children_eval(paid_ctx *c, const paid_params *p, const double *l, unsig
   P.ff_identity = identity;
   P.eval_layout = cfg.eval_layout;
   if (eval_lds_bytes(P) == 0)
-    return fail(c, PAID_EINVAL, "frequency-sum table of %d rows does not fit in LDS (T too small against the band)",
-                P.tab_rows);
+    return fail(c, PAID_EINVAL, "frequency-sum table of %d doubles does not fit in LDS (T too small against the band)",
+                P.tab_doubles);
   P.products = leaves_hold_products(P) ? 1 : 0;
   const int MQ = P.MQ = P.products ? kProd : MU;
   if ((rc = stage_pair_coefficients(c, P, hff.data())) != PAID_OK) return rc;
-  DevBuf code, key, Q, si, dv, de, itau, cnt, ctrid, ifl;
+  DevBuf code, key, Q, si, selc, dv, de, itau, cnt, ctrid, ifl;
   HIPCHK(c, code.ensure(sizeof(uint64_t) * cap));
   HIPCHK(c, key.ensure(sizeof(double) * cap));
   HIPCHK(c, Q.ensure(sizeof(double) * cap * MQ));
@@ -1003,11 +1024,14 @@ int paid_children_eval(paid_ctx *c, const paid_params *p, const double *l, unsig
   HIPCHK(c, dv.ensure(sizeof(double) * (size_t)n * MQ));
   HIPCHK(c, de.ensure(sizeof(double) * (size_t)n));
   HIPCHK(c, itau.ensure(sizeof(float) * MU));
-  HIPCHK(c, cnt.ensure(256));
+  HIPCHK(c, cnt.ensure(256 + sizeof(int) * kXcds * kXcdStride));
+  HIPCHK(c, hipMemsetAsync(cnt.p, 0, 256 + sizeof(int) * kXcds * kXcdStride, c->stream));
   HIPCHK(c, ifl.ensure(sizeof(int) * (size_t)n));
   HIPCHK(c, hipMemsetAsync(Q.p, 0, sizeof(double) * cap * MQ, c->stream));
   HIPCHK(c, hipMemsetAsync(key.p, 0, sizeof(double) * cap, c->stream));
+  HIPCHK(c, selc.ensure(sizeof(uint64_t) * (size_t)n));
   HIPCHK(c, hipMemcpyAsync(code.p, pc.data(), sizeof(uint64_t) * n, hipMemcpyHostToDevice, c->stream));
+  HIPCHK(c, hipMemcpyAsync(selc.p, pc.data(), sizeof(uint64_t) * n, hipMemcpyHostToDevice, c->stream));
   // slot state: cid 0, state active, nleaf n, selcnt n, woff {0, n}, flags, depth; sel = 0..n-1
   std::vector<int> hs(8 + (size_t)n, 0);
   hs[0] = 0;      // cid
@@ -1040,10 +1064,14 @@ int paid_children_eval(paid_ctx *c, const paid_params *p, const double *l, unsig
   P.st_depth = s + 5;
   P.woff = s + 6;
   P.sel = s + 8;
+  P.selc = selc.as<uint64_t>();
+  P.sctr = c->ctr.as<Ctr>();  // (slot 0 holds container 0)
+  P.one_row = 1;
   P.itau = itau.as<float>();
   P.dv = dv.as<double>();
   P.de = de.as<double>();
   P.counters = cnt.as<int>() + 4;
+  P.xcount = cnt.as<int>() + 64;
   P.ifill = ifl.as<int>();
   HIPCHK(c, launch_eval(P, n < 4096 ? n : 4096, c->stream));
   std::vector<double> hQ((size_t)cap * MQ), hk(cap);

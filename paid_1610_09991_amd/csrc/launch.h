@@ -19,18 +19,25 @@ struct RuleConst {
   // delta_a = (pi 2^-(d+1)) xi_a for parent depth d and a = 0..4 (the nodes
   // a = 5..8 have the opposite offsets)
   double cdel[kDelDepths][5], sdel[kDelDepths][5];
+  // Taylor coefficients of sin (from degree 17 down to 3) and cos (18 to 2),
+  // read by scalar loads where a wave must not wait behind its stores
+  double sin_c[8], cos_c[9];
 };
 
 // ------------------------------------------------------------------ tables
 struct TabArgs {
-  Entry *entries;    // [n_entries], J/tab_off/nmats/emax filled by the host
+  Entry *entries;    // [n_entries], J/JV/tab_off/nmats/emax filled by the host
   int n_entries;
-  int max_J;
+  int max_rows;      // value and close rows of the largest entry
+  long max_points;   // circle points of the largest entry
   double *tab;       // table buffer
   double *zeta;      // [n_entries][kTabKTail+1] scratch
-  double2 *svals;    // [n_entries][max_J][kTabPts] scratch
+  double2 *svals;    // [n_entries][max_points] scratch
+  // set by launch_tables
+  double econ[kTabDeg - kValDeg][kValDeg + 1];
+  double cosine[kTabPts];  // cos(2 pi m / kTabPts)
 };
-hipError_t launch_tables(const TabArgs &a, hipStream_t s);
+hipError_t launch_tables(TabArgs a, hipStream_t s);
 
 // ------------------------------------------------------------------ setup
 hipError_t launch_container_setup(Ctr *ctr, int n_ctr, const double *q, int n_q, int n_ch,
@@ -39,6 +46,9 @@ hipError_t launch_container_setup(Ctr *ctr, int n_ctr, const double *q, int n_q,
 // ------------------------------------------------------------------ pool and queue
 // SLOT_MOVE: a container in a small slot waiting for a large one
 enum SlotState { SLOT_EMPTY = 0, SLOT_NEW = 1, SLOT_ACTIVE = 2, SLOT_DONE = 3, SLOT_MOVE = 4 };
+
+// chunk counters of the evaluation: one per XCD, each in a cache line of its own
+constexpr int kXcds = 8, kXcdStride = 32;
 
 struct Problem {      // everything the round kernels need, passed by value
   // static description
@@ -70,7 +80,8 @@ struct Problem {      // everything the round kernels need, passed by value
   int *moveq;                 // [W] scratch: the waiting small slots in slot order
   int bmin, bmax;
   int lds_wave_doubles;       // per-wave LDS of the evaluation kernel (set at launch)
-  int tab_rows;               // rows of the largest frequency-sum table (the LDS table)
+  int tab_doubles;            // doubles of the largest parameter row's tables (staged in LDS)
+  int close_doubles;          // and of its close rows alone
   int lds_limit;              // bytes of LDS a workgroup may use on the device
   int sym;                    // 1: half zone p_y >= 0 with the parity factors of the pairs
   // 1: a leaf stands for itself and its mirror image under p -> -p.  Both
@@ -89,6 +100,9 @@ struct Problem {      // everything the round kernels need, passed by value
   float *E;                   // [regions*MU] or NULL
   // slot state
   int *cid, *state, *nleaf, *selcnt, *sel, *woff;  // sel: [W*bmax], woff: [W+1]
+  uint64_t *selc;             // [W*bmax] codes of the selected leaves
+  Ctr *sctr;                  // [W] the slots' containers
+  int one_row;                // 1: one parameter row in the call
   int *flags;                 // [W]: bit0 = converged, bit1 = budget hit
   double *val;                // [W*MQ]
   double *err;                // [W]   (sum of keys)
@@ -103,6 +117,7 @@ struct Problem {      // everything the round kernels need, passed by value
   // queue and global counters
   int *qhead;                 // next container to admit
   int *counters;              // [0] done, [1] not converged, [2] total work items, [3] chunk counter
+  int *xcount;                // [kXcds * kXcdStride] the evaluation's chunk counters
   long long *gstats;          // [0] rounds [1] splits [2] leaves [3] max depth
   // outputs (device)
   double *out, *err_out;      // [n_ctr][M][M]

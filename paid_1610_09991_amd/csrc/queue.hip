@@ -224,6 +224,20 @@ __device__ inline int key_bin(double k, int emax_bits) {
   return b < 0 ? 0 : (b > kBins - 1 ? kBins - 1 : b);
 }
 
+// The deepest level that the splits of a selection reach (d: the deepest leaf
+// this thread has selected, -1: none).  One value per container and round here
+// instead of an atomic per split in the evaluation, where a round's splits of
+// one container queued up on its word (57k cycles a group of eight).
+__device__ inline void note_depth(const Problem &P, int s, int d, int *sh) {
+  for (int o = 32; o >= 1; o >>= 1) d = max(d, __shfl_xor(d, o, 64));
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = d;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < (int)(blockDim.x >> 6); ++w) d = max(d, sh[w]);
+    if (d + 1 > P.st_depth[s]) P.st_depth[s] = d + 1;
+  }
+}
+
 __global__ void __launch_bounds__(kSelThreads) k_select(Problem P) {
   __shared__ double shd[2 * kSelThreads];
   __shared__ int shi[kSelThreads];
@@ -246,15 +260,21 @@ __global__ void __launch_bounds__(kSelThreads) k_select(Problem P) {
     if (kl > n) kl = n;
     const int kmax = (int)kl;
     int *sel = P.sel + (long)s * P.bmax;
-    int out = 0;
+    int out = 0, dmax = -1;
     for (long b0 = 0; b0 < n && out < kmax; b0 += blockDim.x) {
       long i = b0 + t;
       int flag = (i < n) && seed_split(P, s, P.code[base + i]), ex;
       int tot = block_scan(flag, shi, ex);
-      if (flag && out + ex < kmax) sel[out + ex] = (int)i;
+      if (flag && out + ex < kmax) {
+        sel[out + ex] = (int)i;
+        const uint64_t code = P.code[base + i];
+        P.selc[(long)s * P.bmax + out + ex] = code;
+        dmax = max(dmax, code_depth(code));
+      }
       out += tot;
     }
     if (out > 0) {
+      note_depth(P, s, dmax, shi);
       if (t == 0) P.selcnt[s] = out < kmax ? out : kmax;
       return;
     }
@@ -333,9 +353,12 @@ __global__ void __launch_bounds__(kSelThreads) k_select(Problem P) {
           bi = shi[kSelThreads / 64 + w2];
         }
       }
-      const int deep = code_depth(P.code[base + bi]) >= kMaxDepth;
+      const uint64_t code = P.code[base + bi];
+      const int deep = code_depth(code) >= kMaxDepth;
       P.sel[(long)s * P.bmax] = (int)bi;
+      P.selc[(long)s * P.bmax] = code;
       P.selcnt[s] = deep ? 0 : 1;
+      if (!deep && code_depth(code) + 1 > P.st_depth[s]) P.st_depth[s] = code_depth(code) + 1;
       if (deep) {
         P.flags[s] |= 2;
         P.state[s] = SLOT_DONE;
@@ -526,10 +549,14 @@ __global__ void __launch_bounds__(kSelThreads) k_select(Problem P) {
   // the container stops with the budget flag, as on an exhausted pool
   const int ksel = out < s_k ? out : s_k;
   __syncthreads();  // sel is complete
-  int deep = 0;
-  for (int j = t; j < ksel; j += blockDim.x)
-    deep |= code_depth(P.code[base + sel[j]]) >= kMaxDepth ? 1 : 0;
-  deep = __syncthreads_or(deep);
+  int dmax = -1;
+  for (int j = t; j < ksel; j += blockDim.x) {
+    const uint64_t code = P.code[base + sel[j]];
+    P.selc[(long)s * P.bmax + j] = code;
+    dmax = max(dmax, code_depth(code));
+  }
+  const int deep = __syncthreads_or(dmax >= kMaxDepth);
+  if (!deep) note_depth(P, s, dmax, shi);
   if (t == 0) {
     if (deep) {
       P.selcnt[s] = 0;
@@ -554,8 +581,9 @@ __global__ void k_worklist(Problem P) {
   if (t == 0) {
     P.woff[P.W] = carry;
     P.counters[2] = carry;
-    P.counters[3] = 0;  // the evaluation's chunk counter
+    P.counters[3] = 0;  // the evaluation's chunk counters
   }
+  if (t < kXcds) P.xcount[t * kXcdStride] = 0;
 }
 
 // Container admission: empty slots take the next containers of the queue in
@@ -806,6 +834,7 @@ __global__ void k_move_finish(Problem P) {
     for (int k = t; k < kPyr; k += blockDim.x) P.pyr[(long)b * kPyr + k] = P.pyr[(long)src * kPyr + k];
   if (t == 0) {
     P.cid[b] = P.cid[src];
+    P.sctr[b] = P.sctr[src];
     P.nleaf[b] = P.nleaf[src];
     P.flags[b] = P.flags[src];
     P.st_depth[b] = P.st_depth[src];

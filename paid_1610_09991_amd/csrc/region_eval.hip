@@ -123,33 +123,28 @@ __device__ inline double half_zone_factor(int m, int n) {
 
 // sin and cos of |x| <= pi (+ rounding): reduction by pi/2 in two parts
 // (Cody-Waite; q*pi/2 is exact for |q| <= 2) to |r| <= pi/4, then the Taylor
-// series of sin and cos to degree 17/18 (truncation below 1e-19 there).
+// series of sin and cos to degree 17/18 (truncation below 1e-19 there).  The
+// coefficients come by scalar loads through a pointer that the compiler cannot
+// follow: as literals in a loop they are hoisted out of it into registers that
+// the loop has not got, and reloaded from scratch memory.
 __device__ inline void sincos_zone(double x, double *s, double *c) {
+  typedef const __attribute__((address_space(4))) RuleConst CR;
+  CR *cr = (CR *)&c_rule;
+#ifdef __HIP_DEVICE_COMPILE__
+  asm volatile("" : "+s"(cr));
+#endif
   const double pio2_hi = 1.5707963267948966, pio2_lo = 6.123233995736766e-17;
   const double q = rint(x * 0.63661977236758134);
   const double r = (x - q * pio2_hi) - q * pio2_lo, r2 = r * r;
-  double ps = 1.0 / 355687428096000.0;  // 1/17!
-  ps = fma(ps, r2, -1.0 / 1307674368000.0);
-  ps = fma(ps, r2, 1.0 / 6227020800.0);
-  ps = fma(ps, r2, -1.0 / 39916800.0);
-  ps = fma(ps, r2, 1.0 / 362880.0);
-  ps = fma(ps, r2, -1.0 / 5040.0);
-  ps = fma(ps, r2, 1.0 / 120.0);
-  ps = fma(ps, r2, -1.0 / 6.0);
-  const double sr = fma(ps * r2, r, r);
-  double pc = 1.0 / 6402373705728000.0;  // 1/18!
-  pc = fma(pc, r2, -1.0 / 20922789888000.0);
-  pc = fma(pc, r2, 1.0 / 87178291200.0);
-  pc = fma(pc, r2, -1.0 / 479001600.0);
-  pc = fma(pc, r2, 1.0 / 3628800.0);
-  pc = fma(pc, r2, -1.0 / 40320.0);
-  pc = fma(pc, r2, 1.0 / 720.0);
-  pc = fma(pc, r2, -1.0 / 24.0);
-  pc = fma(pc, r2, 0.5);
-  const double cr = fma(-pc, r2, 1.0);
+  double ps = cr->sin_c[0], pc = cr->cos_c[0];
+#pragma unroll
+  for (int i = 1; i < 8; ++i) ps = fma(ps, r2, cr->sin_c[i]);
+#pragma unroll
+  for (int i = 1; i < 9; ++i) pc = fma(pc, r2, cr->cos_c[i]);
+  const double sr = fma(ps * r2, r, r), cr1 = fma(-pc, r2, 1.0);
   const int k = ((int)q) & 3;
-  *s = (k == 0) ? sr : (k == 1) ? cr : (k == 2) ? -sr : -cr;
-  *c = (k == 0) ? cr : (k == 1) ? -sr : (k == 2) ? -cr : sr;
+  *s = (k == 0) ? sr : (k == 1) ? cr1 : (k == 2) ? -sr : -cr1;
+  *c = (k == 0) ? cr1 : (k == 1) ? -sr : (k == 2) ? -cr1 : sr;
 }
 
 // Coordinates of one axis: nco = 17 (four children of a rectangle of width
@@ -161,7 +156,7 @@ __device__ inline double axis_coord(int j, int nco, double x0, double wdt) {
 }
 
 // Per-axis data and the integrand on the nco x nco node grid.  `tab` is the
-// parameter row's frequency-sum table (LDS or global memory).
+// parameter row's close rows (LDS or global memory).
 template <int L>
 __device__ void fill_nodes(WaveLds<L> &S, const Problem &P, const Ctr &C, const Entry &E,
                            const double *tab, int nco, double x0, double y0, double wdt) {
@@ -203,7 +198,7 @@ __device__ void fill_nodes(WaveLds<L> &S, const Problem &P, const Ctr &C, const 
       double px = S.cp[0][ix], py = S.cp[1][iy], mx = S.cm[0][ix], my = S.cm[1][iy];
       double a = -2.0 * E.t * (px + py) - 4.0 * E.tp * px * py - E.mu;
       double b = -2.0 * E.t * (mx + my) - 4.0 * E.tp * mx * my - E.mu;
-      g = K_eval(E, tab, C.ch, a, b);
+      g = K_taylor(E, tab, C.ch, a, b);
     } else if (P.kind == 2) {
       g = 1.0;
     } else {
@@ -705,6 +700,7 @@ __global__ void __launch_bounds__(64) k_root(Problem P) {
   if (s >= P.W || P.state[s] != SLOT_NEW) return;
   build_pidmap<L>(pidmap, podd, threadIdx.x, 64);
   const int c = P.cid[s];
+  if (threadIdx.x == 0) P.sctr[s] = P.ctr[c];
   // key weights: the pair weights in the weighted mode, else one (the
   // per-integral mode refreshes them with 1/tau every round)
   for (int pid = threadIdx.x; pid < P.MU; pid += 64) {
@@ -739,7 +735,7 @@ __global__ void __launch_bounds__(64) k_root(Problem P) {
   } else {
     const Ctr C = P.ctr[c];
     const Entry E = P.entries[C.entry];
-    const double *tab = P.tab + E.tab_off;
+    const double *tab = P.tab + E.tab_off + (long)E.JV * kValStride;  // close rows
     const double wr = half ? kPi : kTwoPi;
     if (half) {  // the sums below add up the quadrants
       for (int i = threadIdx.x; i < P.MQ; i += 64) P.val[(long)s * P.MQ + i] = 0.0;
@@ -808,7 +804,7 @@ __device__ inline int item_slot(const Problem &P, int w) {
 template <int L, int GRAM>
 __device__ void do_item(WaveLds<L> &S, const Problem &P, const int *pidmap, const int *podd, int s, int r,
                         const double *tab) {
-  const Ctr C = P.ctr[P.cid[s]];
+  const Ctr C = P.sctr[s];
   const Entry E = P.entries[C.entry];
   // the pool and the deltas hold P.MU form-factor pairs (<= the box pairs)
   constexpr int KMAX = (Dims<L>::MU + 63) / 64;
@@ -916,12 +912,11 @@ __device__ void do_item(WaveLds<L> &S, const Problem &P, const int *pidmap, cons
   if (lane == 0) {
     P.de[it] = dkey;
     if (P.ifill) P.ifill[it] = skip != 15;
-    if (d + 1 > P.st_depth[s]) atomicMax(&P.st_depth[s], d + 1);
   }
 }
 
 // parameter row of slot s
-__device__ inline int slot_entry(const Problem &P, int s) { return P.ctr[P.cid[s]].entry; }
+__device__ inline int slot_entry(const Problem &P, int s) { return P.sctr[s].entry; }
 
 // The problem description of a kernel whose only argument is a Problem, read
 // through a pointer into the kernel-argument segment that the compiler cannot
@@ -1009,7 +1004,7 @@ __global__ void __launch_bounds__(256) k_children(Problem P) {
   // the wave index is uniform in a wave: keep it (and all per-item
   // bookkeeping derived from it) in scalar registers
   const int nw = blockDim.x >> 6, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  WaveLds<L> &S = *reinterpret_cast<WaveLds<L> *>(lds_raw + (size_t)P.tab_rows * kTabStride +
+  WaveLds<L> &S = *reinterpret_cast<WaveLds<L> *>(lds_raw + (size_t)P.close_doubles +
                                                   (size_t)wv * P.lds_wave_doubles);
   __shared__ int next[2];
   Chunk k = first_chunk(P, 1);
@@ -1032,8 +1027,9 @@ __global__ void __launch_bounds__(256) k_children(Problem P) {
     if (e != loaded) {
       __syncthreads();  // every wave is done with the previous table
       const Entry E0 = P.entries[e];
-      const double *src = P.tab + E0.tab_off;
-      for (int i = threadIdx.x; i < E0.J * kTabStride; i += blockDim.x) tabl[i] = src[i];
+      const double *src = P.tab + E0.tab_off + (long)E0.JV * kValStride;
+      const int nt = close_doubles(E0);
+      for (int i = threadIdx.x; i < nt; i += blockDim.x) tabl[i] = src[i];
       __syncthreads();
       loaded = e;
     }
@@ -1080,11 +1076,15 @@ __global__ void __launch_bounds__(256) k_children(Problem P) {
 namespace lpc {
 
 constexpr int kItems = 8;              // work items per wave
-constexpr int kYRow = 6;               // doubles per node row: C, D, phi_1..phi_4
-// the 9 node rows of one child row, padded to an odd number of doubles so
-// that the blocks the lanes of a wave read at one time fall on distinct banks
-constexpr int kYBlock = kNF * kYRow + 1;
-constexpr int kYDoubles = kItems * 2 * kYBlock;  // per-wave LDS: rows of both child rows
+constexpr int kYRow = 2;               // doubles per node row: cos y, sin y
+// the 9 node rows of one child row: 144 bytes, so that the 16-byte rows that
+// the 16 child rows of a wave read at one time cover all 64 banks once
+constexpr int kYBlock = kNF * kYRow;
+constexpr int kYRows = kItems * 2 * kYBlock;  // per-wave LDS: rows of both child rows,
+// then what a column starts from, per child: cos and sin of its centre in x and
+// of l/2 (odd stride; read anew for each column rather than held in 12 registers)
+constexpr int kCol = 7;
+constexpr int kYDoubles = kYRows + 4 * kItems * kCol;
 // records are staged in LDS, kStage values of each of the wave's 32 children at
 // a time (an odd stride: the children's lanes write to distinct banks)
 constexpr int kChildren = 4 * kItems;
@@ -1100,7 +1100,7 @@ __host__ __device__ constexpr int area_doubles(bool with_e, bool general) {
 __host__ __device__ constexpr int wave_doubles(bool with_e, bool with_w, bool general) {
   return area_doubles(with_e, general) + kChildren + kItems + (with_w ? kItems * kPairs9 / 2 : 0);
 }
-static_assert(kChildren * kPairs9 / 2 <= kYDoubles, "the box basis' errors fit in the area");
+static_assert(kChildren * kPairs9 / 2 <= kChildren * kStage, "the box basis' errors fit in the area");
 
 // sum of v over the four children of the item, the same in all lanes of the
 // item with the same h: ((c0 + c1) + (c2 + c3)) with a + b = b + a exactly
@@ -1114,33 +1114,193 @@ __device__ inline double swap_h(double v) { return dpp_move<0xB1>(v); }  // part
 
 }  // namespace lpc
 
-// Sine and cosine of one coordinate, out of line: the constants of the
-// series then live only while it runs instead of occupying registers across
-// the caller's loops.
-__device__ __noinline__ double2 sincos_out_of_line(double x) {
-  double sn, cs;
-  sincos_zone(x, &sn, &cs);
-  return make_double2(sn, cs);
+// What a group needs of its lane's item (items past the group's end repeat the
+// last one and store nothing).
+struct LpcItem {
+  int s, r;       // slot, place in its selection
+  uint64_t pc;    // parent's code
+  int ch;         // channel
+  double cLx, sLx, cLy, sLy;
+};
+
+// The slot holding item g (woff[s] <= g < woff[s + 1]; woff is non-decreasing),
+// the same in every lane: each step splits the range in 64 by one load per
+// lane, two or three dependent loads instead of the eleven of a binary search
+// over a thousand slots (each one the latency of L2 or beyond).
+__device__ inline int wave_slot(const Problem &P, int g) {
+  const int lane = lane_id();
+  int lo = 0, hi = P.W;
+  while (hi - lo > 1) {
+    const int step = (hi - lo + 63) >> 6, i = lo + (lane + 1) * step;
+    const int c = __popcll(__ballot(i < hi && P.woff[i] <= g));
+    lo += c * step;
+    hi = min(lo + step, hi);
+  }
+  return lo;
 }
 
-// Slot, item and parent of lane group `it` of a wave whose first item is g0
-// in slot s0 (items g0 + it >= gend repeat the last item and store nothing).
-struct LpcItem {
-  int s, r;
-  long leaf, pbase;
-  uint64_t pc;
-};
-__device__ inline LpcItem lpc_item(const Problem &P, int w, int s0) {
+// The items of a group, one per eight lanes: w is the lane's item, g0 the first
+// of the group.  The slots of the eight items follow from one load of the next
+// 64 offsets.
+__device__ inline LpcItem lpc_item(const Problem &P, int g0, int w) {
+  const int lane = lane_id();
+  int s = wave_slot(P, g0);
+  const int next = min(s + 1 + lane, P.W);
+  const int off = P.woff[next];
+  int mine = 0;
+#pragma unroll
+  for (int i = 0; i < lpc::kItems; ++i) {  // offsets at or below each lane group's item
+    const int c = __popcll(__ballot(off <= __shfl(w, 8 * i, 64)));
+    if (i == lane >> 3) mine = c;
+  }
+  // (every lane takes part in the exchange: an idle lane's value reads as zero)
+  const int first = P.woff[s], prev = __shfl(off, max(mine - 1, 0), 64);
+  int lo = mine ? prev : first;
+  s += mine;
+  while (mine == 64 && P.woff[s + 1] <= w) lo = P.woff[++s];  // (more than 63 empty slots between two items)
   LpcItem q;
-  int s = s0;
-  while (P.woff[s + 1] <= w) ++s;
   q.s = s;
-  q.r = w - P.woff[s];
-  q.leaf = P.sel[(long)s * P.bmax + q.r];
-  q.pbase = slot_base(P, s) + q.leaf;
-  q.pc = P.code[q.pbase];
+  q.r = w - lo;
+  q.pc = P.selc[(long)s * P.bmax + q.r];
+  const Ctr C = P.sctr[s];
+  q.ch = C.ch;
+  q.cLx = C.cLx;
+  q.sLx = C.sLx;
+  q.cLy = C.cLy;
+  q.sLy = C.sLy;
   return q;
 }
+
+// End of the run of items from slot s on that belong to one parameter row e,
+// at most i1, the same in every lane (slots without items are passed over)
+__device__ inline int row_end(const Problem &P, int s, int e, int i1) {
+  if (P.one_row) return i1;
+  const int lane = lane_id();
+  for (int t0 = s + 1; t0 < P.W; t0 += 64) {
+    const int t = t0 + lane;
+    const int lo = t < P.W ? P.woff[t] : i1, up = t < P.W ? P.woff[t + 1] : i1;
+    const bool other = lo < i1 && up > lo && P.sctr[t].entry != e;
+    const unsigned long long m = __ballot(other), past = __ballot(lo >= i1);
+    if (m) return __shfl(lo, __ffsll((long long)m) - 1, 64);
+    if (past) break;
+  }
+  return i1;
+}
+
+// How the items are shared out: an eighth of the round's items per XCD (the
+// workgroups b = x mod 8, which the hardware places on XCD x), each workgroup of
+// an XCD a first chunk by its index and then chunks from the XCD's own counter
+// (one counter for all is a queue of thousands of atomics on one address: 50k
+// cycles a wait); within a workgroup the waves take groups of eight items from
+// its range, a run of one parameter row.  A wave that finds the range empty
+// takes the next one for all (the lock), while the others finish their groups:
+// no barrier until another row's table is needed or the items are gone.  (With
+// a barrier at every chunk the waves of one flow scale's rounds spent 37% of
+// their time waiting, 60% in the per-integral mode.)
+struct LpcShare {
+  unsigned long long range;  // end << 32 | next item
+  int lock;
+  int mode;                  // 0: run, 1: another row's table, 2: no items left
+  int row, lo, hi;           // the next range and its row (mode 1)
+  int rest, end;             // what is left of the chunk behind the range
+  int base, total;           // the XCD's items behind the first chunks
+};
+
+// chunk sizes: half of an even share of the XCD's items left, in whole groups
+__device__ inline int share_items(int left) {
+  const int half = left / (2 * (((int)gridDim.x + kXcds - 1) / kXcds));  // (its workgroups, or one more)
+  return max(lpc::kItems, half / lpc::kItems * lpc::kItems);
+}
+
+// the next range of this workgroup (one wave): of the present chunk, or of a
+// new one from the counter
+__device__ inline void next_range(const Problem &P, LpcShare &sh, int loaded) {
+  const int lane = lane_id();
+  int i0 = sh.rest, i1 = sh.end;
+  if (i0 >= i1) {
+    if (lane == 0 && sh.base < sh.total) {
+      int *count = P.xcount + (blockIdx.x % min(kXcds, (int)gridDim.x)) * kXcdStride;
+      const int seen = sh.base + __hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (seen < sh.total) {
+        const int c = share_items(sh.total - seen);
+        i0 = min(sh.base + atomicAdd(count, c), sh.total);
+        i1 = min(i0 + c, sh.total);
+      }
+    }
+    i0 = __builtin_amdgcn_readfirstlane(i0);
+    i1 = __builtin_amdgcn_readfirstlane(i1);
+  }
+  if (i0 >= i1) {
+    if (lane == 0) sh.mode = 2;
+    return;
+  }
+  const int s = wave_slot(P, i0), e = __builtin_amdgcn_readfirstlane(P.sctr[s].entry);
+  const int hi = row_end(P, s, e, i1);
+  if (lane == 0) {
+    sh.rest = hi;
+    sh.end = i1;
+    if (e == loaded) {
+      atomicExch(&sh.range, ((unsigned long long)hi << 32) | (unsigned)i0);
+    } else {
+      sh.row = e;
+      sh.lo = i0;
+      sh.hi = hi;
+      sh.mode = 1;
+    }
+  }
+}
+
+// a group of items for this wave: its first item (end: the range's end), or -1
+// when the workgroup needs another table or has no items left
+__device__ inline int take_group(const Problem &P, LpcShare &sh, int loaded, int &end) {
+  const int lane = lane_id();
+  for (;;) {
+    unsigned long long r = 0;
+    int mode = 0;
+    if (lane == 0) {
+      r = __hip_atomic_load(&sh.range, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      if ((unsigned)r < (unsigned)(r >> 32)) r = atomicAdd(&sh.range, (unsigned long long)lpc::kItems);
+      mode = __hip_atomic_load(&sh.mode, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    const int g = __builtin_amdgcn_readfirstlane((int)(unsigned)r);
+    end = __builtin_amdgcn_readfirstlane((int)(r >> 32));
+    if (g < end) return g;
+    if (__builtin_amdgcn_readfirstlane(mode)) return -1;
+    int mine = 0;
+    if (lane == 0) mine = atomicCAS(&sh.lock, 0, 1) == 0;
+    if (__builtin_amdgcn_readfirstlane(mine)) {
+      // (another wave may have taken a range since)
+      int empty = 0;
+      if (lane == 0) {
+        const unsigned long long q = __hip_atomic_load(&sh.range, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        empty = (unsigned)q >= (unsigned)(q >> 32) &&
+                __hip_atomic_load(&sh.mode, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == 0;
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+      if (__builtin_amdgcn_readfirstlane(empty)) next_range(P, sh, loaded);
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+      if (lane == 0) atomicExch(&sh.lock, 0);
+    } else {
+      __builtin_amdgcn_s_sleep(4);  // (the holder is a running wave and ends its turn)
+    }
+  }
+}
+
+// the rule in LDS: node offsets (cos, sin) of every depth, then the fine and the
+// coarse weights of the nine nodes
+constexpr int kDelWeights = kDelDepths * 10, kDelDoubles = kDelWeights + 2 * kNF;
+
+__device__ inline double rule_value(int i) {
+  if (i < kDelWeights) return i % 10 < 5 ? c_rule.cdel[i / 10][i % 10] : c_rule.sdel[i / 10][i % 10 - 5];
+  i -= kDelWeights;
+  return i < kNF ? c_rule.w2[i] : ((i - kNF) & 1) ? 0.0 : c_rule.w1[(i - kNF) >> 1];
+}
+
+// a parameter row's constants, in scalar registers (energies in units of w = pi T)
+struct LpcRow {
+  double mt2, mtp4, mmu;
+  int J, JV;
+};
 
 // a value that is the same in every lane, held in scalar registers
 __device__ inline double wave_uniform(double v) {
@@ -1150,55 +1310,61 @@ __device__ inline double wave_uniform(double v) {
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
-// One group of up to 8 work items of one parameter row (row entry erow,
-// table tab in LDS, the wave's LDS at Yw), first item g0 in slot s0; items
-// g0 + it >= gend are inactive (their lanes repeat the last item and store
-// nothing).  BUB: the bubble integrands (kinds 0 and 1); otherwise the unit
-// integrand.  WE: per-pair errors are stored (FP32 records and deltas);
-// otherwise the children's errors only form their keys.  WW: the keys weigh
-// the pairs (per-integral and weighted modes); otherwise they are plain sums.
-// GEN: general form factors (pairs from P.pcoef); otherwise the box basis
-// itself, whose leaves hold the product integrals.
+// row of element e of a staged block [rows][n]: e / n (a constant for the box
+// basis; e < 800 and n <= 25 otherwise, where the rounded product is exact)
+template <bool GEN>
+__device__ inline int stage_row(int e, int n, float inv_n) {
+  return GEN ? (int)(((float)e + 0.5f) * inv_n) : e / kProd;
+}
+
+// One group of up to 8 work items of one parameter row (row R, its tables tab,
+// the node offsets del and the pairs' coefficients co in LDS, the wave's LDS at
+// Yw), first item g0; items g0 + it >= gend are inactive (their lanes repeat the
+// last item and store nothing).  cur: the lane's item; on return g0, gend and
+// cur are those of the wave's next group (take), g0 = -1 if there is none.  The
+// next group's items, and the parents' values, are read before this group's records are stored: loads and stores of a wave complete
+// in order, so a load behind the stores would wait until they have reached L2.
+// Between its stores and the end of the next node loop a wave reads LDS only.
+// BUB: the bubble integrands (kinds 0 and 1); otherwise the unit integrand.
+// WE: per-pair errors are stored (FP32 records and deltas); otherwise the
+// children's errors only form their keys.  WW: the keys weigh the pairs
+// (per-integral and weighted modes); otherwise they are plain sums.  GEN:
+// general form factors (pairs from P.pcoef); otherwise the box basis itself,
+// whose leaves hold the product integrals.
 template <bool BUB, bool WE, bool WW, bool GEN>
-__device__ void lpc_group(const Problem &P, int erow, const double *tab, double *Yw, int g0,
-                          int gend, int s0) {
+__device__ void lpc_group(const Problem &P, const LpcRow &R, const double *tab, const double *del,
+                          const double *co, double *Yw, LpcShare &share, int loaded, int &g0, int &gend,
+                          LpcItem &cur) {
   using namespace lpc;
-  // the parameter row's constants in scalar registers (read for each group
-  // rather than held in vector registers across the kernel's loops)
-  const Entry &Erow = P.entries[erow];
   Entry E;
-  E.t = wave_uniform(Erow.t);
-  E.tp = wave_uniform(Erow.tp);
-  E.mu = wave_uniform(Erow.mu);
-  E.w = wave_uniform(Erow.w);
-  E.inv_w = wave_uniform(Erow.inv_w);
-  E.J = __builtin_amdgcn_readfirstlane(Erow.J);
+  E.J = R.J;
+  E.JV = R.JV;
+  const double mt2 = R.mt2, mtp4 = R.mtp4, mmu = R.mmu;
   // the lane's place, formed anew for every group rather than held in
   // registers across the kernel's loops
   int lane = lane_id();
   asm volatile("" : "+v"(lane));
   const int it = lane >> 3, ch = (lane >> 1) & 3, h = lane & 1;
   const int cx = ch & 1, cy = ch >> 1;
-  const int w = min(g0 + it, gend - 1);
   const int MU = P.MU;
 
   // ---- the items: placeholders, node rows
-  int d, chl;
-  double cxm = 0.0, sxm = 0.0, cLx, sLx;
+  const int d = code_depth(cur.pc), chl = cur.ch;
+  double *col = Yw + kYRows + (lane >> 1) * kCol;
+  // slot, place and code of the items, for the records
+  uint64_t *home = reinterpret_cast<uint64_t *>(Yw + lpc::area_doubles(WE, GEN));
+  if ((lane & 7) == 0) {
+    home[2 * it] = ((uint64_t)(unsigned)cur.s << 32) | (unsigned)cur.r;
+    home[2 * it + 1] = cur.pc;
+  }
   unsigned long long pm;
   bool wave_skip;
   {
-    const LpcItem q = lpc_item(P, w, s0);
-    const Ctr C = P.ctr[P.cid[q.s]];
-    chl = C.ch;
-    cLx = C.cLx;
-    sLx = C.sLx;
-    d = code_depth(q.pc);
-    const uint64_t ix = code_ix(q.pc), iy = code_iy(q.pc);
+    const uint64_t ix = code_ix(cur.pc), iy = code_iy(cur.pc);
     const uint64_t ccode = make_code(d + 1, 2 * ix + cx, 2 * iy + cy);
     // seed phase: children the seed tree splits again are placeholders
     const bool valid = g0 + it < gend;
-    const bool phc = P.seed_y && (P.flags[q.s] & kFlagSeed) && seed_split(P, q.s, ccode);
+    const bool phc = P.seed_y && (P.flags[cur.s] & kFlagSeed) && seed_split(P, cur.s, ccode);
     pm = __ballot(phc && valid);
     wave_skip = pm == __ballot(valid);  // every child of the group is one
     // trigonometric values of the nodes by angle addition: node a of a child
@@ -1209,12 +1375,17 @@ __device__ void lpc_group(const Problem &P, int erow, const double *tab, double 
       const double wdt = kTwoPi * ldexp(1.0, -d);
       const double xm = -kPi + (double)ix * wdt + (0.25 + 0.5 * cx) * wdt;
       const double ym = -kPi + (double)iy * wdt + (0.25 + 0.5 * cy) * wdt;
-      const double2 sc = sincos_out_of_line(h ? ym : xm);
-      const double c1 = sc.y, s1 = sc.x;
-      const double c2 = lpc::swap_h(c1), s2 = lpc::swap_h(s1);
-      cxm = h ? c2 : c1;
-      sxm = h ? s2 : s1;
-      // rows of both child rows of every item: cos(l_y/2 + y), cos(l_y/2 - y), phi_1..4(y)
+      double c1, s1;
+      sincos_zone(h ? ym : xm, &s1, &c1);
+      if (h == 0) {
+        col[0] = c1;
+        col[1] = s1;
+        col[2] = cur.cLx;
+        col[3] = cur.sLx;
+        col[4] = cur.cLy;
+        col[5] = cur.sLy;
+      }
+      // rows of both child rows of every item
 #pragma unroll 1
       for (int t0 = 0; t0 < kItems * 2 * kNF; t0 += 64) {
         // every lane takes part in the exchanges; lanes past the last row idle after them
@@ -1222,20 +1393,14 @@ __device__ void lpc_group(const Problem &P, int erow, const double *tab, double 
         const int rem = t - ti * (2 * kNF), tcy = min(rem / kNF, 1), b = rem - tcy * kNF;
         const int src = 8 * ti + 4 * tcy + 1;  // lane 1 of child (0, tcy) of item ti
         const double cm = __shfl(c1, src, 64), sm = __shfl(s1, src, 64);
-        const double cL = __shfl(C.cLy, src, 64), sL = __shfl(C.sLy, src, 64);
         const int td = __shfl(d, 8 * ti, 64);
         if (t >= kItems * 2 * kNF) continue;
         const int bb = b < 5 ? b : 8 - b;
-        const double cd = c_rule.cdel[td][bb];
-        const double sd = b < 5 ? c_rule.sdel[td][bb] : -c_rule.sdel[td][bb];
-        const double cyv = cm * cd - sm * sd, sy = sm * cd + cm * sd;
+        const double cd = del[td * 10 + bb];
+        const double sd = b < 5 ? del[td * 10 + 5 + bb] : -del[td * 10 + 5 + bb];
         double *row = Yw + (ti * 2 + tcy) * kYBlock + b * kYRow;
-        row[0] = cL * cyv - sL * sy;  // cos(l_y/2 + y)
-        row[1] = cL * cyv + sL * sy;  // cos(l_y/2 - y)
-        row[2] = kSqrt2 * cyv;
-        row[3] = kSqrt2 * sy;
-        row[4] = (cyv - sy) * (cyv + sy);
-        row[5] = 2.0 * sy * cyv;
+        row[0] = cm * cd - sm * sd;  // cos y
+        row[1] = sm * cd + cm * sd;  // sin y
       }
     }
   }
@@ -1243,7 +1408,7 @@ __device__ void lpc_group(const Problem &P, int erow, const double *tab, double 
 
   // ---- the integrand and the sums
   const double *Yc = Yw + (it * 2 + cy) * kYBlock;
-  const double mt2 = -2.0 * E.t, mtp4 = -4.0 * E.tp;
+  const unsigned sgn_ch = chl ? 0u : 0x80000000u;  // pp takes -b
   double I[5][5];
 #pragma unroll
   for (int j = 0; j < 5; ++j)
@@ -1253,37 +1418,82 @@ __device__ void lpc_group(const Problem &P, int erow, const double *tab, double 
   // cos and sin of column a of this lane's child
   auto column_trig = [&](int a, double &cxv, double &sx) {
     const int aa = a < 5 ? a : 8 - a;
-    const double cd = c_rule.cdel[d][aa], sd = a < 5 ? c_rule.sdel[d][aa] : -c_rule.sdel[d][aa];
+    const double cd = del[d * 10 + aa], sd = a < 5 ? del[d * 10 + 5 + aa] : -del[d * 10 + 5 + aa];
+    const double cxm = col[0], sxm = col[1];
     cxv = cxm * cd - sxm * sd;
     sx = sxm * cd + cxm * sd;
   };
-  // the integrand along rows [b0, b1) of column a: y-sums with the fine (H2)
-  // and the coarse (H1) weights
-  auto column = [&](int a, int b0, int b1, double (&H2)[5], double (&H1)[5]) {
+  // y-sums of column a over N nodes, of {1, c, s, c^2, c s} (c, s the node's
+  // cosine and sine in y; the sums of phi follow from them, linearly, at the
+  // end) with the fine (H2) and the coarse (H1) weights: rows i = 0..8 (N = 9),
+  // or the lane's part of a column that both lanes share, rows 0..4 (h = 0) or
+  // 8..5 (h = 1; the weights are symmetric) (N = 5).  The loop over the nodes
+  // is unrolled: weights, row offsets and the rows without a coarse weight are
+  // then known, and the loads of a node (both table rows and the next node's
+  // cosine and sine) are issued together and waited for once; left to itself
+  // the compiler loads a coefficient pair, waits, uses it and loads the next,
+  // ten LDS round trips in a row per node.  What bounds the loop is LDS
+  // bandwidth (160 bytes a node and lane at 128 bytes a clock, plus the bank
+  // conflicts of the table rows), so a node's energies are formed from c and s
+  // by two FMAs each instead of being read as cosines with phi_1..4 (48
+  // bytes).  Close pairs are marked and summed after the loop.
+  auto column = [&](int a, auto count, double (&H2)[5], double (&H1)[5]) {
+    constexpr int N = decltype(count)::value;
     double cxv, sx;
     column_trig(a, cxv, sx);
+    const double cLx = col[2], sLx = col[3], cLy = col[4], sLy = col[5];
     const double Cx = cLx * cxv - sLx * sx, Dx = cLx * cxv + sLx * sx;
-    // the energies along the column are affine in the row's cosine:
+    // the energies along the column are affine in the row's cosine
+    // cos(l_y/2 +- y) = cLy c -+ sLy s:
     // -2t (Cx + py) - 4t' Cx py - mu = (-2t Cx - mu) + py (-2t - 4t' Cx)
-    const double Aa = fma(mt2, Cx, -E.mu), Ba = fma(mtp4, Cx, mt2);
-    const double Ab = fma(mt2, Dx, -E.mu), Bb = fma(mtp4, Dx, mt2);
+    const double Aa = fma(mt2, Cx, mmu), Ba = fma(mtp4, Cx, mt2);
+    const double Ab = fma(mt2, Dx, mmu), Bb = fma(mtp4, Dx, mt2);
+    const double Pa = Ba * cLy, Qa = -Ba * sLy, Pb = Bb * cLy, Qb = Bb * sLy;
+    const double *first = (N < kNF && h) ? Yc + 8 * kYRow : Yc;
+    const int rstep = (N < kNF && h) ? -kYRow : kYRow;
+    auto add = [](double (&H)[5], double g, double c, double s) {
+      const double gc = g * c;
+      H[0] += g;
+      H[1] += gc;
+      H[2] = fma(g, s, H[2]);
+      H[3] = fma(gc, c, H[3]);
+      H[4] = fma(gc, s, H[4]);
+    };
 #pragma unroll
     for (int k = 0; k < 5; ++k) {
       H2[k] = 0.0;
       H1[k] = 0.0;
     }
-#pragma unroll 1
-    for (int b = b0; b < b1; ++b) {
-      const double *row = Yc + b * kYRow;
-      double g = 1.0;  // PAID_UNIT
-      if constexpr (BUB) g = K_eval(E, tab, chl, fma(row[0], Ba, Aa), fma(row[1], Bb, Ab));
-      const double g2 = c_rule.w2[b] * g, g1 = ((b & 1) ? 0.0 : c_rule.w1[b >> 1]) * g;
-      H2[0] += g2;
-      H1[0] += g1;
+    unsigned close = 0;
+    double cn = first[0], sn = first[1];
 #pragma unroll
-      for (int k = 1; k < 5; ++k) {
-        H2[k] = fma(g2, row[1 + k], H2[k]);
-        H1[k] = fma(g1, row[1 + k], H1[k]);
+    for (int i = 0; i < N; ++i) {
+      const double c = cn, s = sn;
+      double g = 1.0;  // PAID_UNIT
+      if (i + 1 < N) {
+        cn = first[(i + 1) * rstep];
+        sn = first[(i + 1) * rstep + 1];
+      }
+      if constexpr (BUB) {
+        const double ea = fma(c, Pa, fma(s, Qa, Aa)), eb = fma(c, Pb, fma(s, Qb, Ab));
+        const PairNode n = pair_node(E, tab, sgn_ch, ea, eb, cn, sn);
+        const bool cl = n.close;
+        close |= cl ? 1u << i : 0u;
+        g = cl ? 0.0 : n.s;
+      }
+      if (N < kNF && i == N - 1) g = h ? 0.0 : g;  // the middle row is lane 0's
+      add(H2, c_rule.w2[i] * g, c, s);
+      if (!(i & 1)) add(H1, c_rule.w1[i >> 1] * g, c, s);
+    }
+    if constexpr (BUB) {
+      if (N < kNF && h) close &= (1u << (N - 1)) - 1u;
+      while (close) {
+        const int i = __ffs(close) - 1;
+        close &= close - 1;
+        const double c = first[i * rstep], s = first[i * rstep + 1];
+        const double g = pair_close(E, tab, sgn_ch, fma(c, Pa, fma(s, Qa, Aa)), fma(c, Pb, fma(s, Qb, Ab)));
+        add(H2, del[kDelWeights + i] * g, c, s);
+        add(H1, del[kDelWeights + kNF + i] * g, c, s);
       }
     }
   };
@@ -1309,9 +1519,10 @@ __device__ void lpc_group(const Problem &P, int erow, const double *tab, double 
   };
   // one step: this lane's column a and the partner's; each lane forms the
   // y-sum vector the partner needs from its own column and swaps it
-  auto step = [&](int a, int b0, int b1, double wf, double wc, bool split) {
+  auto step = [&](int a, auto count, double wf, double wc) {
+    constexpr bool split = decltype(count)::value < kNF;
     double H2[5], H1[5];
-    column(a, b0, b1, H2, H1);
+    column(a, count, H2, H1);
     if (split) {  // both lanes hold part of the same column: add the parts
 #pragma unroll
       for (int k = 0; k < 5; ++k) {
@@ -1342,9 +1553,18 @@ __device__ void lpc_group(const Problem &P, int erow, const double *tab, double 
     // symmetric, so both columns of a step carry the same weights
 #pragma unroll 1
     for (int st = 0; st < 4; ++st)
-      step(h ? 8 - st : st, 0, kNF, c_rule.w2[st], (st & 1) ? 0.0 : c_rule.w1[st >> 1], false);
-    // column 4: rows 0-4 on lane 0, rows 5-8 on lane 1
-    step(4, h ? 5 : 0, h ? kNF : 5, c_rule.w2[4], c_rule.w1[2], true);
+      step(h ? 8 - st : st, std::integral_constant<int, kNF>{}, c_rule.w2[st],
+           (st & 1) ? 0.0 : c_rule.w1[st >> 1]);
+    // column 4: rows 0-4 on lane 0, rows 8-5 on lane 1
+    step(4, std::integral_constant<int, 5>{}, c_rule.w2[4], c_rule.w1[2]);
+    // from {1, c, s, c^2, c s} to phi in y
+#pragma unroll
+    for (int j = 0; j < 5; ++j) {
+      I[j][1] *= kSqrt2;
+      I[j][2] *= kSqrt2;
+      I[j][3] = fma(2.0, I[j][3], -I[j][0]);
+      I[j][4] *= 2.0;
+    }
   }
   // the item's bookkeeping is read again below rather than held in
   // registers across the loops above
@@ -1356,17 +1576,28 @@ __device__ void lpc_group(const Problem &P, int erow, const double *tab, double 
   // items' deltas (children minus parent) are sums over the staged values.
   // Stored straight from the lanes, each value is a write of its own in L2 (32
   // lanes, 32 records): 236 requests a parent kept L2 busy 95% of the time.
-  const LpcItem q = lpc_item(P, w, s0);
   const bool valid = g0 + it < gend;
-  const int dd = code_depth(q.pc);
-  const uint64_t ix = code_ix(q.pc), iy = code_iy(q.pc);
+  const uint64_t place = home[2 * it], pc = home[2 * it + 1];
+  const int item_s = (int)(place >> 32), item_r = (int)(unsigned)place;
+  const long sbase = slot_base(P, item_s);
+  const long itm = (long)item_s * P.bmax + item_r;
+  const long leaf = P.sel[itm];
+  const long nold = P.nleaf[item_s];
+  const double pkey = P.key[sbase + leaf];
+  // the next group's items (cleared otherwise: the old ones are not kept
+  // through the node loop)
+  cur = LpcItem{};
+  g0 = take_group(P, share, loaded, gend);
+  if (g0 >= 0) cur = lpc_item(P, g0, min(g0 + it, gend - 1));
+  const int dd = code_depth(pc);
+  const uint64_t ix = code_ix(pc), iy = code_iy(pc);
   const uint64_t ccode = make_code(dd + 1, 2 * ix + cx, 2 * iy + cy);
   const bool phc = (pm >> lane) & 1ull;
   const bool item_skip = ((pm >> (8 * it)) & 0xFFull) == 0xFFull;
-  const double pkey = P.key[q.pbase];
   const double wdt = kTwoPi * ldexp(1.0, -dd);
   const double fa = (0.25 * wdt) * (0.25 * wdt) / (4.0 * kPi * kPi);
-  const double fm = P.mirror ? 2.0 * fa : fa;  // the child and its mirror image
+  // the child and its mirror image; the node loop summed S[x,y], which is -K for pp
+  const double fk = (BUB && !chl) ? -fa : fa, fm = P.mirror ? 2.0 * fk : fk;
   const double fx = phc ? 0.0 : fm;            // placeholders store zeros
   if (P.mirror && h == 0) {  // odd product integrals cancel between the images
 #pragma unroll
@@ -1375,9 +1606,8 @@ __device__ void lpc_group(const Problem &P, int erow, const double *tab, double 
       for (int k = 0; k < kPhi; ++k)
         if (product_odd(kPhi * j + k)) I[j][k] = 0.0;
   }
-  const long ri = (ch == 0) ? q.leaf : (long)P.nleaf[q.s] + 3L * q.r + (ch - 1);
-  const long base = slot_base(P, q.s) + ri;
-  const long itm = (long)q.s * P.bmax + q.r;
+  const long ri = (ch == 0) ? leaf : nold + 3L * item_r + (ch - 1);
+  const long base = sbase + ri;
   const bool head = valid && ch == 0;
   const int child = lane >> 1;
   const long MQ = P.MQ;
@@ -1385,54 +1615,110 @@ __device__ void lpc_group(const Problem &P, int erow, const double *tab, double 
   long *cbase = reinterpret_cast<long *>(Yw + lpc::area_doubles(WE, GEN));  // [32] region, -1: inactive
   long *ibase = cbase + kChildren;                                          // [8] item of the deltas
   [[maybe_unused]] float *wgt = reinterpret_cast<float *>(ibase + kItems);  // [8][45] key weights
+  wave_sync();  // (cbase takes the place of home)
   if (h == 0) cbase[child] = valid ? base : -1;
   if ((lane & 7) == 0) ibase[it] = valid ? itm : -1;
   if constexpr (WW)
-    for (int k = lane & 7; k < MU; k += 8) wgt[it * kPairs9 + k] = P.itau[(long)q.s * MU + k];
+    for (int k = lane & 7; k < MU; k += 8) wgt[it * kPairs9 + k] = P.itau[(long)item_s * MU + k];
+  wave_sync();
+  // the parents' values of the first kProd columns, for the deltas
+  constexpr int kPar = (kItems * kProd + 63) / 64;
+  const int n1 = GEN ? min(MU, kStage) : kProd;  // (columns staged at a time)
+  const float inv_n1 = 1.0f / (float)n1;
+  double par[kPar];
+#pragma unroll
+  for (int i = 0; i < kPar; ++i) {
+    const int e = lane + 64 * i, q = min(stage_row<GEN>(e, n1, inv_n1), kItems - 1), k = e - q * n1;
+    const long b = cbase[4 * q];
+    par[i] = (e < kItems * n1 && b >= 0) ? P.Q[b * MQ + k] : 0.0;
+  }
+#ifdef __HIP_DEVICE_COMPILE__
+  __builtin_amdgcn_sched_barrier(0);  // (the loads above stay above the keys below)
+#endif
   // staged values [32][n] of columns p0.. of the value records: deltas, then
   // the records (child 0's takes its parent's place, whose values the deltas
   // have read by then)
-  auto put_values = [&](auto n_, int p0) {
-    const int n = n_;
-#pragma unroll 4
-    for (int e = lane; e < kItems * n; e += 64) {
-      const int i = e / n, k = e - i * n;
-      const long m = ibase[i];
-      if (m >= 0) {
-        const double *c = rec + i * 4 * kStage + k;
+  auto put_values = [&](int n, float inv_n, int p0) {
+#pragma unroll
+    for (int i = 0; i < kPar; ++i) {
+      const int e = lane + 64 * i, q = min(stage_row<GEN>(e, n, inv_n), kItems - 1), k = e - q * n;
+      const long m = ibase[q];
+      if (e < kItems * n && m >= 0) {
+        const double *c = rec + q * 4 * kStage + k;
         const double sum = (c[0] + c[kStage]) + (c[2 * kStage] + c[3 * kStage]);
-        P.dv[m * MQ + p0 + k] = sum - P.Q[cbase[4 * i] * MQ + p0 + k];
+        P.dv[m * MQ + p0 + k] = sum - (p0 ? P.Q[cbase[4 * q] * MQ + p0 + k] : par[i]);
       }
     }
     wave_sync();
 #pragma unroll 4
     for (int e = lane; e < kChildren * n; e += 64) {
-      const int c = e / n, k = e - c * n;
+      const int c = stage_row<GEN>(e, n, inv_n), k = e - c * n;
       const long b = cbase[c];
       if (b >= 0) P.Q[b * MQ + p0 + k] = rec[c * kStage + k];
     }
   };
   // the same for errors, staged as float [32][ld]; the deltas carry the
   // float-rounded errors that are stored and later subtracted
-  [[maybe_unused]] auto put_errors = [&](const float *re, int ld, int n, int p0) {
-    for (int e = lane; e < kItems * n; e += 64) {
-      const int i = e / n, k = e - i * n;
-      const long m = ibase[i];
-      if (m >= 0) {
-        const float *c = re + i * 4 * ld + k;
+  [[maybe_unused]] auto put_errors = [&](const float *re, int ld, int n, float inv_n, int p0) {
+    constexpr int kPe = (kItems * (GEN ? kStage : kPairs9) + 63) / 64;
+    float pe[kPe];  // the parents' errors, read together
+#pragma unroll
+    for (int i = 0; i < kPe; ++i) {
+      const int e = lane + 64 * i, q = min((int)(((float)e + 0.5f) * inv_n), kItems - 1), k = e - q * n;
+      const long b = cbase[4 * q];
+      pe[i] = (e < kItems * n && b >= 0) ? P.E[b * MU + p0 + k] : 0.0f;
+    }
+#pragma unroll
+    for (int i = 0; i < kPe; ++i) {
+      const int e = lane + 64 * i, q = min((int)(((float)e + 0.5f) * inv_n), kItems - 1), k = e - q * n;
+      const long m = ibase[q];
+      if (e < kItems * n && m >= 0) {
+        const float *c = re + q * 4 * ld + k;
         const double sum = ((double)c[0] + (double)c[ld]) + ((double)c[2 * ld] + (double)c[3 * ld]);
-        P.dep[m * MU + p0 + k] = sum - (double)P.E[cbase[4 * i] * MU + p0 + k];
+        P.dep[m * MU + p0 + k] = sum - (double)pe[i];
       }
     }
     wave_sync();
+#pragma unroll 4
     for (int e = lane; e < kChildren * n; e += 64) {
-      const int c = e / n, k = e - c * n;
+      const int c = (int)(((float)e + 0.5f) * inv_n), k = e - c * n;
       const long b = cbase[c];
       if (b >= 0) P.E[b * MU + p0 + k] = re[c * ld + k];
     }
   };
+  // the next group's items have arrived: they are not waited for behind the stores
+  auto loads_done = [&]() {
+#ifdef __HIP_DEVICE_COMPILE__
+    asm volatile("" : "+v"(cur.s), "+v"(cur.r), "+v"(cur.pc), "+v"(cur.ch), "+v"(cur.cLx), "+v"(cur.sLx),
+                      "+v"(cur.cLy), "+v"(cur.sLy));
+#endif
+  };
   double key = 0.0;
   if constexpr (!GEN) {
+    // the key's pairs (and their errors for the records) from the registers
+    [[maybe_unused]] float *re = reinterpret_cast<float *>(rec);
+    auto pairs = [&]() {
+      constexpr PairTab PT = make_pair_tab();
+#pragma unroll
+      for (int p = 0; p < kPairs9; ++p) {
+        const signed char *tp = PT.t[p];
+        double v = I[tp[0]][tp[3]];
+        if (tp[4] >= 0) v = tp[5] > 0 ? v + I[tp[0]][tp[4]] : v - I[tp[0]][tp[4]];
+        if (tp[1] >= 0) {
+          double u = I[tp[1]][tp[3]];
+          if (tp[4] >= 0) u = tp[5] > 0 ? u + I[tp[1]][tp[4]] : u - I[tp[1]][tp[4]];
+          v = tp[2] > 0 ? v + u : v - u;
+        }
+        const double e = fabs(fx * v);  // lane 1: |E| of the pair
+        if constexpr (WW)
+          key += e * (double)wgt[it * kPairs9 + p];
+        else
+          key += e;
+        if constexpr (WE)
+          if (h == 1) re[child * kPairs9 + p] = err_f32(e);
+      }
+    };
+    if constexpr (!WE) pairs();  // the loads above complete behind them
     if (h == 0) {
 #pragma unroll
       for (int j = 0; j < kPhi; ++j)
@@ -1440,49 +1726,32 @@ __device__ void lpc_group(const Problem &P, int erow, const double *tab, double 
         for (int k = 0; k < kPhi; ++k) rec[child * kStage + kPhi * j + k] = fx * I[j][k];
     }
     wave_sync();
-    put_values(std::integral_constant<int, kProd>{}, 0);
-    if constexpr (WE) wave_sync();  // the errors take the values' place
-    float *re = reinterpret_cast<float *>(rec);
-    constexpr PairTab PT = make_pair_tab();
-#pragma unroll
-    for (int p = 0; p < kPairs9; ++p) {
-      const signed char *tp = PT.t[p];
-      double v = I[tp[0]][tp[3]];
-      if (tp[4] >= 0) v = tp[5] > 0 ? v + I[tp[0]][tp[4]] : v - I[tp[0]][tp[4]];
-      if (tp[1] >= 0) {
-        double u = I[tp[1]][tp[3]];
-        if (tp[4] >= 0) u = tp[5] > 0 ? u + I[tp[1]][tp[4]] : u - I[tp[1]][tp[4]];
-        v = tp[2] > 0 ? v + u : v - u;
-      }
-      const double e = fabs(fx * v);  // lane 1: |E| of the pair
-      if constexpr (WW)
-        key += e * (double)wgt[it * kPairs9 + p];
-      else
-        key += e;
-      if constexpr (WE)
-        if (h == 1) re[child * kPairs9 + p] = err_f32(e);
-    }
-    if constexpr (WE) {
+    loads_done();
+    put_values(kProd, 0.0f, 0);
+    if constexpr (WE) {  // the errors take the values' place
       wave_sync();
-      put_errors(re, kPairs9, kPairs9, 0);
+      pairs();
+      wave_sync();
+      put_errors(re, kPairs9, kPairs9, 1.0f / kPairs9, 0);
     }
   } else {
-    // pairs from the product integrals, kStage at a time (the coefficients
-    // are the same for every lane: scalar loads)
+    // pairs from the product integrals, kStage at a time, with the coefficients
+    // from LDS (the same for every lane; by scalar loads from memory each pair
+    // of a cold launch waited for its own)
     [[maybe_unused]] float *re = reinterpret_cast<float *>(rec + kChildren * kStage);
-    typedef const __attribute__((address_space(4))) double CD;
-    CD *co = (CD *)P.pcoef;
 #pragma unroll 1
     for (int p0 = 0; p0 < MU; p0 += kStage) {
       const int n = min(kStage, MU - p0);
-#pragma unroll 1
-      for (int j = 0; j < n; ++j, co += kProd) {
-        double v = 0.0;
+#pragma unroll 3
+      for (int j = 0; j < n; ++j) {
+        const double *c = co + (p0 + j) * kProd;
+        double v = 0.0, u = 0.0;
 #pragma unroll
-        for (int a = 0; a < kPhi; ++a)
-#pragma unroll
-          for (int b = 0; b < kPhi; ++b) v = fma(co[kPhi * a + b], I[a][b], v);
-        const double x = fx * v, e = fabs(x);
+        for (int a = 0; a < kProd; ++a) {
+          double &t = (a & 1) ? u : v;
+          t = fma(c[a], I[a / kPhi][a % kPhi], t);
+        }
+        const double x = fx * (v + u), e = fabs(x);
         if constexpr (WW)
           key += e * (double)wgt[it * kPairs9 + p0 + j];
         else
@@ -1492,8 +1761,9 @@ __device__ void lpc_group(const Problem &P, int erow, const double *tab, double 
           if (h == 1) re[child * kStage + j] = err_f32(e);
       }
       wave_sync();
-      put_values(n, p0);
-      if constexpr (WE) put_errors(re, kStage, n, p0);
+      if (p0 == 0) loads_done();
+      put_values(n, 1.0f / (float)n, p0);
+      if constexpr (WE) put_errors(re, kStage, n, 1.0f / (float)n, p0);
       wave_sync();
     }
   }
@@ -1502,67 +1772,75 @@ __device__ void lpc_group(const Problem &P, int erow, const double *tab, double 
   if (valid) {
     if (h == 1) P.key[base] = key;
     else P.code[base] = ccode;
-    if (P.born && h == 0) P.born[base] = (unsigned int)(1 + 4 * P.st_splits[q.s] + ch);
+    if (P.born && h == 0) P.born[base] = (unsigned int)(1 + 4 * P.st_splits[item_s] + ch);
   }
   if (head && h == 1) P.de[itm] = kk - pkey;
-  if (head && h == 0) {
-    if (P.ifill) P.ifill[itm] = !item_skip;
-    if (dd + 1 > P.st_depth[q.s]) atomicMax(&P.st_depth[q.s], dd + 1);
-  }
+  if (head && h == 0 && P.ifill) P.ifill[itm] = !item_skip;
   wave_sync();  // the next group's node rows take the records' place
 }
 
-// The same work partition and table staging as k_children; inside a segment
-// (items of one parameter row) wave wv takes the groups of 8 items that
-// start at seg + 8 (wv + nw k).
+// The grid is the workgroups resident at once; a workgroup stages a parameter
+// row's tables and its waves take groups of 8 items (LpcShare).
 template <bool BUB, bool WE, bool WW, bool GEN>
-__global__ void __launch_bounds__(512) k_children_lpc(Problem P) {
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(3))) k_children_lpc(Problem P) {
   extern __shared__ double lds_raw[];
-  double *tabl = lds_raw;
-  const int nw = blockDim.x >> 6, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  double *Yw = lds_raw + (size_t)P.tab_rows * kTabStride + (size_t)wv * P.lds_wave_doubles;
-  __shared__ int next[2];
-  Chunk k = first_chunk(P, lpc::kItems);
-  if (k.i0 >= k.i1) return;  // uniform in the workgroup
-  int loaded = -1;
-#pragma unroll 1
-  for (; k.i0 < k.i1; k = next_chunk(P, lpc::kItems, next)) {
-  const int i1 = k.i1;
-  int s = item_slot(P, k.i0), hi = P.woff[s + 1];
-  int seg = k.i0;
-#pragma unroll 1
-  while (seg < i1) {
-    const int e = __builtin_amdgcn_readfirstlane(slot_entry(P, s));
-    int t = s + 1;
-    while (t < P.W && P.woff[t] < i1 && (P.woff[t + 1] == P.woff[t] || slot_entry(P, t) == e)) ++t;
-    const int seg_hi = (t < P.W && P.woff[t] < i1) ? P.woff[t] : i1;
-    if (e != loaded) {
-      __syncthreads();  // every wave is done with the previous table
-      const Entry E0 = P.entries[e];
-      const double *src = P.tab + E0.tab_off;
-      for (int i = threadIdx.x; i < E0.J * kTabStride; i += blockDim.x) tabl[i] = src[i];
-      __syncthreads();
-      loaded = e;
-    }
-#pragma unroll 1
-    for (int g = seg + lpc::kItems * wv; g < seg_hi; g += lpc::kItems * nw) {
-      if (g >= hi) {  // slot holding item g (woff is non-decreasing)
-        int a = s + 1, b = P.W;  // woff[a] <= g < woff[b]
-        while (b - a > 1) {
-          const int mid = (a + b) >> 1;
-          if (P.woff[mid] <= g) a = mid; else b = mid;
-        }
-        s = a;
-        hi = P.woff[s + 1];
+  double *del = lds_raw, *co = lds_raw + kDelDoubles, *tabl = co + (GEN ? (P.MU * kProd + 1) / 2 * 2 : 0);
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  double *Yw = tabl + P.tab_doubles + wv * P.lds_wave_doubles;
+  __shared__ LpcShare share;
+  {  // the first chunk, by index in the XCD's items [x0, x1)
+    // (a grid of fewer workgroups than XCDs: a share per workgroup)
+    const int nx = min(kXcds, (int)gridDim.x), x = blockIdx.x % nx;
+    const int nb = ((int)gridDim.x - x + nx - 1) / nx;  // the XCD's workgroups
+    const long total = P.counters[2];
+    const int x0 = (int)(total * x / nx), x1 = (int)(total * (x + 1) / nx);
+    const int c = share_items(x1 - x0);
+    const int i0 = (int)min((long)x0 + (long)(blockIdx.x / nx) * c, (long)x1), i1 = min(i0 + c, x1);
+    if (i0 >= i1) return;  // uniform in the workgroup
+    if (threadIdx.x < 64) {
+      if (threadIdx.x == 0) {
+        share.base = (int)min((long)x0 + (long)nb * c, (long)x1);
+        share.total = x1;
+        share.lock = 0;
+        share.mode = 0;
+        share.range = 0;
+        share.rest = i0;
+        share.end = i1;
       }
-      lpc_group<BUB, WE, WW, GEN>(kernarg_problem(P), e, tabl, Yw, g, seg_hi, s);
-    }
-    seg = seg_hi;
-    if (seg < i1) {
-      s = t;
-      hi = P.woff[s + 1];
+      wave_sync();
+      next_range(P, share, -1);
     }
   }
+  for (int i = threadIdx.x; i < kDelDoubles; i += blockDim.x) del[i] = rule_value(i);
+  if constexpr (GEN)
+    for (int i = threadIdx.x; i < P.MU * kProd; i += blockDim.x) co[i] = P.pcoef[i];
+#pragma unroll 1
+  for (;;) {
+    __syncthreads();  // every wave is done with the previous row's table
+    if (share.mode == 2) break;
+    const int e = __builtin_amdgcn_readfirstlane(share.row);
+    const Entry E0 = P.entries[e];
+    const double *src = P.tab + E0.tab_off;
+    const int nt = tab_doubles(E0);
+    for (int i = threadIdx.x; i < nt; i += blockDim.x) tabl[i] = src[i];
+    __syncthreads();  // (and has read share.mode)
+    if (threadIdx.x == 0) {
+      atomicExch(&share.range, ((unsigned long long)share.hi << 32) | (unsigned)share.lo);
+      atomicExch(&share.mode, 0);
+    }
+    __syncthreads();
+    LpcRow R;
+    R.mt2 = wave_uniform(-2.0 * E0.t * E0.inv_w);
+    R.mtp4 = wave_uniform(-4.0 * E0.tp * E0.inv_w);
+    R.mmu = wave_uniform(-E0.mu * E0.inv_w);
+    R.J = __builtin_amdgcn_readfirstlane(E0.J);
+    R.JV = __builtin_amdgcn_readfirstlane(E0.JV);
+    int gend, g = take_group(P, share, e, gend);
+    if (g < 0) continue;
+    LpcItem cur = lpc_item(P, g, min(g + (lane_id() >> 3), gend - 1));
+#pragma unroll 1
+    do lpc_group<BUB, WE, WW, GEN>(kernarg_problem(P), R, tabl, del, co, Yw, share, e, g, gend, cur);
+    while (g >= 0);
   }
 }
 
@@ -1589,7 +1867,7 @@ template <int L>
 size_t eval_lds_t(const Problem &p, int *waves_out, int *wave_doubles_out) {
   const size_t wave_b = sizeof(double) * wave_lds_doubles<L>(p.ff_identity);
   // fixed: the kernel's static LDS (two int tables over the form-factor pairs)
-  const size_t tab_b = sizeof(double) * (size_t)p.tab_rows * kTabStride, fixed = 4096;
+  const size_t tab_b = sizeof(double) * (size_t)p.close_doubles, fixed = 4096;
   size_t budget = 65536;
   if (tab_b + wave_b + fixed > budget) budget = p.lds_limit > 0 ? (size_t)p.lds_limit : 65536;
   if (tab_b + wave_b + fixed > budget) return 0;
@@ -1649,7 +1927,8 @@ const void *lpc_kernel(const Problem &p) {
 // table and wave size.
 size_t lpc_lds(const Problem &p, int *waves_out) {
   const size_t wave_b = sizeof(double) * lpc_wave_doubles(p);
-  const size_t tab_b = sizeof(double) * (size_t)p.tab_rows * kTabStride;
+  const size_t tab_b = sizeof(double) * ((size_t)p.tab_doubles + kDelDoubles +
+                                         (needs_pair_coefficients(p) ? (size_t)(p.MU * kProd + 1) / 2 * 2 : 0));
   const size_t limit = p.lds_limit > 0 ? (size_t)p.lds_limit : 65536;
   thread_local size_t memo_tab = 0, memo_wave = 0, memo_limit = 0;
   thread_local int memo_waves = 0;

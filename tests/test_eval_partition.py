@@ -69,3 +69,80 @@ def test_results_do_not_depend_on_the_number_of_workgroups(layout):
         if ref is None:
             ref = out, st["regions"]
         assert np.array_equal(out, ref[0]) and st["regions"] == ref[1]
+
+
+# ------------------------------------------------------------------ slots of items
+def wave_slot(woff, W, g):
+    lo, hi = 0, W
+    while hi - lo > 1:
+        step = (hi - lo + 63) >> 6
+        c = sum(1 for lane in range(64) if lo + (lane + 1) * step < hi and woff[lo + (lane + 1) * step] <= g)
+        lo += c * step
+        hi = min(lo + step, hi)
+    return lo
+
+
+def group_items(woff, W, g0, gend):
+    """slot and place of each of the eight lane groups' items, as the wave forms them"""
+    s = wave_slot(woff, W, g0)
+    off = [woff[min(s + 1 + lane, W)] for lane in range(64)]
+    out = []
+    for it in range(8):
+        w = min(g0 + it, gend - 1)
+        mine = sum(1 for o in off if o <= w)
+        prev = off[max(mine - 1, 0)]
+        lo, t = (prev if mine else woff[s]), s + mine
+        while mine == 64 and woff[t + 1] <= w:
+            t += 1
+            lo = woff[t]
+        out.append((t, w - lo))
+    return out
+
+
+@pytest.mark.parametrize("W", [1, 2, 3, 63, 64, 65, 66, 700, 4097, 5000])
+@pytest.mark.parametrize("fill", [0.02, 0.5, 1.0])
+def test_slots_of_items(W, fill):
+    """against the definition (slot t holds items woff[t]..woff[t + 1] - 1), with
+    runs of empty slots longer than the 64 offsets a wave reads at a time"""
+    rng = np.random.default_rng(W)
+    cnt = np.where(rng.random(W) < fill, rng.integers(1, 40, W), 0)
+    cnt[rng.integers(0, W)] += 5
+    woff = np.concatenate([[0], np.cumsum(cnt)]).tolist()
+    total = woff[-1]
+    slot = np.repeat(np.arange(W), cnt)
+    for g0 in list(range(0, min(total, 200))) + rng.integers(0, total, 100).tolist():
+        assert wave_slot(woff, W, g0) == slot[g0]
+        gend = min(total, g0 + int(rng.integers(1, 20)))
+        for it, (t, r) in enumerate(group_items(woff, W, g0, gend)):
+            w = min(g0 + it, gend - 1)
+            assert t == slot[w] and r == w - woff[t] and 0 <= r < cnt[t]
+
+
+def row_end(woff, entry, W, s, i1):
+    for t0 in range(s + 1, W, 64):
+        past = False
+        for t in range(t0, t0 + 64):
+            lo, up = (woff[t], woff[t + 1]) if t < W else (i1, i1)
+            if lo < i1 and up > lo and entry[t] != entry[s]:
+                return lo
+            past |= lo >= i1
+        if past:
+            break
+    return i1
+
+
+@pytest.mark.parametrize("W", [1, 5, 64, 65, 129, 1000])
+def test_runs_of_one_parameter_row(W):
+    rng = np.random.default_rng(W + 1)
+    cnt = np.where(rng.random(W) < 0.4, rng.integers(1, 9, W), 0)
+    cnt[0] += 1
+    woff = np.concatenate([[0], np.cumsum(cnt)]).tolist()
+    entry = np.sort(rng.integers(0, 1 + W // 20, W))
+    row = np.repeat(entry, cnt)
+    slot = np.repeat(np.arange(W), cnt)
+    for g in rng.integers(0, woff[-1], 200):
+        i1 = int(min(woff[-1], g + rng.integers(1, 500)))
+        want = g
+        while want < i1 and row[want] == row[g]:
+            want += 1
+        assert row_end(woff, entry, W, int(slot[g]), i1) == want
