@@ -2,6 +2,7 @@
 // checks, device workspace, the round loop of the adaptive scheme (Alg. 2)
 // over all containers, and the diagnostic entry points.
 #include <hip/hip_runtime.h>
+#include <limits.h>
 #include <math.h>
 #include <stdarg.h>
 #include <stdio.h>
@@ -12,6 +13,7 @@
 #include <mutex>
 #include <random>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "launch.h"
@@ -78,7 +80,6 @@ struct paid_ctx {
   float *noalloc = nullptr;      // this device's fixed working memory (paid_mlp_loss_grad_noalloc)
   // profile: around the evaluation launch of the two rounds in flight
   hipEvent_t ev0 = nullptr, ev1 = nullptr, ev2 = nullptr, ev3 = nullptr;
-  hipEvent_t evd[2] = {nullptr, nullptr};  // end of each of the two rounds in flight
 };
 
 namespace {
@@ -346,6 +347,28 @@ int finish_out(paid_ctx *c, T *p, const T *d, size_t n) {
   return PAID_OK;
 }
 
+// Waits until the device has stored round `r` of a call in the pinned `h`.  The
+// store comes before the round's evaluation, so a wait is mostly that of the
+// round before; the loop looks at the stream now and then (an error or an idle
+// stream ends it) and gives the processor away once the wait is a long one.
+hipError_t await_round(const HostRound *h, int r, hipStream_t st) {
+  using clock = std::chrono::steady_clock;
+  auto there = [&] { return __atomic_load_n(&h->round, __ATOMIC_ACQUIRE) >= r; };
+  const auto t0 = clock::now();
+  for (;;) {
+    for (int k = 0; k < 256; ++k) {
+      if (there()) return hipSuccess;
+      __builtin_ia32_pause();
+    }
+    const auto waited = clock::now() - t0;
+    if (waited < std::chrono::microseconds(200)) continue;
+    const hipError_t e = hipStreamQuery(st);
+    if (e == hipSuccess) return there() ? hipSuccess : hipErrorUnknown;
+    if (e != hipErrorNotReady) return e;
+    if (waited > std::chrono::milliseconds(2)) std::this_thread::sleep_for(std::chrono::microseconds(20));
+  }
+}
+
 // the form-factor pairs as combinations of the 25 product integrals (general
 // sets over the 9-function box, or over its first function), on the device
 int stage_pair_coefficients(paid_ctx *c, Problem &P, const double *ff) {
@@ -450,7 +473,7 @@ int paid_create(paid_ctx **out, const paid_config *cfg_in) {
     }
     c->own_stream = true;
   }
-  e = hipHostMalloc((void **)&c->host_counters, 64, hipHostMallocDefault);
+  e = hipHostMalloc((void **)&c->host_counters, 256, hipHostMallocDefault);
   if (e != hipSuccess) {
     paid_destroy(c);
     return fail(nullptr, PAID_ENOMEM, "pinned counters: %s", hipGetErrorString(e));
@@ -462,11 +485,6 @@ int paid_create(paid_ctx **out, const paid_config *cfg_in) {
       return fail(nullptr, PAID_EDEVICE, "hipEventCreate failed");
     }
   }
-  for (int k = 0; k < 2; ++k)
-    if (hipEventCreateWithFlags(&c->evd[k], hipEventDisableTiming) != hipSuccess) {
-      paid_destroy(c);
-      return fail(nullptr, PAID_EDEVICE, "hipEventCreate failed");
-    }
   int rc = ensure_rule(c);
   if (rc == PAID_OK) rc = ensure_noalloc(c);
   if (rc != PAID_OK) {
@@ -491,7 +509,7 @@ void paid_destroy(paid_ctx *c) {
                     &c->lq,      &c->pcoef, &c->rowsz, &c->rperm, &c->movei, &c->upart};
   for (DevBuf *b : bufs) b->release();
   if (c->host_counters) (void)hipHostFree(c->host_counters);
-  for (hipEvent_t ev : {c->ev0, c->ev1, c->ev2, c->ev3, c->evd[0], c->evd[1]})
+  for (hipEvent_t ev : {c->ev0, c->ev1, c->ev2, c->ev3})
     if (ev) (void)hipEventDestroy(ev);
   if (c->own_stream && c->stream) (void)hipStreamDestroy(c->stream);
   delete c;
@@ -705,10 +723,6 @@ int paid_integrate(paid_ctx *c, const paid_params *params, int n_params, const d
   }
   P.err_out = err_out ? (err_dev ? err_out : c->errs.as<double>()) : nullptr;
 
-  HIPCHK(c, hipMemsetAsync(c->slot_i.p, 0, sizeof(int) * (8 * W + 8), c->stream));
-  HIPCHK(c, hipMemsetAsync(c->counters.p, 0, 256, c->stream));
-  HIPCHK(c, hipMemsetAsync(c->stl.p, 0, sizeof(long) * 3 * W, c->stream));
-
   if (cfg.err_mode == PAID_ERR_WEIGHTED) {
     if (!c->pair_w) return fail(c, PAID_EINVAL, "PAID_ERR_WEIGHTED needs paid_set_pair_weights");
     const size_t nw = (size_t)n_ctr * M * M;
@@ -791,40 +805,37 @@ int paid_integrate(paid_ctx *c, const paid_params *params, int n_params, const d
   const int eval_grid = dev_cus * (cfg.eval_wg_per_cu > 0 ? cfg.eval_wg_per_cu : eval_occupancy(P));
   long rounds = 0, eval_items = 0;
   double eval_ms = 0.0;
-  // one device round in three parts: admission, roots, selection and work
-  // list; evaluation; updates, finalisation and the read-back of the three
-  // counters the host needs (into one of two pinned buffers: parts 2 and 3
-  // are the third part with buffer 0 and 1)
-  auto part = [&](int k, hipStream_t st) -> hipError_t {
+  // One device round in two parts: the moves and roots of what was admitted,
+  // the deltas of the last evaluation, selection and work list; evaluation.
+  // `items` (of the last round) and `fresh` bound what is left to do: a launch
+  // that would find nothing is not made.
+  HostRound *hr = reinterpret_cast<HostRound *>(c->host_counters + 32);
+  auto part = [&](int k, long items, int fresh, hipStream_t st) -> hipError_t {
     hipError_t e;
-    if (k == 0) {
-      if ((e = launch_move(P, st)) != hipSuccess) return e;
-      if ((e = launch_admit(P, st)) != hipSuccess) return e;
-      if ((e = launch_root(P, st)) != hipSuccess) return e;
-      if ((e = launch_select(P, st)) != hipSuccess) return e;
-      return launch_worklist(P, st);
-    }
     if (k == 1) return launch_eval(P, eval_grid, st);
-    if ((e = launch_update(P, st)) != hipSuccess) return e;
-    if ((e = launch_finalize(P, st)) != hipSuccess) return e;
-    return hipMemcpyAsync(c->host_counters + 4 * (k - 2), cnt + 4, 12, hipMemcpyDeviceToHost, st);
+    if ((e = launch_move(P, st)) != hipSuccess) return e;
+    if ((e = launch_admit(P, st)) != hipSuccess) return e;
+    if ((fresh > 0 || P.Wb > 0) && (e = launch_root(P, st)) != hipSuccess) return e;
+    if ((e = launch_update(P, items, st)) != hipSuccess) return e;
+    if ((e = launch_slots(P, st)) != hipSuccess) return e;
+    return launch_worklist(P, hr, st);
   };
-  // with cfg.graph each part is captured once and replayed every round (the
-  // arguments of every launch are the same in every round); the profiling
+  // with cfg.graph each part is captured once, whole, and replayed every round
+  // (the arguments of every launch are the same in every round); the profiling
   // events are recorded between the parts, outside the graphs
-  hipGraphExec_t gexec[4] = {nullptr, nullptr, nullptr, nullptr};
+  hipGraphExec_t gexec[2] = {nullptr, nullptr};
   struct GraphGuard {
     hipGraphExec_t *ge;
     ~GraphGuard() {
-      for (int k = 0; k < 4; ++k)
+      for (int k = 0; k < 2; ++k)
         if (ge[k]) (void)hipGraphExecDestroy(ge[k]);
     }
   } gguard{gexec};
   if (cfg.graph) {
-    for (int k = 0; k < 4; ++k) {
+    for (int k = 0; k < 2; ++k) {
       hipGraph_t g = nullptr;
       HIPCHK(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeRelaxed));
-      hipError_t e1 = part(k, c->stream);
+      hipError_t e1 = part(k, LONG_MAX, 1, c->stream);
       hipError_t e2 = hipStreamEndCapture(c->stream, &g);
       if (e1 != hipSuccess || e2 != hipSuccess) {
         if (g) (void)hipGraphDestroy(g);
@@ -835,45 +846,45 @@ int paid_integrate(paid_ctx *c, const paid_params *params, int n_params, const d
       HIPCHK(c, e3);
     }
   }
-  auto run_part = [&](int k) -> hipError_t {
-    return gexec[k] ? hipGraphLaunch(gexec[k], c->stream) : part(k, c->stream);
+  auto run_part = [&](int k, long items, int fresh) -> hipError_t {
+    return gexec[k] ? hipGraphLaunch(gexec[k], c->stream) : part(k, items, fresh, c->stream);
   };
-  // Two rounds in flight: round r + 1 is queued before the host reads the
-  // counters of round r, so the device does not wait for the host between
-  // rounds.  A round queued after the last one finds nothing to do (no
-  // container left to admit, select or update).
   hipEvent_t evb[2] = {c->ev0, c->ev2}, eve[2] = {c->ev1, c->ev3};
-  auto launch_round = [&](int buf) -> hipError_t {
+  auto launch_round = [&](int buf, long items, int fresh) -> hipError_t {
     hipError_t e;
-    if ((e = run_part(0)) != hipSuccess) return e;
+    if ((e = run_part(0, items, fresh)) != hipSuccess) return e;
     if (cfg.profile && (e = hipEventRecord(evb[buf], c->stream)) != hipSuccess) return e;
-    if ((e = run_part(1)) != hipSuccess) return e;
+    if ((e = run_part(1, items, fresh)) != hipSuccess) return e;
     if (cfg.profile && (e = hipEventRecord(eve[buf], c->stream)) != hipSuccess) return e;
-    if ((e = run_part(2 + buf)) != hipSuccess) return e;
-    return hipEventRecord(c->evd[buf], c->stream);
+    return hipSuccess;
   };
-  HIPCHK(c, launch_round(0));
-  int last = 0;  // buffer of the last round read
+  auto add_eval_ms = [&](int buf) -> hipError_t {
+    hipError_t e = hipEventSynchronize(eve[buf]);
+    float ms = 0.f;
+    if (e == hipSuccess) e = hipEventElapsedTime(&ms, evb[buf], eve[buf]);
+    eval_ms += ms;
+    return e;
+  };
+  // The host has a round's counters when its work list stands, before its
+  // evaluation, and queues the next round while that runs: the device does
+  // not wait for the host, and no round is queued after the last.
+  HIPCHK(c, launch_start(P, c->stream));
+  hr->round = 0;
+  HostRound h{};
   for (long r = 0;; ++r) {
-    const int buf = (int)(r & 1);
-    HIPCHK(c, launch_round(buf ^ 1));
-    HIPCHK(c, hipEventSynchronize(c->evd[buf]));
-    const int *hc = c->host_counters + 4 * buf;
-    last = buf;
+    HIPCHK(c, launch_round((int)(r & 1), h.items, r == 0 ? 1 : h.fresh));
     ++rounds;
-    eval_items += hc[2];
-    if (cfg.profile) {
-      float ms = 0.f;
-      HIPCHK(c, hipEventElapsedTime(&ms, evb[buf], eve[buf]));
-      eval_ms += ms;
-    }
-    if (hc[0] >= n_ctr) break;
+    HIPCHK(c, await_round(hr, rounds, c->stream));
+    h = *hr;
+    eval_items += h.items;
+    if (cfg.profile && r > 0) HIPCHK(c, add_eval_ms((int)(r - 1) & 1));
+    if (h.done >= n_ctr) break;
     if (rounds > 4L * cfg.max_regions + 64L * (n_ctr / Ws + 1)) {
       (void)hipStreamSynchronize(c->stream);
       return fail(c, PAID_EINTERNAL, "round loop did not finish (%ld rounds)", rounds);
     }
   }
-  HIPCHK(c, hipStreamSynchronize(c->stream));  // the round queued after the last
+  if (cfg.profile) HIPCHK(c, add_eval_ms((int)(rounds - 1) & 1));
   if (!out_dev) HIPCHK(c, hipMemcpyAsync(out, c->outs.p, out_bytes, hipMemcpyDeviceToHost, c->stream));
   if (err_out && !err_dev)
     HIPCHK(c, hipMemcpyAsync(err_out, c->errs.p, out_bytes, hipMemcpyDeviceToHost, c->stream));
@@ -887,19 +898,17 @@ int paid_integrate(paid_ctx *c, const paid_params *params, int n_params, const d
   if (c->lab_out && P.labels != c->lab_out)
     HIPCHK(c, hipMemcpyAsync(c->lab_out, P.labels, sizeof(float) * kMlpOut * (size_t)n_ctr,
                              hipMemcpyDefault, c->stream));
-  long long gs[5] = {0, 0, 0, 0, 0};
-  HIPCHK(c, hipMemcpyAsync(gs, P.gstats, sizeof gs, hipMemcpyDeviceToHost, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
-  const int notconv = c->host_counters[4 * last + 1];
+  const int notconv = h.not_converged;
   if (stats) {
     memset(stats, 0, sizeof *stats);
     stats->containers = n_ctr;
     stats->not_converged = notconv;
-    stats->rounds = gs[0];
-    stats->splits = gs[1];
-    stats->regions = gs[2];
-    stats->max_depth = (int)gs[3];
-    stats->kernel_evals = gs[4];
+    stats->rounds = h.stats[0];
+    stats->splits = h.stats[1];
+    stats->regions = h.stats[2];
+    stats->max_depth = (int)h.stats[3];
+    stats->kernel_evals = h.stats[4];
     stats->launch_rounds = rounds;
     stats->max_active = (int)W;
     stats->seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();

@@ -116,7 +116,7 @@ struct Problem {      // everything the round kernels need, passed by value
   int *st_depth;              // [W]
   // queue and global counters
   int *qhead;                 // next container to admit
-  int *counters;              // [0] done, [1] not converged, [2] total work items, [3] chunk counter
+  int *counters;              // [0] done, [1] not converged, [2] total work items, [3] chunk counter, [4] round
   int *xcount;                // [kXcds * kXcdStride] the evaluation's chunk counters
   long long *gstats;          // [0] rounds [1] splits [2] leaves [3] max depth
   // outputs (device)
@@ -212,8 +212,20 @@ hipError_t launch_move(const Problem &p, hipStream_t s);
 // of max(0, 2^y - 1)), in a fixed summation order
 hipError_t launch_seed_rowsize(const float *y, int n_rows, int per_row, double *out, hipStream_t s);
 hipError_t launch_root(const Problem &p, hipStream_t s);
-hipError_t launch_select(const Problem &p, hipStream_t s);
-hipError_t launch_worklist(const Problem &p, hipStream_t s);
+// what the host reads of a round, in its pinned memory
+struct HostRound {
+  int round;                // rounds so far, written last
+  int done, not_converged;  // containers
+  int items;                // parents to evaluate in this round
+  int fresh;                // containers admitted for the next one
+  long long stats[5];       // Problem::gstats
+};
+// slots and counters cleared, the first containers admitted
+hipError_t launch_start(const Problem &p, hipStream_t s);
+// deltas, termination tests, selections and outputs of every slot
+hipError_t launch_slots(const Problem &p, hipStream_t s);
+// work list, admission and the host's counters
+hipError_t launch_worklist(const Problem &p, HostRound *host, hipStream_t s);
 // whether leaves hold the 25 product integrals instead of the pairs (by the
 // static description alone)
 bool leaves_hold_products(const Problem &p);
@@ -226,8 +238,8 @@ size_t eval_lds_bytes(const Problem &p);
 // evaluation workgroups that fit on one compute unit at once for p
 int eval_occupancy(const Problem &p);
 hipError_t launch_eval(const Problem &p, int grid, hipStream_t s);
-hipError_t launch_update(const Problem &p, hipStream_t s);
-hipError_t launch_finalize(const Problem &p, hipStream_t s);
+// chunk sums of the deltas of containers that split many leaves at once
+hipError_t launch_update(const Problem &p, long items, hipStream_t s);
 
 // diagnostics
 hipError_t launch_kernel_eval(const Entry *e, const double *tab, int ch, const double *a,

@@ -95,7 +95,7 @@ __device__ inline int block_scan(int v, int *sh, int &excl) {
 // and four independent accumulators keep loads in flight; the R partials of
 // a column are then added in order.  Wider blocks go column by column.
 template <class T>
-__device__ void column_sums(const T *A, long rows, int ncol, double *out, double *shd) {
+__device__ __forceinline__ void column_sums(const T *A, long rows, int ncol, double *out, double *shd) {
   const int t = threadIdx.x, nt = blockDim.x;
   if (ncol <= nt) {
     const int R = nt / ncol, span = R * ncol;
@@ -139,7 +139,7 @@ __device__ void column_sums(const T *A, long rows, int ncol, double *out, double
 // Sum of the leaf keys of a slot (fixed order); with per-pair errors stored,
 // also their column sums.  The values themselves are the running FP64 sums
 // of Q over the leaves (updated at every split).
-__device__ double resum_errors(const Problem &P, int s, double *shd) {
+__device__ __forceinline__ double resum_errors(const Problem &P, int s, double *shd) {
   const int t = threadIdx.x;
   const long n = P.nleaf[s], base = slot_base(P, s);
   double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
@@ -172,7 +172,7 @@ constexpr double kResumMargin = 1e-3;
 // the margin (the error sums must be recomputed from the leaves before it is
 // accepted), 2 if it passes by more than the margin.  In the per-integral
 // mode also refreshes the key weights 1/tau used for new children.
-__device__ int tolerance_test(const Problem &P, int s, double *shd, double &eps, double &deficit) {
+__device__ __forceinline__ int tolerance_test(const Problem &P, int s, double *shd, double &eps, double &deficit) {
   const int t = threadIdx.x;
   double a = 0.0, mx = 0.0;
   for (int pid = t; pid < P.MU; pid += blockDim.x) {
@@ -238,18 +238,13 @@ __device__ inline void note_depth(const Problem &P, int s, int d, int *sh) {
   }
 }
 
-__global__ void __launch_bounds__(kSelThreads) k_select(Problem P) {
-  __shared__ double shd[2 * kSelThreads];
-  __shared__ int shi[kSelThreads];
+// Termination test and, where it fails, the leaves that an active slot splits
+// this round.
+__device__ __forceinline__ void select_leaves(const Problem &P, int s, double *shd, int *shi) {
   __shared__ unsigned int hcnt[kBins];
   __shared__ unsigned long long hsum[kBins];
   __shared__ int s_bfull, s_bpart, s_part, s_k;
-  const int s = blockIdx.x, t = threadIdx.x;
-  if (s >= P.W) return;
-  if (P.state[s] != SLOT_ACTIVE) {
-    if (t == 0) P.selcnt[s] = 0;
-    return;
-  }
+  const int t = threadIdx.x;
   if (P.flags[s] & kFlagSeed) {
     // seed phase: the leaves the seed tree splits, in index order; no
     // termination test while placeholders may exist.  The seed tree has at
@@ -568,7 +563,73 @@ __global__ void __launch_bounds__(kSelThreads) k_select(Problem P) {
   }
 }
 
-__global__ void k_worklist(Problem P) {
+// the container at place k of the queue
+__device__ inline int queued(const Problem &P, int k) {
+  return P.row_perm ? P.row_perm[k / P.per_row] * P.per_row + k % P.per_row : k;
+}
+
+// The start of a call: every slot and counter cleared, the first containers
+// admitted.
+__global__ void k_start(Problem P) {
+  const int s = blockIdx.x * blockDim.x + threadIdx.x;
+  const int first = P.n_ctr < P.W - P.Wb ? P.n_ctr : P.W - P.Wb;
+  if (s < P.W) {
+    const int k = s - P.Wb;
+    const bool take = k >= 0 && k < first;
+    P.cid[s] = take ? queued(P, k) : 0;
+    P.state[s] = take ? SLOT_NEW : SLOT_EMPTY;
+    P.nleaf[s] = 0;
+    P.selcnt[s] = 0;
+    P.flags[s] = 0;
+    P.st_depth[s] = 0;
+    P.st_rounds[s] = 0;
+    P.st_splits[s] = 0;
+    P.st_evals[s] = 0;
+  }
+  if (blockIdx.x == 0) {
+    const int t = threadIdx.x;
+    if (t == 0) *P.qhead = first;
+    if (t < 5) P.counters[t] = 0;
+    if (t < 5) P.gstats[t] = 0;
+    if (t < kXcds) P.xcount[t * kXcdStride] = 0;
+  }
+}
+
+// Admission of containers (one workgroup): empty slots take the next of the
+// queue in slot order.  Returns how many.
+__device__ __forceinline__ int admit(const Problem &P, int *shi) {
+  __shared__ int s_head;
+  const int t = threadIdx.x;
+  if (t == 0) s_head = *P.qhead;
+  __syncthreads();
+  const int head0 = s_head;
+  if (head0 >= P.n_ctr) return 0;
+  int head = head0;
+  for (int b0 = 0; b0 < P.W; b0 += blockDim.x) {
+    // new containers start in small slots (all slots when there is one kind)
+    int s = b0 + t, e = (s < P.W && s >= P.Wb && P.state[s] == SLOT_EMPTY) ? 1 : 0, ex;
+    int tot = block_scan(e, shi, ex);
+    if (e && head + ex < P.n_ctr) {
+      P.cid[s] = queued(P, head + ex);
+      P.state[s] = SLOT_NEW;
+    }
+    head += tot;
+  }
+  if (head > P.n_ctr) head = P.n_ctr;
+  if (t == 0) *P.qhead = head;
+  return head - head0;
+}
+
+__global__ void __launch_bounds__(1024) k_admit(Problem P) {
+  __shared__ int shi[1024];
+  admit(P, shi);
+}
+
+// The round's work list (an exclusive prefix over the slots' selections), the
+// admission for the next round (with slots of two sizes it follows the moves
+// of that round instead) and the host's copy of the counters, stored straight
+// to its pinned memory, the round's number last.
+__global__ void __launch_bounds__(1024) k_worklist(Problem P, HostRound *host) {
   __shared__ int shi[1024];
   const int t = threadIdx.x;
   int carry = 0;
@@ -578,36 +639,20 @@ __global__ void k_worklist(Problem P) {
     if (s < P.W) P.woff[s] = carry + ex;
     carry += tot;
   }
+  const int fresh = P.Wb > 0 ? 0 : admit(P, shi);
+  if (t < kXcds) P.xcount[t * kXcdStride] = 0;
   if (t == 0) {
     P.woff[P.W] = carry;
     P.counters[2] = carry;
     P.counters[3] = 0;  // the evaluation's chunk counters
+    const int round = ++P.counters[4];
+    host->done = P.counters[0];
+    host->not_converged = P.counters[1];
+    host->items = carry;
+    host->fresh = fresh;
+    for (int k = 0; k < 5; ++k) host->stats[k] = P.gstats[k];
+    __hip_atomic_store(&host->round, round, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
   }
-  if (t < kXcds) P.xcount[t * kXcdStride] = 0;
-}
-
-// Container admission: empty slots take the next containers of the queue in
-// slot order.
-__global__ void k_admit(Problem P) {
-  __shared__ int shi[1024];
-  __shared__ int s_head;
-  const int t = threadIdx.x;
-  if (t == 0) s_head = *P.qhead;
-  __syncthreads();
-  if (s_head >= P.n_ctr) return;
-  int head = s_head;
-  for (int b0 = 0; b0 < P.W; b0 += blockDim.x) {
-    // new containers start in small slots (all slots when there is one kind)
-    int s = b0 + t, e = (s < P.W && s >= P.Wb && P.state[s] == SLOT_EMPTY) ? 1 : 0, ex;
-    int tot = block_scan(e, shi, ex);
-    if (e && head + ex < P.n_ctr) {
-      const int k = head + ex;
-      P.cid[s] = P.row_perm ? P.row_perm[k / P.per_row] * P.per_row + k % P.per_row : k;
-      P.state[s] = SLOT_NEW;
-    }
-    head += tot;
-  }
-  if (t == 0) *P.qhead = head < P.n_ctr ? head : P.n_ctr;
 }
 
 // The per-parent deltas of a round, summed per container in a fixed order:
@@ -624,12 +669,8 @@ __device__ inline int upd_chunks(int k) {
 }
 
 // one chunk's sums: [MQ] values, [MU] per-pair errors, key delta, filled items
-__global__ void __launch_bounds__(kSelThreads) k_update_part(Problem P) {
-  __shared__ double shd[2 * kSelThreads];
-  const int s = blockIdx.x, c = blockIdx.y, t = threadIdx.x;
-  if (s >= P.W) return;
-  const int k = P.selcnt[s], nch = upd_chunks(k);
-  if (c >= nch) return;
+__device__ __forceinline__ void chunk_sums(const Problem &P, int s, int c, int k, int nch, double *shd) {
+  const int t = threadIdx.x;
   const int per = (k + nch - 1) / nch, r0 = c * per, r1 = r0 + per < k ? r0 + per : k;
   const long it0 = (long)s * P.bmax + r0;
   const long MU = P.MU, MQ = P.MQ;
@@ -649,12 +690,22 @@ __global__ void __launch_bounds__(kSelThreads) k_update_part(Problem P) {
   }
 }
 
-__global__ void __launch_bounds__(kSelThreads) k_update(Problem P) {
-  const int s = blockIdx.x, t = threadIdx.x;
-  if (s >= P.W) return;
-  const int k = P.selcnt[s];
-  if (k == 0) return;
-  const int nch = upd_chunks(k);
+// the chunks of the containers that have more than one (one is summed where it
+// is added)
+__global__ void __launch_bounds__(kSelThreads) k_update_part(Problem P) {
+  __shared__ double shd[2 * kSelThreads];
+  const int s = blockIdx.x, c = blockIdx.y;
+  const int k = P.selcnt[s], nch = upd_chunks(k);
+  if (nch > 1 && c < nch) chunk_sums(P, s, c, k, nch, shd);
+}
+
+// the deltas of the last round's k splits into the slot's sums
+__device__ __forceinline__ void add_deltas(const Problem &P, int s, int k, double *shd) {
+  const int t = threadIdx.x, nch = upd_chunks(k);
+  if (nch == 1) {
+    chunk_sums(P, s, 0, k, 1, shd);
+    __syncthreads();
+  }
   const long MU = P.MU, MQ = P.MQ, len = MQ + MU + 2;
   const double *part = P.upart + (long)s * kUpdChunks * len;
   for (long i = t; i < MQ; i += blockDim.x) {
@@ -680,6 +731,7 @@ __global__ void __launch_bounds__(kSelThreads) k_update(Problem P) {
     P.st_rounds[s] += 1;
     P.st_splits[s] += (long)k * images(P);
   }
+  __syncthreads();
 }
 
 // Labels of a finished tree: per cell of the 16 x 16 grid, log2(1 + n) with
@@ -715,10 +767,9 @@ __device__ void tree_labels(const Problem &P, int s, long c, double *cnt) {
     P.labels[c * (kSeedG * kSeedG) + seed_model_cell(fold, k & 15, k >> 4)] = (float)log2(1.0 + cnt[k]);
 }
 
-__global__ void __launch_bounds__(kSelThreads) k_finalize(Problem P) {
-  __shared__ double shd[2 * kSelThreads];
-  const int s = blockIdx.x, t = threadIdx.x;
-  if (s >= P.W || P.state[s] != SLOT_DONE) return;
+// outputs and statistics of a finished container; its slot is free again
+__device__ __forceinline__ void finish_slot(const Problem &P, int s, double *shd) {
+  const int t = threadIdx.x;
   if (P.flags[s] & 2) resum_errors(P, s, shd);  // budget exit: error sums from the leaves
   const long c = P.cid[s];
   if (P.labels) tree_labels(P, s, c, shd);
@@ -770,6 +821,26 @@ __global__ void __launch_bounds__(kSelThreads) k_finalize(Problem P) {
     atomicAdd((unsigned long long *)&P.gstats[4], (unsigned long long)P.st_evals[s]);
     P.state[s] = SLOT_EMPTY;
   }
+}
+
+// One round of a slot's bookkeeping in one launch: the deltas of the splits that
+// the last evaluation made, the termination test, the selection of the leaves
+// to split next and, for a container that has ended, its outputs.  (Seven
+// launches a round and a copy to the host, each a few microseconds beside an
+// evaluation of twenty, were two thirds of a small call's time.)
+__global__ void __launch_bounds__(kSelThreads) k_slot(Problem P) {
+  __shared__ double shd[2 * kSelThreads];
+  __shared__ int shi[kSelThreads];
+  const int s = blockIdx.x, t = threadIdx.x;
+  if (P.state[s] != SLOT_ACTIVE) {
+    if (t == 0) P.selcnt[s] = 0;
+    return;
+  }
+  const int k = P.selcnt[s];
+  if (k > 0) add_deltas(P, s, k, shd);
+  select_leaves(P, s, shd, shi);
+  __syncthreads();
+  if (P.state[s] == SLOT_DONE) finish_slot(P, s, shd);
 }
 
 }  // namespace
@@ -880,28 +951,28 @@ hipError_t launch_seed_rowsize(const float *y, int n_rows, int per_row, double *
   return hipGetLastError();
 }
 
+hipError_t launch_start(const Problem &p, hipStream_t s) {
+  hipLaunchKernelGGL(k_start, dim3((p.W + 255) / 256), dim3(256), 0, s, p);
+  return hipGetLastError();
+}
 hipError_t launch_admit(const Problem &p, hipStream_t s) {
+  if (p.Wb == 0) return hipSuccess;  // done by k_worklist
   hipLaunchKernelGGL(k_admit, dim3(1), dim3(1024), 0, s, p);
   return hipGetLastError();
 }
-hipError_t launch_select(const Problem &p, hipStream_t s) {
-  hipLaunchKernelGGL(k_select, dim3(p.W), dim3(kSelThreads), 0, s, p);
+hipError_t launch_slots(const Problem &p, hipStream_t s) {
+  hipLaunchKernelGGL(k_slot, dim3(p.W), dim3(kSelThreads), 0, s, p);
   return hipGetLastError();
 }
-hipError_t launch_worklist(const Problem &p, hipStream_t s) {
-  hipLaunchKernelGGL(k_worklist, dim3(1), dim3(1024), 0, s, p);
+hipError_t launch_worklist(const Problem &p, HostRound *host, hipStream_t s) {
+  hipLaunchKernelGGL(k_worklist, dim3(1), dim3(1024), 0, s, p, host);
   return hipGetLastError();
 }
-hipError_t launch_update(const Problem &p, hipStream_t s) {
+hipError_t launch_update(const Problem &p, long items, hipStream_t s) {
+  if (p.bmax <= kUpdMinRows || items <= kUpdMinRows) return hipSuccess;  // one chunk each: summed by k_slot
   hipLaunchKernelGGL(k_update_part, dim3(p.W, kUpdChunks), dim3(kSelThreads), 0, s, p);
-  hipLaunchKernelGGL(k_update, dim3(p.W), dim3(64), 0, s, p);
   return hipGetLastError();
 }
 
 size_t update_scratch_doubles(int W, int MQ, int MU) { return (size_t)W * kUpdChunks * ((size_t)MQ + MU + 2); }
-hipError_t launch_finalize(const Problem &p, hipStream_t s) {
-  hipLaunchKernelGGL(k_finalize, dim3(p.W), dim3(kSelThreads), 0, s, p);
-  return hipGetLastError();
-}
-
 }  // namespace paid
