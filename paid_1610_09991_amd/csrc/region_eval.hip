@@ -1583,7 +1583,7 @@ __device__ void lpc_group(const Problem &P, const LpcRow &R, const double *tab, 
   const long itm = (long)item_s * P.bmax + item_r;
   const long leaf = P.sel[itm];
   const long nold = P.nleaf[item_s];
-  const double pkey = P.key[sbase + leaf];
+  double pkey = P.key[sbase + leaf];
   // the next group's items (cleared otherwise: the old ones are not kept
   // through the node loop)
   cur = LpcItem{};
@@ -1632,6 +1632,19 @@ __device__ void lpc_group(const Problem &P, const LpcRow &R, const double *tab, 
     const long b = cbase[4 * q];
     par[i] = (e < kItems * n1 && b >= 0) ? P.Q[b * MQ + k] : 0.0;
   }
+  // and their errors
+  constexpr int kPe = WE ? (kItems * (GEN ? kStage : kPairs9) + 63) / 64 : 1;
+  const int ne1 = GEN ? n1 : kPairs9;
+  const float inv_ne1 = GEN ? inv_n1 : 1.0f / kPairs9;
+  [[maybe_unused]] float pe[kPe];
+  if constexpr (WE) {
+#pragma unroll
+    for (int i = 0; i < kPe; ++i) {
+      const int e = lane + 64 * i, q = min((int)(((float)e + 0.5f) * inv_ne1), kItems - 1), k = e - q * ne1;
+      const long b = cbase[4 * q];
+      pe[i] = (e < kItems * ne1 && b >= 0) ? P.E[b * MU + k] : 0.0f;
+    }
+  }
 #ifdef __HIP_DEVICE_COMPILE__
   __builtin_amdgcn_sched_barrier(0);  // (the loads above stay above the keys below)
 #endif
@@ -1660,14 +1673,6 @@ __device__ void lpc_group(const Problem &P, const LpcRow &R, const double *tab, 
   // the same for errors, staged as float [32][ld]; the deltas carry the
   // float-rounded errors that are stored and later subtracted
   [[maybe_unused]] auto put_errors = [&](const float *re, int ld, int n, float inv_n, int p0) {
-    constexpr int kPe = (kItems * (GEN ? kStage : kPairs9) + 63) / 64;
-    float pe[kPe];  // the parents' errors, read together
-#pragma unroll
-    for (int i = 0; i < kPe; ++i) {
-      const int e = lane + 64 * i, q = min((int)(((float)e + 0.5f) * inv_n), kItems - 1), k = e - q * n;
-      const long b = cbase[4 * q];
-      pe[i] = (e < kItems * n && b >= 0) ? P.E[b * MU + p0 + k] : 0.0f;
-    }
 #pragma unroll
     for (int i = 0; i < kPe; ++i) {
       const int e = lane + 64 * i, q = min((int)(((float)e + 0.5f) * inv_n), kItems - 1), k = e - q * n;
@@ -1675,7 +1680,7 @@ __device__ void lpc_group(const Problem &P, const LpcRow &R, const double *tab, 
       if (e < kItems * n && m >= 0) {
         const float *c = re + q * 4 * ld + k;
         const double sum = ((double)c[0] + (double)c[ld]) + ((double)c[2 * ld] + (double)c[3 * ld]);
-        P.dep[m * MU + p0 + k] = sum - (double)pe[i];
+        P.dep[m * MU + p0 + k] = sum - (double)(p0 ? P.E[cbase[4 * q] * MU + p0 + k] : pe[i]);
       }
     }
     wave_sync();
@@ -1686,9 +1691,14 @@ __device__ void lpc_group(const Problem &P, const LpcRow &R, const double *tab, 
       if (b >= 0) P.E[b * MU + p0 + k] = re[c * ld + k];
     }
   };
-  // the next group's items have arrived: they are not waited for behind the stores
+  // everything read has arrived, the next group's items too: no load is waited
+  // for behind the stores
   auto loads_done = [&]() {
 #ifdef __HIP_DEVICE_COMPILE__
+    asm volatile("" : "+v"(pkey));
+    if constexpr (WE)
+#pragma unroll
+      for (int i = 0; i < kPe; ++i) asm volatile("" : "+v"(pe[i]));
     asm volatile("" : "+v"(cur.s), "+v"(cur.r), "+v"(cur.pc), "+v"(cur.ch), "+v"(cur.cLx), "+v"(cur.sLx),
                       "+v"(cur.cLy), "+v"(cur.sLy));
 #endif
@@ -1735,30 +1745,45 @@ __device__ void lpc_group(const Problem &P, const LpcRow &R, const double *tab, 
       put_errors(re, kPairs9, kPairs9, 1.0f / kPairs9, 0);
     }
   } else {
-    // pairs from the product integrals, kStage at a time, with the coefficients
-    // from LDS (the same for every lane; by scalar loads from memory each pair
-    // of a cold launch waited for its own)
+    // pairs from the product integrals, kStage at a time.  Lane a of each half
+    // wave reads coefficient a of a pair from LDS and hands it on through a
+    // scalar register: read by every lane as they stand, the 25 coefficients
+    // of a pair are thirteen LDS round trips in a row, and by scalar loads from
+    // memory each pair of a cold launch waits for its own.
     [[maybe_unused]] float *re = reinterpret_cast<float *>(rec + kChildren * kStage);
+    const int ca = min(lane & 31, kProd - 1);
 #pragma unroll 1
     for (int p0 = 0; p0 < MU; p0 += kStage) {
       const int n = min(kStage, MU - p0);
-#pragma unroll 3
-      for (int j = 0; j < n; ++j) {
-        const double *c = co + (p0 + j) * kProd;
-        double v = 0.0, u = 0.0;
+      // two pairs at a time: one of each half wave's coefficients
+      double cn = co[min(p0 + (lane >> 5), MU - 1) * kProd + ca];
+#pragma unroll 1
+      for (int j = 0; j < n; j += 2) {
+        const long long cb = __double_as_longlong(cn);
+        cn = co[min(p0 + j + 2 + (lane >> 5), MU - 1) * kProd + ca];
+        const int clo = (int)cb, chi = (int)(cb >> 32);
 #pragma unroll
-        for (int a = 0; a < kProd; ++a) {
-          double &t = (a & 1) ? u : v;
-          t = fma(c[a], I[a / kPhi][a % kPhi], t);
+        for (int jj = 0; jj < 2; ++jj) {
+          double v = 0.0, u = 0.0;
+#pragma unroll
+          for (int a = 0; a < kProd; ++a) {
+            const int lo = __builtin_amdgcn_readlane(clo, 32 * jj + a);
+            const int hi = __builtin_amdgcn_readlane(chi, 32 * jj + a);
+            const double c = __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+            double &t = (a & 1) ? u : v;
+            t = fma(c, I[a / kPhi][a % kPhi], t);
+          }
+          if (j + jj < n) {  // (an odd last pair)
+            const double x = fx * (v + u), e = fabs(x);
+            if constexpr (WW)
+              key += e * (double)wgt[it * kPairs9 + p0 + j + jj];
+            else
+              key += e;
+            if (h == 0) rec[child * kStage + j + jj] = x;
+            if constexpr (WE)
+              if (h == 1) re[child * kStage + j + jj] = err_f32(e);
+          }
         }
-        const double x = fx * (v + u), e = fabs(x);
-        if constexpr (WW)
-          key += e * (double)wgt[it * kPairs9 + p0 + j];
-        else
-          key += e;
-        if (h == 0) rec[child * kStage + j] = x;
-        if constexpr (WE)
-          if (h == 1) re[child * kStage + j] = err_f32(e);
       }
       wave_sync();
       if (p0 == 0) loads_done();
