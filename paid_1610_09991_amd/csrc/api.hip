@@ -57,6 +57,8 @@ struct paid_ctx {
   DevBuf entries, tab, zeta, svals, ctr, qv, ffc, pcoef;
   DevBuf code, key, Q, E;
   DevBuf slot_i, slot_d, sel, selc, sctr, dv, de, dep, itau, errp, stl, counters, outs, errs;
+  DevBuf con[7];  // host arrays of a contraction (bubbles, three couplings, three results)
+  DevBuf flow;    // a flow's couplings, bubbles and right-hand side
   // learned seeding
   DevBuf seedw, sfeat, sfold, sy, pyr, seedd, ifill, labtmp, rowsz, rperm, movei, upart;
   bool seed_on = false;
@@ -506,8 +508,10 @@ void paid_destroy(paid_ctx *c) {
                     &c->errp,    &c->stl,  &c->counters, &c->outs, &c->errs,
                     &c->seedw,   &c->sfeat, &c->sfold, &c->sy,  &c->pyr,
                     &c->seedd,   &c->ifill, &c->labtmp, &c->pairw, &c->born, &c->lcodes,
-                    &c->lq,      &c->pcoef, &c->rowsz, &c->rperm, &c->movei, &c->upart};
+                    &c->lq,      &c->pcoef, &c->rowsz, &c->rperm, &c->movei, &c->upart,
+                    &c->flow};
   for (DevBuf *b : bufs) b->release();
+  for (DevBuf &b : c->con) b.release();
   if (c->host_counters) (void)hipHostFree(c->host_counters);
   for (hipEvent_t ev : {c->ev0, c->ev1, c->ev2, c->ev3})
     if (ev) (void)hipEventDestroy(ev);
@@ -1371,7 +1375,8 @@ int paid_contract(paid_ctx *c, int n_l, int M, const double *chi, const double *
   if (!chi || !VP || !VC || !VD || !dP || !dC || !dD) return fail(c, PAID_EINVAL, "NULL array");
   HIPCHK(c, hipSetDevice(c->cfg.device));
   const size_t n = (size_t)n_l * M * M;
-  DevBuf tc, tp, tcc, td, o1, o2, o3;
+  DevBuf &tc = c->con[0], &tp = c->con[1], &tcc = c->con[2], &td = c->con[3];
+  DevBuf &o1 = c->con[4], &o2 = c->con[5], &o3 = c->con[6];
   const double *dchi, *dvp, *dvc, *dvd;
   double *rp, *rc, *rd;
   int rc_;
@@ -1422,14 +1427,19 @@ int paid_flow(paid_ctx *c, const paid_params *base, const double *q, int n_q, co
     if (is_device_ptr(a)) return fail(c, PAID_EINVAL, "the flow takes couplings and state in host memory");
   const int M = n_ff;
   const size_t nm = (size_t)n_q * M * M, ny = 3 * nm;  // state: P, C, D
-  std::vector<double> y(ny), V(ny);
+  std::vector<double> y(ny);
   memcpy(y.data(), P, sizeof(double) * nm);
   memcpy(y.data() + nm, C, sizeof(double) * nm);
   memcpy(y.data() + 2 * nm, D, sizeof(double) * nm);
-  memcpy(V.data(), VP, sizeof(double) * nm);
-  memcpy(V.data() + nm, VC, sizeof(double) * nm);
-  memcpy(V.data() + 2 * nm, VD, sizeof(double) * nm);
-  std::vector<double> chi(2 * nm), rhs(ny);
+  // The couplings are on the device for the whole flow; the bubbles stay there
+  // between the integration and the contraction, so that an evaluation of the
+  // right-hand side copies nothing but its result.
+  HIPCHK(c, hipSetDevice(c->cfg.device));
+  HIPCHK(c, c->flow.ensure(sizeof(double) * 8 * nm));
+  double *dV = c->flow.as<double>(), *dchi = dV + ny, *drhs = dchi + 2 * nm;
+  HIPCHK(c, hipMemcpyAsync(dV, VP, sizeof(double) * nm, hipMemcpyHostToDevice, c->stream));
+  HIPCHK(c, hipMemcpyAsync(dV + nm, VC, sizeof(double) * nm, hipMemcpyHostToDevice, c->stream));
+  HIPCHK(c, hipMemcpyAsync(dV + 2 * nm, VD, sizeof(double) * nm, hipMemcpyHostToDevice, c->stream));
   paid_flow_stats st;
   memset(&st, 0, sizeof st);
   // f(s) = dy/d(ln Omega) = Omega dy/dOmega at Omega = e^s (independent of y)
@@ -1438,15 +1448,16 @@ int paid_flow(paid_ctx *c, const paid_params *base, const double *q, int n_q, co
     p.Omega = exp(s);
     paid_stats is;
     int rc = paid_integrate(c, &p, 1, q, n_q, ff, n_ff, ff_L, PAID_PP | PAID_PH, o.rtol_int, 0.0,
-                            chi.data(), nullptr, &is);
+                            dchi, nullptr, &is);
     if (rc == PAID_ENOCONV)
       return fail(c, PAID_ENOCONV, "flow: the integration at Omega = %g hit max_regions", p.Omega);
     if (rc != PAID_OK) return rc;
     st.evaluations++;
     st.kernel_evals += is.kernel_evals;
-    rc = paid_contract(c, n_q, M, chi.data(), V.data(), V.data() + nm, V.data() + 2 * nm, out,
-                       out + nm, out + 2 * nm);
-    if (rc != PAID_OK) return rc;
+    HIPCHK(c, launch_contract(n_q, M, dchi, dV, dV + nm, dV + 2 * nm, drhs, drhs + nm, drhs + 2 * nm,
+                              c->stream));
+    HIPCHK(c, hipMemcpyAsync(out, drhs, sizeof(double) * ny, hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
     for (size_t i = 0; i < ny; ++i) out[i] *= p.Omega;
     return PAID_OK;
   };
