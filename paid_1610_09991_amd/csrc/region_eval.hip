@@ -1087,6 +1087,9 @@ constexpr int kCol = 7;
 constexpr int kYDoubles = kYRows + 4 * kItems * kCol;
 // records are staged in LDS, kStage values of each of the wave's 32 children at
 // a time (an odd stride: the children's lanes write to distinct banks)
+// a wide group holds its vectors behind its 18 node rows and behind the columns
+constexpr int kWideOwn = 64, kWideSend = 512;
+static_assert(kWideOwn >= 2 * kYBlock && kWideOwn + 200 <= kYRows && kWideSend >= kYDoubles, "wide groups' vectors");
 constexpr int kChildren = 4 * kItems;
 constexpr int kStage = kProd;
 static_assert(kStage & 1, "bank spread of the staged records");
@@ -1204,12 +1207,26 @@ struct LpcShare {
   int row, lo, hi;           // the next range and its row (mode 1)
   int rest, end;             // what is left of the chunk behind the range
   int base, total;           // the XCD's items behind the first chunks
+  int group;                 // items per group
 };
 
+// Items per group: eight, or one where that leaves no wave a second group.  A
+// round of few items is bound by the latency of one group, 41 nodes one after
+// the other in each lane; a wide group's lanes take one column each, 14 nodes
+// (30k -> 13k clocks of a launch of 57k).  With twice as many items the eight
+// lane groups of a common group are the better use of the wave: five form
+// factors on 8x8 momenta take 666 us with this rule, 684 with twice and 742
+// with four times as many items, 700 without wide groups.  (One momentum: 434
+// -> 381 us.)
+__device__ inline int group_items(long total) {
+  return total <= (long)gridDim.x * (blockDim.x >> 6) ? 1 : lpc::kItems;
+}
+
 // chunk sizes: half of an even share of the XCD's items left, in whole groups
-__device__ inline int share_items(int left) {
-  const int half = left / (2 * (((int)gridDim.x + kXcds - 1) / kXcds));  // (its workgroups, or one more)
-  return max(lpc::kItems, half / lpc::kItems * lpc::kItems);
+__device__ inline int share_items(int left, int group) {
+  const int wgs = ((int)gridDim.x + kXcds - 1) / kXcds;  // (the XCD's workgroups, or one more)
+  if (group == 1) return max(1, (left + wgs - 1) / wgs);
+  return max(group, left / (2 * wgs) / group * group);
 }
 
 // the next range of this workgroup (one wave): of the present chunk, or of a
@@ -1222,7 +1239,7 @@ __device__ inline void next_range(const Problem &P, LpcShare &sh, int loaded) {
       int *count = P.xcount + (blockIdx.x % min(kXcds, (int)gridDim.x)) * kXcdStride;
       const int seen = sh.base + __hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       if (seen < sh.total) {
-        const int c = share_items(sh.total - seen);
+        const int c = share_items(sh.total - seen, sh.group);
         i0 = min(sh.base + atomicAdd(count, c), sh.total);
         i1 = min(i0 + c, sh.total);
       }
@@ -1250,7 +1267,7 @@ __device__ inline void next_range(const Problem &P, LpcShare &sh, int loaded) {
   }
 }
 
-// a group of items for this wave: its first item (end: the range's end), or -1
+// a group of items for this wave: its first item (end: the one behind its last), or -1
 // when the workgroup needs another table or has no items left
 __device__ inline int take_group(const Problem &P, LpcShare &sh, int loaded, int &end) {
   const int lane = lane_id();
@@ -1259,12 +1276,15 @@ __device__ inline int take_group(const Problem &P, LpcShare &sh, int loaded, int
     int mode = 0;
     if (lane == 0) {
       r = __hip_atomic_load(&sh.range, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      if ((unsigned)r < (unsigned)(r >> 32)) r = atomicAdd(&sh.range, (unsigned long long)lpc::kItems);
+      if ((unsigned)r < (unsigned)(r >> 32)) r = atomicAdd(&sh.range, (unsigned long long)sh.group);
       mode = __hip_atomic_load(&sh.mode, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
     const int g = __builtin_amdgcn_readfirstlane((int)(unsigned)r);
     end = __builtin_amdgcn_readfirstlane((int)(r >> 32));
-    if (g < end) return g;
+    if (g < end) {
+      end = min(end, g + __builtin_amdgcn_readfirstlane(sh.group));
+      return g;
+    }
     if (__builtin_amdgcn_readfirstlane(mode)) return -1;
     int mine = 0;
     if (lane == 0) mine = atomicCAS(&sh.lock, 0, 1) == 0;
@@ -1333,7 +1353,7 @@ __device__ inline int stage_row(int e, int n, float inv_n) {
 // whose leaves hold the product integrals.
 template <bool BUB, bool WE, bool WW, bool GEN>
 __device__ void lpc_group(const Problem &P, const LpcRow &R, const double *tab, const double *del,
-                          const double *co, double *Yw, LpcShare &share, int loaded, int &g0, int &gend,
+                          const double *co, double *Yw, LpcShare &share, int loaded, bool wide, int &g0, int &gend,
                           LpcItem &cur) {
   using namespace lpc;
   Entry E;
@@ -1387,14 +1407,14 @@ __device__ void lpc_group(const Problem &P, const LpcRow &R, const double *tab, 
       }
       // rows of both child rows of every item
 #pragma unroll 1
-      for (int t0 = 0; t0 < kItems * 2 * kNF; t0 += 64) {
+      for (int t0 = 0; t0 < (wide ? 1 : kItems * 2 * kNF); t0 += 64) {
         // every lane takes part in the exchanges; lanes past the last row idle after them
         const int t = t0 + lane, ti = min(t / (2 * kNF), kItems - 1);
         const int rem = t - ti * (2 * kNF), tcy = min(rem / kNF, 1), b = rem - tcy * kNF;
         const int src = 8 * ti + 4 * tcy + 1;  // lane 1 of child (0, tcy) of item ti
         const double cm = __shfl(c1, src, 64), sm = __shfl(s1, src, 64);
         const int td = __shfl(d, 8 * ti, 64);
-        if (t >= kItems * 2 * kNF) continue;
+        if (t >= (wide ? 2 * kNF : kItems * 2 * kNF)) continue;
         const int bb = b < 5 ? b : 8 - b;
         const double cd = del[td * 10 + bb];
         const double sd = b < 5 ? del[td * 10 + 5 + bb] : -del[td * 10 + 5 + bb];
@@ -1407,7 +1427,7 @@ __device__ void lpc_group(const Problem &P, const LpcRow &R, const double *tab, 
   wave_sync();
 
   // ---- the integrand and the sums
-  const double *Yc = Yw + (it * 2 + cy) * kYBlock;
+  const double *Yc = Yw + ((wide ? 0 : it) * 2 + cy) * kYBlock;
   const unsigned sgn_ch = chl ? 0u : 0x80000000u;  // pp takes -b
   double I[5][5];
 #pragma unroll
@@ -1420,8 +1440,8 @@ __device__ void lpc_group(const Problem &P, const LpcRow &R, const double *tab, 
     const int aa = a < 5 ? a : 8 - a;
     const double cd = del[d * 10 + aa], sd = a < 5 ? del[d * 10 + 5 + aa] : -del[d * 10 + 5 + aa];
     const double cxm = col[0], sxm = col[1];
-    cxv = cxm * cd - sxm * sd;
-    sx = sxm * cd + cxm * sd;
+    cxv = fma(cxm, cd, -(sxm * sd));  // (the same rounding wherever it is used)
+    sx = fma(sxm, cd, cxm * sd);
   };
   // y-sums of column a over N nodes, of {1, c, s, c^2, c s} (c, s the node's
   // cosine and sine in y; the sums of phi follow from them, linearly, at the
@@ -1517,13 +1537,12 @@ __device__ void lpc_group(const Problem &P, const LpcRow &R, const double *tab, 
 #pragma unroll
       for (int k = 0; k < 5; ++k) I[j][k] = fma(px[j], dk[k], I[j][k]);
   };
-  // one step: this lane's column a and the partner's; each lane forms the
-  // y-sum vector the partner needs from its own column and swaps it
-  auto step = [&](int a, auto count, double wf, double wc) {
-    constexpr bool split = decltype(count)::value < kNF;
+  // the y-sum vectors of this lane's column a: its own (dk) and the one that
+  // the partner needs (sk)
+  auto sums = [&](int a, auto count, double wf, double wc, double (&dk)[5], double (&sk)[5]) {
     double H2[5], H1[5];
     column(a, count, H2, H1);
-    if (split) {  // both lanes hold part of the same column: add the parts
+    if (decltype(count)::value < kNF) {  // both lanes hold part of the same column: add the parts
 #pragma unroll
       for (int k = 0; k < 5; ++k) {
         H2[k] += lpc::swap_h(H2[k]);
@@ -1531,32 +1550,82 @@ __device__ void lpc_group(const Problem &P, const LpcRow &R, const double *tab, 
       }
     }
     const double wown = h ? wc : 0.0, wsend = h ? 0.0 : wc;
-    double dk[5], sk[5], px[5];
 #pragma unroll
     for (int k = 0; k < 5; ++k) {
       dk[k] = fma(wf, H2[k], -wown * H1[k]);
       sk[k] = fma(wf, H2[k], -wsend * H1[k]);
     }
-    column_basis(a, px);
-    xsum(dk, px);
-    if (!split) {
-#pragma unroll
-      for (int k = 0; k < 5; ++k) sk[k] = lpc::swap_h(sk[k]);
-#pragma unroll
-      for (int j = 1; j < 5; ++j) px[j] = lpc::swap_h(px[j]);
-      xsum(sk, px);
-    }
   };
 
   if (!wave_skip) {
-    // columns s (lane 0) and 8 - s (lane 1), s = 0..3: the CC weights are
-    // symmetric, so both columns of a step carry the same weights
+    // Columns s (lane 0) and 8 - s (lane 1), s = 0..3: the CC weights are
+    // symmetric, so both columns of a step carry the same weights.  In a wide
+    // group, whose one item every lane group repeats, lane group s takes step s
+    // and its vectors go to LDS.
+    double *Vd = Yw + kWideOwn, *Vs = Yw + kWideSend, *V4 = Vs + 160, *T = Vd;
 #pragma unroll 1
-    for (int st = 0; st < 4; ++st)
-      step(h ? 8 - st : st, std::integral_constant<int, kNF>{}, c_rule.w2[st],
-           (st & 1) ? 0.0 : c_rule.w1[st >> 1]);
-    // column 4: rows 0-4 on lane 0, rows 8-5 on lane 1
-    step(4, std::integral_constant<int, 5>{}, c_rule.w2[4], c_rule.w1[2]);
+    for (int st = 0; st < (wide ? 1 : 4); ++st) {
+      const int u = wide ? min(it, 3) : st, a = h ? 8 - u : u;
+      double dk[5], sk[5], px[5];
+      sums(a, std::integral_constant<int, kNF>{}, del[kDelWeights + u], del[kDelWeights + kNF + u], dk, sk);
+      if (wide) {
+        if (it < 4)
+#pragma unroll
+          for (int k = 0; k < 5; ++k) {
+            Vd[((lane & 7) * 4 + it) * 5 + k] = dk[k];
+            Vs[((lane & 7) * 4 + it) * 5 + k] = sk[k];
+          }
+      } else {
+        column_basis(a, px);
+        xsum(dk, px);
+#pragma unroll
+        for (int k = 0; k < 5; ++k) sk[k] = lpc::swap_h(sk[k]);
+#pragma unroll
+        for (int j = 1; j < 5; ++j) px[j] = lpc::swap_h(px[j]);
+        xsum(sk, px);
+      }
+    }
+    {  // column 4: rows 0-4 on lane 0, rows 8-5 on lane 1
+      double dk[5], sk[5], px[5];
+      sums(4, std::integral_constant<int, 5>{}, c_rule.w2[4], c_rule.w1[2], dk, sk);
+      if (wide) {
+        if (it == 0)
+#pragma unroll
+          for (int k = 0; k < 5; ++k) V4[(lane & 7) * 5 + k] = dk[k];
+      } else {
+        column_basis(4, px);
+        xsum(dk, px);
+      }
+    }
+    if (wide) {
+      // lane group k adds up the sums with index k, in the order of the steps
+      const int k = min(it, 4), q = lane & 7;
+      wave_sync();
+      double acc[5], px[5];
+#pragma unroll
+      for (int j = 0; j < 5; ++j) acc[j] = 0.0;
+      auto more = [&](double v, int a) {
+        column_basis(a, px);
+        acc[0] += v;
+#pragma unroll
+        for (int j = 1; j < 5; ++j) acc[j] = fma(px[j], v, acc[j]);
+      };
+#pragma unroll 1
+      for (int st = 0; st < 4; ++st) {
+        more(Vd[(q * 4 + st) * 5 + k], h ? 8 - st : st);
+        more(Vs[((q ^ 1) * 4 + st) * 5 + k], h ? st : 8 - st);
+      }
+      more(V4[q * 5 + k], 4);
+      wave_sync();
+      if (it < 5)
+#pragma unroll
+        for (int j = 0; j < 5; ++j) T[q * 25 + 5 * j + k] = acc[j];
+      wave_sync();
+#pragma unroll
+      for (int j = 0; j < 5; ++j)
+#pragma unroll
+        for (int k2 = 0; k2 < 5; ++k2) I[j][k2] = T[q * 25 + 5 * j + k2];
+    }
     // from {1, c, s, c^2, c s} to phi in y
 #pragma unroll
     for (int j = 0; j < 5; ++j) {
@@ -1804,6 +1873,20 @@ __device__ void lpc_group(const Problem &P, const LpcRow &R, const double *tab, 
   wave_sync();  // the next group's node rows take the records' place
 }
 
+// n doubles of a table to LDS by nt threads, t of them this one; four loads in
+// flight each
+__device__ inline void copy_table(double *dst, const double *src, int n, int t, int nt) {
+  int i = t;
+  for (; i + 3 * nt < n; i += 4 * nt) {
+    const double a = src[i], b = src[i + nt], c = src[i + 2 * nt], d = src[i + 3 * nt];
+    dst[i] = a;
+    dst[i + nt] = b;
+    dst[i + 2 * nt] = c;
+    dst[i + 3 * nt] = d;
+  }
+  for (; i < n; i += nt) dst[i] = src[i];
+}
+
 // The grid is the workgroups resident at once; a workgroup stages a parameter
 // row's tables and its waves take groups of 8 items (LpcShare).
 template <bool BUB, bool WE, bool WW, bool GEN>
@@ -1813,19 +1896,22 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(3))) k
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   double *Yw = tabl + P.tab_doubles + wv * P.lds_wave_doubles;
   __shared__ LpcShare share;
+  // (with one parameter row its table is staged before the items are known)
+  bool staged = P.one_row && blockDim.x > 64;
   {  // the first chunk, by index in the XCD's items [x0, x1)
     // (a grid of fewer workgroups than XCDs: a share per workgroup)
     const int nx = min(kXcds, (int)gridDim.x), x = blockIdx.x % nx;
     const int nb = ((int)gridDim.x - x + nx - 1) / nx;  // the XCD's workgroups
     const long total = P.counters[2];
     const int x0 = (int)(total * x / nx), x1 = (int)(total * (x + 1) / nx);
-    const int c = share_items(x1 - x0);
+    const int group = group_items(total), c = share_items(x1 - x0, group);
     const int i0 = (int)min((long)x0 + (long)(blockIdx.x / nx) * c, (long)x1), i1 = min(i0 + c, x1);
     if (i0 >= i1) return;  // uniform in the workgroup
-    if (threadIdx.x < 64) {
+    if (wv == 0) {
       if (threadIdx.x == 0) {
         share.base = (int)min((long)x0 + (long)nb * c, (long)x1);
         share.total = x1;
+        share.group = group;
         share.lock = 0;
         share.mode = 0;
         share.range = 0;
@@ -1833,7 +1919,10 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(3))) k
         share.end = i1;
       }
       wave_sync();
-      next_range(P, share, -1);
+      next_range(P, share, staged ? 0 : -1);
+    } else if (staged) {  // the only row's table, while the first wave finds the range
+      const Entry E0 = P.entries[0];
+      copy_table(tabl, P.tab + E0.tab_off, tab_doubles(E0), threadIdx.x - 64, blockDim.x - 64);
     }
   }
   for (int i = threadIdx.x; i < kDelDoubles; i += blockDim.x) del[i] = rule_value(i);
@@ -1842,29 +1931,31 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(3))) k
 #pragma unroll 1
   for (;;) {
     __syncthreads();  // every wave is done with the previous row's table
-    if (share.mode == 2) break;
-    const int e = __builtin_amdgcn_readfirstlane(share.row);
+    if (!staged && share.mode == 2) break;
+    const int e = staged ? 0 : __builtin_amdgcn_readfirstlane(share.row);
     const Entry E0 = P.entries[e];
-    const double *src = P.tab + E0.tab_off;
-    const int nt = tab_doubles(E0);
-    for (int i = threadIdx.x; i < nt; i += blockDim.x) tabl[i] = src[i];
-    __syncthreads();  // (and has read share.mode)
-    if (threadIdx.x == 0) {
-      atomicExch(&share.range, ((unsigned long long)share.hi << 32) | (unsigned)share.lo);
-      atomicExch(&share.mode, 0);
+    if (!staged) {
+      copy_table(tabl, P.tab + E0.tab_off, tab_doubles(E0), threadIdx.x, blockDim.x);
+      __syncthreads();  // (and has read share.mode)
+      if (threadIdx.x == 0) {
+        atomicExch(&share.range, ((unsigned long long)share.hi << 32) | (unsigned)share.lo);
+        atomicExch(&share.mode, 0);
+      }
+      __syncthreads();
     }
-    __syncthreads();
+    staged = false;
     LpcRow R;
     R.mt2 = wave_uniform(-2.0 * E0.t * E0.inv_w);
     R.mtp4 = wave_uniform(-4.0 * E0.tp * E0.inv_w);
     R.mmu = wave_uniform(-E0.mu * E0.inv_w);
     R.J = __builtin_amdgcn_readfirstlane(E0.J);
     R.JV = __builtin_amdgcn_readfirstlane(E0.JV);
+    const bool wide = __builtin_amdgcn_readfirstlane(share.group) == 1;
     int gend, g = take_group(P, share, e, gend);
     if (g < 0) continue;
     LpcItem cur = lpc_item(P, g, min(g + (lane_id() >> 3), gend - 1));
 #pragma unroll 1
-    do lpc_group<BUB, WE, WW, GEN>(kernarg_problem(P), R, tabl, del, co, Yw, share, e, g, gend, cur);
+    do lpc_group<BUB, WE, WW, GEN>(kernarg_problem(P), R, tabl, del, co, Yw, share, e, wide, g, gend, cur);
     while (g >= 0);
   }
 }

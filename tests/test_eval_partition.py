@@ -71,6 +71,31 @@ def test_results_do_not_depend_on_the_number_of_workgroups(layout):
         assert np.array_equal(out, ref[0]) and st["regions"] == ref[1]
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("err_mode,err", [(0, False), (0, True), (1, False)])
+@pytest.mark.parametrize("basis", ["box0", "box1", "five", "mixed"])
+def test_groups_of_one_item_hold_the_same_values(basis, err_mode, err):
+    """a round of at most as many items as waves is taken in groups of one item,
+    otherwise of eight: the same sums in the same order.  With seven times the
+    workgroups some round (each has about four times the items of the one
+    before) is of the one kind here and of the other there."""
+    import paid_1610_09991_amd as P
+    if basis == "mixed":
+        ff, L = np.linalg.qr(np.random.default_rng(5).normal(size=(9, 9)))[0][:4].copy(), 1
+    else:
+        ff, L = (W.ff5(), 1) if basis == "five" else (W.ff_box(int(basis[-1])), int(basis[-1]))
+    p = [[1.0, -0.25, -0.95, 0.03, 0.1]]
+    for q in (W.q_grid(16)[37:38], W.q_grid(16)[::29]):
+        got = []
+        for wg in (1, 7):
+            with P.Context(max_regions=1 << 18, pool_gib=16, eval_wg_per_cu=wg, err_mode=err_mode) as c:
+                out, e, st, rc = c.integrate(p, q, ff, L, rtol=1e-6, err=err)
+            assert rc == P.OK
+            got.append((out, e, st["regions"]))
+        assert np.array_equal(got[0][0], got[1][0]) and got[0][2] == got[1][2]
+        assert not err or np.array_equal(got[0][1], got[1][1])
+
+
 # ------------------------------------------------------------------ slots of items
 def wave_slot(woff, W, g):
     lo, hi = 0, W
