@@ -80,7 +80,7 @@ struct paid_ctx {
   int max_tab = 1, max_close = 1;  // doubles of the largest tables of the last build, and of their close rows
   int lds_limit = 0;             // LDS bytes per workgroup (device attribute)
   float *noalloc = nullptr;      // this device's fixed working memory (paid_mlp_loss_grad_noalloc)
-  // profile: around the evaluation launch of the two rounds in flight
+  // profile: around the evaluation launches of a round and the one before
   hipEvent_t ev0 = nullptr, ev1 = nullptr, ev2 = nullptr, ev3 = nullptr;
 };
 

@@ -1,8 +1,12 @@
 // region_eval.hip -- the hot kernel: evaluation of rectangles with the nested
 // Clenshaw-Curtis pair (Sec. 3) for all form-factor pairs at once.
 //
-// One wavefront owns one work item: a parent rectangle and its four children
-// (Alg. 2: split into 4, evaluate Q_N and Q_2N on each).  The children share
+// Two kernels compute the same rule sums.  k_children_lpc (second half of the
+// file) serves form factors over the 9-function box in the separable FP64 form
+// over the full zone; k_children everything else: the 25-function box, the dense
+// Gram, the half-zone mode and the Gaussian test integrand.  In k_children one
+// wavefront owns one work item: a parent rectangle and its four children (Alg.
+// 2: split into 4, evaluate Q_N and Q_2N on each).  The children share
 // 17 x 17 node coordinates, so the integrand g is evaluated 289 times instead
 // of 324.  Per child the projection onto the box basis U[node][m] is the
 // weighted Gram contraction
@@ -78,15 +82,18 @@ struct WaveLds {
     double h2[2][kNX][NP];         // y-sums with the fine weights, per child row
     double u[2][kNX][NB];          // box harmonics per axis (dense Gram)
   };
-  double cq[MU], ce[MU];           // one child's Q_2N and E over form-factor pairs
+  // one child's Q_2N and E over form-factor pairs: not for the box basis itself
+  // in the separable form, whose pairs go straight to memory (the root's too
+  // are staged)
+  double cq[MU], ce[MU];
   // general form-factor sets only (dropped from the allocation otherwise)
   double tq[MB * MB], ts[MB * MB], tr[MB * MB];
 };
 
 template <int L>
-constexpr size_t wave_lds_doubles(bool identity) {
-  return (sizeof(WaveLds<L>) - (identity ? 3 * sizeof(double) * Dims<L>::MB * Dims<L>::MB : 0)) /
-         sizeof(double);
+constexpr size_t wave_lds_doubles(bool identity, bool direct = false) {
+  return sizeof(WaveLds<L>) / sizeof(double) - (identity ? 3 * Dims<L>::MB * Dims<L>::MB : 0) -
+         (identity && direct ? 2 * Dims<L>::MU : 0);
 }
 
 // wave-local synchronisation for LDS traffic between lanes of one wave
@@ -261,6 +268,27 @@ __device__ void sep_xsums_all(WaveLds<L> &S) {
   wave_sync();
 }
 
+// x-sums of one child
+template <int L>
+__device__ void sep_xsums(WaveLds<L> &S, int cx, int cy) {
+  constexpr int NP = Dims<L>::NP;
+  const int lane = lane_id();
+  for (int idx = lane; idx < NP * NP; idx += 64) {
+    int j = idx / NP, k = idx - j * NP;
+    double s2 = 0.0, s1 = 0.0;
+#pragma unroll
+    for (int a = 0; a < kNF; ++a) {
+      int x = 8 * cx + a;
+      double pj = S.pp[0][x][j];
+      s2 = fma(c_rule.w2[a] * pj, S.h2[cy][x][k], s2);
+      if (!(a & 1)) s1 = fma(c_rule.w1[a >> 1] * pj, S.h1[cy][x >> 1][k], s1);
+    }
+    S.g2[idx] = s2;
+    S.g1[idx] = s1;
+  }
+  wave_sync();
+}
+
 template <int L>
 __device__ void sep_stage2(WaveLds<L> &S, const Problem &P, const int *pidmap, const int *podd,
                            int cx, int cy, double fa, bool xsums_done) {
@@ -276,20 +304,7 @@ __device__ void sep_stage2(WaveLds<L> &S, const Problem &P, const int *pidmap, c
     }
   }
   if (!done) {
-    for (int idx = lane; idx < NP * NP; idx += 64) {
-      int j = idx / NP, k = idx - j * NP;
-      double s2 = 0.0, s1 = 0.0;
-#pragma unroll
-      for (int a = 0; a < kNF; ++a) {
-        int x = 8 * cx + a;
-        double pj = S.pp[0][x][j];
-        s2 = fma(c_rule.w2[a] * pj, S.h2[cy][x][k], s2);
-        if (!(a & 1)) s1 = fma(c_rule.w1[a >> 1] * pj, S.h1[cy][x >> 1][k], s1);
-      }
-      S.g2[idx] = s2;
-      S.g1[idx] = s1;
-    }
-    wave_sync();
+    sep_xsums<L>(S, cx, cy);
   }
   if (P.ff_identity) {
     for (int pid = lane; pid < MU; pid += 64) {
@@ -853,11 +868,20 @@ __device__ void do_item(WaveLds<L> &S, const Problem &P, const int *pidmap, cons
       wave_sync();
       continue;
     }
-    if constexpr (GRAM == kSep && kXsumsAll<L>) {
+    if constexpr (GRAM == kSep) {
       if (P.ff_identity) {
-        // box-basis pairs straight from the x-sums into the child's record
-        // and the parent's delta, without staging them in LDS
-        const double *G2 = S.g2b[ch], *G1 = S.g1b[ch];
+        // Box-basis pairs straight from the x-sums into the child's record and
+        // the parent's delta.  Staged in LDS, the 325 pairs of the 25-function
+        // box took 5 KB of a wave's 19, and six waves a CU instead of ten.
+        const double *G2, *G1;
+        if constexpr (kXsumsAll<L>) {
+          G2 = S.g2b[ch];
+          G1 = S.g1b[ch];
+        } else {
+          sep_xsums<L>(S, cx, cy);
+          G2 = S.g2;
+          G1 = S.g1;
+        }
         const long base = slot_base(P, s) + ri;
         double part = 0.0;
 #pragma unroll
@@ -997,7 +1021,7 @@ __device__ inline Chunk next_chunk(const Problem &P, int unit, int *sh) {
 // runs through its items on its own.  The slot of an item is found by a
 // search only when the wave's items leave the current slot's range.
 template <int L, int GRAM>
-__global__ void __launch_bounds__(256) k_children(Problem P) {
+__global__ void __launch_bounds__(GRAM == kSep ? 512 : 256) k_children(Problem P) {
   extern __shared__ double lds_raw[];
   __shared__ int pidmap[Dims<L>::MU], podd[Dims<L>::MU];
   double *tabl = lds_raw;
@@ -1064,15 +1088,21 @@ __global__ void __launch_bounds__(256) k_children(Problem P) {
 // wave holds 8 work items (parents); lane 8 it + 2 ch + h evaluates child ch of
 // item it together with its partner lane (h = 0, 1).  Every pair of form
 // factors of a rectangle is a combination of the 25 product integrals I_jk =
-// int g phi_j(x) phi_k(y).  Lane h = 0 accumulates I for the fine rule (Q_2N); lane h = 1 accumulates the same sums with the weight
-// difference of the two rules (E = Q_2N - Q_N, the error estimate), so the
-// key of the child (sum over pairs of |E|) needs no lanes but its own.
+// int g phi_j(x) phi_k(y).  Lane h = 0 accumulates I for the fine rule (Q_2N);
+// lane h = 1 accumulates the same sums with the weight difference of the two
+// rules (E = Q_2N - Q_N, the error estimate), so the key of the child (sum over
+// pairs of |E|) needs no lanes but its own.
 // The two lanes of a child share its 81 nodes column by column: lane 0
 // takes columns 0-3 and rows 0-4 of column 4, lane 1 columns 8-5 and rows
 // 5-8 of column 4; after each column the partners swap their y-sums so
 // that each adds both columns to its x-sums.  Nodes on the edges shared by
 // neighbouring children are evaluated once per child (324 evaluations for
 // the 289 distinct nodes of a parent).
+// What bounds it: LDS bandwidth and the latency of a node's LDS round trip (two
+// table rows of nine doubles and the row's cosine and sine), with three waves
+// per SIMD to cover it.  Nine form factors at one scale on 24 x 24 momenta: 1.8
+// ns a stored parent, with its mirror image 0.9 ns (2.8 ns with rows of degree
+// 13, 45 pairs a record stored lane by lane, and no mirror images).
 namespace lpc {
 
 constexpr int kItems = 8;              // work items per wave
@@ -1976,19 +2006,29 @@ hipError_t launch_root_t(const Problem &p, hipStream_t s) {
   return hipGetLastError();
 }
 
+// projection/precision mode of a problem: separable FP64, or the dense Gram
+// in the requested precision
+int gram_mode(const Problem &p) { return p.gram == PAID_GRAM_SEPARABLE ? kSep : p.precision; }
+
 // Dynamic LDS of the evaluation kernel: the largest table plus one WaveLds
-// per wave, as many waves (up to 4) as fit in 64 KiB, or one wave in the
-// device's limit when the table is larger.  Returns 0 if not even that fits.
+// per wave, with the waves a workgroup that put the most of them on a CU (up to
+// eight; four where the dense Gram needs the registers).  Returns 0 if not even
+// one fits.
 template <int L>
 size_t eval_lds_t(const Problem &p, int *waves_out, int *wave_doubles_out) {
-  const size_t wave_b = sizeof(double) * wave_lds_doubles<L>(p.ff_identity);
+  const size_t wave_b = sizeof(double) * wave_lds_doubles<L>(p.ff_identity, gram_mode(p) == kSep);
   // fixed: the kernel's static LDS (two int tables over the form-factor pairs)
   const size_t tab_b = sizeof(double) * (size_t)p.close_doubles, fixed = 4096;
-  size_t budget = 65536;
-  if (tab_b + wave_b + fixed > budget) budget = p.lds_limit > 0 ? (size_t)p.lds_limit : 65536;
-  if (tab_b + wave_b + fixed > budget) return 0;
-  int waves = (int)((budget - fixed - tab_b) / wave_b);
-  waves = waves > 4 ? 4 : waves;
+  const size_t limit = p.lds_limit > 0 ? (size_t)p.lds_limit : 65536;
+  int waves = 0, best = 0;
+  for (int w = 1; w <= (gram_mode(p) == kSep ? 8 : 4); ++w) {
+    const int n = (int)(limit / (tab_b + fixed + w * wave_b)) * w;
+    if (n > best || (n == best && n > 0 && w <= 4)) {  // (a table is staged per workgroup)
+      best = n;
+      waves = w;
+    }
+  }
+  if (waves == 0) return 0;
   if (waves_out) *waves_out = waves;
   if (wave_doubles_out) *wave_doubles_out = (int)(wave_b / sizeof(double));
   return tab_b + (size_t)waves * wave_b;
@@ -2078,10 +2118,6 @@ size_t lpc_lds(const Problem &p, int *waves_out) {
 }  // namespace
 
 namespace {
-// projection/precision mode of a problem: separable FP64, or the dense Gram
-// in the requested precision
-int gram_mode(const Problem &p) { return p.gram == PAID_GRAM_SEPARABLE ? kSep : p.precision; }
-
 // the two-lanes-per-child kernel serves form factors over the 9-function box
 // (or its first function) with the separable FP64 projection over the full
 // zone (bubble and unit integrands)
