@@ -134,13 +134,16 @@ __global__ void __launch_bounds__(256) k_contract(int n_l, int M, const double *
 #pragma unroll
   for (int t = 0; t < NT; ++t)
 #pragma unroll
-    for (int kb = 0; kb < 4 * NT; ++kb) {
-      v[t][kb] = 2.0 * a[t][kb] - v[t][kb];
-      a[t][kb] = -a[t][kb];
-    }
+    for (int kb = 0; kb < 4 * NT; ++kb) v[t][kb] = 2.0 * a[t][kb] - v[t][kb];
   zero<NT>(acc);
   mul<NT>(v, t1, nk, acc);
-  mul<NT>(a, b, nk, acc);
+  // (sums of their own: one running through both products rounds at the larger
+  // of the two all the way)
+  c4 acc2[NT];
+  zero<NT>(acc2);
+  mul<NT>(a, b, nk, acc2);
+#pragma unroll
+  for (int t = 0; t < NT; ++t) acc[t] -= acc2[t];
   store<NT>(dD + l * mm2, M, tc, acc, 1.0);
 }
 
