@@ -58,10 +58,14 @@ PEAK_FP64_TFLOPS = 78.6  # MI355X FP64: vector (256 CUs x 4 SIMD x 16 lanes x 2 
 #     x-sums  4 children x NP^2 x 42 (fine 9 x (mul + FMA), coarse 5 x (mul + FMA))
 #     pairs   4 children x MB(MB+1)/2 x 3
 #   dense projection (matrix cores): 4 children x 2 M^2 (81 + 25).
-# This is the method's work in the cheapest form of each step the library
-# uses (the separable projection, the per-column energies); work an
-# implementation adds (shared edge nodes evaluated once per child: 324 node
-# evaluations instead of 289) is not counted.
+# This is a fixed count of the method's work (the separable projection, the
+# per-column energies), the same for every version of the library, so that its
+# rate compares over versions: work an implementation adds (shared edge nodes
+# evaluated once per child: 324 node evaluations instead of 289) is not counted,
+# and what the present kernel saves is not taken off either (chains of degree 8
+# instead of 13, five functions per axis instead of six products: about 23,700
+# for 9 form factors instead of 34,120).  An item is a stored parent; its mirror
+# image is not counted again.
 K_FLOPS_PER_NODE = 72
 COLUMNS_PER_ITEM = 17
 K_FLOPS_PER_COLUMN = 8
@@ -70,8 +74,8 @@ K_FLOPS_PER_COLUMN = 8
 # FETCH_SIZE / WRITE_SIZE counters scaled by a plain copy's readings
 # (profiles/k_children_c2_counters.md); valid only for the kernel they were
 # taken with, identified by this hash of the two files that define it.
-TRAFFIC_BYTES_PER_ITEM = 2471
-TRAFFIC_SOURCES_SHA256 = "72f43a61f2f7d824f78660c0e192a3f483e22e6bb9ae10837f50923c3a6f2734"
+TRAFFIC_BYTES_PER_ITEM = 1490
+TRAFFIC_SOURCES_SHA256 = "6fbda8111e4680fa33073d55f868af18c681f421014982f8cbdd1e0d03b1dc97"
 NODES_PER_ITEM = 289
 
 # Per-workload region budget (max_regions): the smallest power of two that
