@@ -86,13 +86,16 @@ struct Problem {      // everything the round kernels need, passed by value
   int sym;                    // 1: half zone p_y >= 0 with the parity factors of the pairs
   // 1: a leaf stands for itself and its mirror image under p -> -p.  Both
   // bubbles are even (the inversion swaps the two energies, in which K_j is
-  // symmetric), so the tree of a container and every rectangle's values are
-  // mirror images of themselves: Q of a pair of odd joint parity cancels
-  // between the two, any other doubles, and the errors and keys double.  Leaves
-  // with p_y >= 0 are kept and evaluated (the root as its two upper quadrants);
-  // capacities and batch sizes here count them, results and statistics count
-  // both images.
+  // symmetric), so the integrals of a box pair over the two are equal or, where
+  // its joint parity is odd, opposite: Q of an odd pair cancels between them, any
+  // other doubles, and so do the errors and keys of pairs that are even or odd.
+  // A pair of form factors without parity (mixed) has the errors e + o and e - o
+  // on the two, e and o its even and odd parts, and |e + o| + |e - o| is stored.
+  // The images are split together.  Leaves with p_y >= 0 are kept and evaluated
+  // (the root as its two upper quadrants); capacities and batch sizes here count
+  // them, results and statistics count both images.
   int mirror;
+  int mixed;                  // 1: mirror, and some form factor is neither even nor odd
   int eval_layout;            // 0: the fastest evaluation kernel for the basis, 1: one wave per parent
   uint64_t *code;             // [regions], slot s from slot_base(s)
   double *key;                // [regions]

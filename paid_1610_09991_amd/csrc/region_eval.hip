@@ -517,18 +517,28 @@ __device__ void gram_mfma(WaveLds<L> &S, const Problem &P, int nco, int offx, in
   wave_sync();
 }
 
-// General form-factor sets: Q_ff = C Q_box C^T for both Q and E.
+// General form-factor sets: Q_ff = C Q_box C^T for both Q and E.  With mirror
+// images kept together and form factors of no parity, a third pass forms the
+// image's E (odd box pairs with the other sign), and E is the mean magnitude.
 template <int L>
 __device__ void transform_ff(WaveLds<L> &S, const Problem &P) {
-  constexpr int MB = Dims<L>::MB;
-  const int lane = lane_id(), M = P.M;
+  constexpr int MB = Dims<L>::MB, NB = Dims<L>::NB;
+  const int lane = lane_id(), M = P.M, passes = P.mixed ? 3 : 2;
   double *R = S.tr;
-  for (int which = 0; which < 2; ++which) {
+  for (int which = 0; which < passes; ++which) {
     const double *G = which ? S.ts : S.tq;
     for (int idx = lane; idx < MB * M; idx += 64) {  // R[a][q] = sum_b G[a][b] C[q][b]
       int a = idx / M, q = idx - a * M;
       double s = 0.0;
-      for (int b = 0; b < MB; ++b) s = fma(G[a * MB + b], P.ffc[q * MB + b], s);
+      if (which == 2) {
+        const int oa = box_odd<NB>(a);
+        for (int b = 0; b < MB; ++b) {
+          const double g = G[a * MB + b];
+          s = fma(box_odd<NB>(b) == oa ? g : -g, P.ffc[q * MB + b], s);
+        }
+      } else {
+        for (int b = 0; b < MB; ++b) s = fma(G[a * MB + b], P.ffc[q * MB + b], s);
+      }
       R[idx] = s;
     }
     wave_sync();
@@ -539,7 +549,7 @@ __device__ void transform_ff(WaveLds<L> &S, const Problem &P) {
       int q = p + k;
       double s = 0.0;
       for (int a = 0; a < MB; ++a) s = fma(P.ffc[p * MB + a], R[a * M + q], s);
-      dst[pid] = s;
+      dst[pid] = which == 2 ? 0.5 * (fabs(S.ce[pid]) + fabs(s)) : s;
     }
     wave_sync();
   }
@@ -1851,6 +1861,7 @@ __device__ void lpc_group(const Problem &P, const LpcRow &R, const double *tab, 
     // memory each pair of a cold launch waits for its own.
     [[maybe_unused]] float *re = reinterpret_cast<float *>(rec + kChildren * kStage);
     const int ca = min(lane & 31, kProd - 1);
+    const bool mixed = P.mixed;
 #pragma unroll 1
     for (int p0 = 0; p0 < MU; p0 += kStage) {
       const int n = min(kStage, MU - p0);
@@ -1869,11 +1880,12 @@ __device__ void lpc_group(const Problem &P, const LpcRow &R, const double *tab, 
             const int lo = __builtin_amdgcn_readlane(clo, 32 * jj + a);
             const int hi = __builtin_amdgcn_readlane(chi, 32 * jj + a);
             const double c = __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-            double &t = (a & 1) ? u : v;
+            double &t = product_odd(a) ? u : v;
             t = fma(c, I[a / kPhi][a % kPhi], t);
           }
           if (j + jj < n) {  // (an odd last pair)
-            const double x = fx * (v + u), e = fabs(x);
+            // (of a mixed pair the image's error is even minus odd part)
+            const double x = fx * (v + u), e = mixed ? 0.5 * (fabs(x) + fabs(fx * (v - u))) : fabs(x);
             if constexpr (WW)
               key += e * (double)wgt[it * kPairs9 + p0 + j + jj];
             else
