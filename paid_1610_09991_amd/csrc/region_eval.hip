@@ -517,42 +517,40 @@ __device__ void gram_mfma(WaveLds<L> &S, const Problem &P, int nco, int offx, in
   wave_sync();
 }
 
-// General form-factor sets: Q_ff = C Q_box C^T for both Q and E.  With mirror
-// images kept together and form factors of no parity, a third pass forms the
-// image's E (odd box pairs with the other sign), and E is the mean magnitude.
+// General form-factor sets: C G C^T of a box matrix G.  IMAGE: of the mirror
+// image's E (odd box pairs with the other sign), and dst becomes the mean
+// magnitude of the two.
+template <int L, bool IMAGE>
+__device__ inline void transform_pairs(WaveLds<L> &S, const Problem &P, const double *G, double *dst) {
+  constexpr int MB = Dims<L>::MB, NB = Dims<L>::NB;
+  const int lane = lane_id(), M = P.M;
+  double *R = S.tr;
+  for (int idx = lane; idx < MB * M; idx += 64) {  // R[a][q] = sum_b G[a][b] C[q][b]
+    int a = idx / M, q = idx - a * M;
+    double s = 0.0;
+    for (int b = 0; b < MB; ++b) {
+      const double g = G[a * MB + b];
+      s = fma(IMAGE && box_odd<NB>(a) != box_odd<NB>(b) ? -g : g, P.ffc[q * MB + b], s);
+    }
+    R[idx] = s;
+  }
+  wave_sync();
+  for (int pid = lane; pid < P.MU; pid += 64) {
+    int p = 0, k = pid;
+    while (k >= M - p) { k -= M - p; ++p; }
+    int q = p + k;
+    double s = 0.0;
+    for (int a = 0; a < MB; ++a) s = fma(P.ffc[p * MB + a], R[a * M + q], s);
+    dst[pid] = IMAGE ? 0.5 * (fabs(dst[pid]) + fabs(s)) : s;
+  }
+  wave_sync();
+}
+
 template <int L>
 __device__ void transform_ff(WaveLds<L> &S, const Problem &P) {
-  constexpr int MB = Dims<L>::MB, NB = Dims<L>::NB;
-  const int lane = lane_id(), M = P.M, passes = P.mixed ? 3 : 2;
-  double *R = S.tr;
-  for (int which = 0; which < passes; ++which) {
-    const double *G = which ? S.ts : S.tq;
-    for (int idx = lane; idx < MB * M; idx += 64) {  // R[a][q] = sum_b G[a][b] C[q][b]
-      int a = idx / M, q = idx - a * M;
-      double s = 0.0;
-      if (which == 2) {
-        const int oa = box_odd<NB>(a);
-        for (int b = 0; b < MB; ++b) {
-          const double g = G[a * MB + b];
-          s = fma(box_odd<NB>(b) == oa ? g : -g, P.ffc[q * MB + b], s);
-        }
-      } else {
-        for (int b = 0; b < MB; ++b) s = fma(G[a * MB + b], P.ffc[q * MB + b], s);
-      }
-      R[idx] = s;
-    }
-    wave_sync();
-    double *dst = which ? S.ce : S.cq;
-    for (int pid = lane; pid < P.MU; pid += 64) {
-      int p = 0, k = pid;
-      while (k >= M - p) { k -= M - p; ++p; }
-      int q = p + k;
-      double s = 0.0;
-      for (int a = 0; a < MB; ++a) s = fma(P.ffc[p * MB + a], R[a * M + q], s);
-      dst[pid] = which == 2 ? 0.5 * (fabs(S.ce[pid]) + fabs(s)) : s;
-    }
-    wave_sync();
-  }
+  for (int which = 0; which < 2; ++which)
+    transform_pairs<L, false>(S, P, which ? S.ts : S.tq, which ? S.ce : S.cq);
+  if (P.mixed) transform_pairs<L, true>(S, P, S.ts, S.ce);
 }
 
 // a double moved between lanes by a DPP pattern (both halves; VALU, no LDS)
@@ -1390,8 +1388,9 @@ __device__ inline int stage_row(int e, int n, float inv_n) {
 // children's errors only form their keys.  WW: the keys weigh the pairs
 // (per-integral and weighted modes); otherwise they are plain sums.  GEN:
 // general form factors (pairs from P.pcoef); otherwise the box basis itself,
-// whose leaves hold the product integrals.
-template <bool BUB, bool WE, bool WW, bool GEN>
+// whose leaves hold the product integrals.  MIX: P.mixed (a kernel of its own:
+// as a branch of the pairs' loop it cost every general set 1 of 33 us a launch).
+template <bool BUB, bool WE, bool WW, bool GEN, bool MIX>
 __device__ void lpc_group(const Problem &P, const LpcRow &R, const double *tab, const double *del,
                           const double *co, double *Yw, LpcShare &share, int loaded, bool wide, int &g0, int &gend,
                           LpcItem &cur) {
@@ -1861,7 +1860,6 @@ __device__ void lpc_group(const Problem &P, const LpcRow &R, const double *tab, 
     // memory each pair of a cold launch waits for its own.
     [[maybe_unused]] float *re = reinterpret_cast<float *>(rec + kChildren * kStage);
     const int ca = min(lane & 31, kProd - 1);
-    const bool mixed = P.mixed;
 #pragma unroll 1
     for (int p0 = 0; p0 < MU; p0 += kStage) {
       const int n = min(kStage, MU - p0);
@@ -1880,12 +1878,12 @@ __device__ void lpc_group(const Problem &P, const LpcRow &R, const double *tab, 
             const int lo = __builtin_amdgcn_readlane(clo, 32 * jj + a);
             const int hi = __builtin_amdgcn_readlane(chi, 32 * jj + a);
             const double c = __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-            double &t = product_odd(a) ? u : v;
+            double &t = (MIX ? product_odd(a) : (a & 1) != 0) ? u : v;
             t = fma(c, I[a / kPhi][a % kPhi], t);
           }
           if (j + jj < n) {  // (an odd last pair)
-            // (of a mixed pair the image's error is even minus odd part)
-            const double x = fx * (v + u), e = mixed ? 0.5 * (fabs(x) + fabs(fx * (v - u))) : fabs(x);
+            // (MIX: the image's error is the even part minus the odd one)
+            const double x = fx * (v + u), e = MIX ? 0.5 * (fabs(x) + fabs(fx * (v - u))) : fabs(x);
             if constexpr (WW)
               key += e * (double)wgt[it * kPairs9 + p0 + j + jj];
             else
@@ -1931,7 +1929,7 @@ __device__ inline void copy_table(double *dst, const double *src, int n, int t, 
 
 // The grid is the workgroups resident at once; a workgroup stages a parameter
 // row's tables and its waves take groups of 8 items (LpcShare).
-template <bool BUB, bool WE, bool WW, bool GEN>
+template <bool BUB, bool WE, bool WW, bool GEN, bool MIX>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(3))) k_children_lpc(Problem P) {
   extern __shared__ double lds_raw[];
   double *del = lds_raw, *co = lds_raw + kDelDoubles, *tabl = co + (GEN ? (P.MU * kProd + 1) / 2 * 2 : 0);
@@ -1997,7 +1995,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(3))) k
     if (g < 0) continue;
     LpcItem cur = lpc_item(P, g, min(g + (lane_id() >> 3), gend - 1));
 #pragma unroll 1
-    do lpc_group<BUB, WE, WW, GEN>(kernarg_problem(P), R, tabl, del, co, Yw, share, e, wide, g, gend, cur);
+    do lpc_group<BUB, WE, WW, GEN, MIX>(kernarg_problem(P), R, tabl, del, co, Yw, share, e, wide, g, gend, cur);
     while (g >= 0);
   }
 }
@@ -2074,18 +2072,20 @@ int lpc_wave_doubles(const Problem &p) {
 }
 
 // the two-lanes-per-child kernel for the problem's integrand and form factors
-template <bool BUB, bool GEN>
+template <bool BUB, bool GEN, bool MIX>
 const void *lpc_kernel_t(bool we, bool ww) {
-  return we ? (ww ? reinterpret_cast<const void *>(&k_children_lpc<BUB, true, true, GEN>)
-                  : reinterpret_cast<const void *>(&k_children_lpc<BUB, true, false, GEN>))
-            : (ww ? reinterpret_cast<const void *>(&k_children_lpc<BUB, false, true, GEN>)
-                  : reinterpret_cast<const void *>(&k_children_lpc<BUB, false, false, GEN>));
+  return we ? (ww ? reinterpret_cast<const void *>(&k_children_lpc<BUB, true, true, GEN, MIX>)
+                  : reinterpret_cast<const void *>(&k_children_lpc<BUB, true, false, GEN, MIX>))
+            : (ww ? reinterpret_cast<const void *>(&k_children_lpc<BUB, false, true, GEN, MIX>)
+                  : reinterpret_cast<const void *>(&k_children_lpc<BUB, false, false, GEN, MIX>));
 }
-const void *lpc_kernel(const Problem &p) {
-  const bool we = p.E != nullptr, ww = p.err_mode != 0, gen = needs_pair_coefficients(p);
-  if (p.kind <= 1) return gen ? lpc_kernel_t<true, true>(we, ww) : lpc_kernel_t<true, false>(we, ww);
-  return gen ? lpc_kernel_t<false, true>(we, ww) : lpc_kernel_t<false, false>(we, ww);
+template <bool BUB>
+const void *lpc_kernel_b(const Problem &p) {
+  const bool we = p.E != nullptr, ww = p.err_mode != 0;
+  if (!needs_pair_coefficients(p)) return lpc_kernel_t<BUB, false, false>(we, ww);
+  return p.mixed ? lpc_kernel_t<BUB, true, true>(we, ww) : lpc_kernel_t<BUB, true, false>(we, ww);
 }
+const void *lpc_kernel(const Problem &p) { return p.kind <= 1 ? lpc_kernel_b<true>(p) : lpc_kernel_b<false>(p); }
 
 // Dynamic LDS of the two-lanes-per-child kernel: the table and each wave's
 // node rows and records.  The table is staged once per workgroup, so the
