@@ -349,7 +349,9 @@ int paid_seed_train(struct paid_ctx *ctx, const float *x, const float *y, int n,
  *   chi  [n_l][2][M][M]: both channels, pp first (the layout paid_integrate
  *        writes with channels PAID_PP | PAID_PH, n_l = n_params * n_q)
  *   VP, VC, VD, dP, dC, dD  [n_l][M][M] FP64 row-major
- * 1 <= M <= 32, n_l >= 0.  Host or device pointers. */
+ * 1 <= M <= 32, n_l >= 0.  Host or device pointers.  In place: dP, dC and dD
+ * may be the arrays VP, VC and VD themselves; other overlaps of an output with
+ * an input are not allowed. */
 int paid_contract(struct paid_ctx *ctx, int n_l, int M, const double *chi, const double *VP,
                   const double *VC, const double *VD, double *dP, double *dC, double *dD);
 
