@@ -1110,7 +1110,12 @@ int paid_children_eval(paid_ctx *c, const paid_params *p, const double *l, unsig
   P.counters = cnt.as<int>() + 4;
   P.xcount = cnt.as<int>() + 64;
   P.ifill = ifl.as<int>();
-  HIPCHK(c, launch_eval(P, n < 4096 ? n : 4096, c->stream));
+  // The kernel that takes parents in groups: of eight, as a round of many items
+  // does, on as few workgroups as fill them; a single parent in a group of one,
+  // as a round of few items.  Otherwise a workgroup per parent.
+  P.wide_items = 1;
+  const int per_wg = P.products || needs_pair_coefficients(P) ? 64 : 1;
+  HIPCHK(c, launch_eval(P, std::min((n + per_wg - 1) / per_wg, 4096), c->stream));
   std::vector<double> hQ((size_t)cap * MQ), hk(cap);
   HIPCHK(c, hipMemcpyAsync(hQ.data(), Q.p, sizeof(double) * cap * MQ, hipMemcpyDeviceToHost, c->stream));
   HIPCHK(c, hipMemcpyAsync(hk.data(), key.p, sizeof(double) * cap, hipMemcpyDeviceToHost, c->stream));

@@ -80,6 +80,7 @@ struct Problem {      // everything the round kernels need, passed by value
   int *moveq;                 // [W] scratch: the waiting small slots in slot order
   int bmin, bmax;
   int lds_wave_doubles;       // per-wave LDS of the evaluation kernel (set at launch)
+  int wide_items;             // rounds of at most so many items are taken in groups of one (0: set at launch)
   int tab_doubles;            // doubles of the largest parameter row's tables (staged in LDS)
   int close_doubles;          // and of its close rows alone
   int lds_limit;              // bytes of LDS a workgroup may use on the device

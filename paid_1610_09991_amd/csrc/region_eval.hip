@@ -1248,7 +1248,8 @@ struct LpcShare {
   int group;                 // items per group
 };
 
-// Items per group: eight, or one where that leaves no wave a second group.  A
+// Items per group: eight, or one where that leaves no wave a second group
+// (P.wide_items: the waves of the grid).  A
 // round of few items is bound by the latency of one group, 41 nodes one after
 // the other in each lane; a wide group's lanes take one column each, 14 nodes
 // (30k -> 13k clocks of a launch of 57k).  With twice as many items the eight
@@ -1256,9 +1257,7 @@ struct LpcShare {
 // factors on 8x8 momenta take 666 us with this rule, 684 with twice and 742
 // with four times as many items, 700 without wide groups.  (One momentum: 434
 // -> 381 us.)
-__device__ inline int group_items(long total) {
-  return total <= (long)gridDim.x * (blockDim.x >> 6) ? 1 : lpc::kItems;
-}
+__device__ inline int group_items(const Problem &P, long total) { return total <= P.wide_items ? 1 : lpc::kItems; }
 
 // chunk sizes: half of an even share of the XCD's items left, in whole groups
 __device__ inline int share_items(int left, int group) {
@@ -1944,7 +1943,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(3))) k
     const int nb = ((int)gridDim.x - x + nx - 1) / nx;  // the XCD's workgroups
     const long total = P.counters[2];
     const int x0 = (int)(total * x / nx), x1 = (int)(total * (x + 1) / nx);
-    const int group = group_items(total), c = share_items(x1 - x0, group);
+    const int group = group_items(P, total), c = share_items(x1 - x0, group);
     const int i0 = (int)min((long)x0 + (long)(blockIdx.x / nx) * c, (long)x1), i1 = min(i0 + c, x1);
     if (i0 >= i1) return;  // uniform in the workgroup
     if (wv == 0) {
@@ -2212,6 +2211,7 @@ hipError_t launch_eval(const Problem &p, int grid, hipStream_t s) {
     if (sh == 0) return hipErrorInvalidValue;
     Problem q = p;
     q.lds_wave_doubles = lpc_wave_doubles(p);
+    if (q.wide_items == 0) q.wide_items = grid * waves;
     void *args[] = {&q};
     const hipError_t e = hipLaunchKernel(lpc_kernel(p), dim3(grid), dim3(64 * waves), args, sh, s);
     if (e != hipSuccess) return e;
