@@ -27,6 +27,7 @@
 #include <type_traits>
 
 #include "launch.h"
+#include "share.h"
 
 namespace paid {
 
@@ -967,54 +968,28 @@ __device__ inline const Problem &kernarg_problem(const Problem &P) {
 #endif
 }
 
-// The round's work items in chunks: the grid is the workgroups resident at
-// once; each takes a first chunk by its index and then further ones from a
-// counter (P.counters[3], zero at the start of a round) until the items are
-// gone.  A chunk is half of an even share of the items that are left, in
-// whole passes of the workgroup's waves, so chunks shrink towards the end and
-// no workgroup is left with a long one; a round of few items is spread over
-// all workgroups, a pass of one wave (`unit` items) at a time.  Which
-// workgroup evaluates an item changes nothing in its result.  (Sixteen
-// generations of workgroups with ranges shrinking by index, before, paid the
-// start of a workgroup - its table, its search for the first slot - sixteen
-// times a round: 80 us a launch for rounds of 300 items.)
-struct Chunk {
-  int i0, i1;
-};
-__device__ inline int chunk_items(int left, int unit) {
-  const int wg = unit * (int)(blockDim.x >> 6), nb = (int)gridDim.x;
-  const int half = left / (2 * nb);
-  if (half >= wg) return half / wg * wg;
-  const int even = (left + nb - 1) / nb;  // spread what is left
-  return max(unit, min(wg, (even + unit - 1) / unit * unit));
-}
-__device__ inline Chunk first_chunk(const Problem &P, int unit) {
-  const int total = P.counters[2], c = chunk_items(total, unit);
-  Chunk k;
-  k.i0 = (int)min((long)blockIdx.x * c, (long)total);
-  k.i1 = min(k.i0 + c, total);
-  return k;
-}
-// the next chunk, the same in every thread (two workgroup barriers)
-__device__ inline Chunk next_chunk(const Problem &P, int unit, int *sh) {
+// The next chunk (share.h), the same in every thread (two workgroup barriers).
+// A counter rather than sixteen generations of workgroups with ranges shrinking
+// by index: those paid the start of a workgroup - its table, its search for the
+// first slot - sixteen times a round, 80 us a launch for rounds of 300 items.
+__device__ inline Span next_chunk(const Problem &P, int *sh) {
   __syncthreads();  // every wave is done with the last chunk (and with sh)
   if (threadIdx.x == 0) {
-    const int total = P.counters[2], c0 = chunk_items(total, unit);
-    const long base = (long)c0 * gridDim.x;
-    int i0 = total, i1 = total;
+    const int total = P.counters[2], waves = blockDim.x >> 6, grid = gridDim.x;
+    const long base = chunk_base(total, waves, grid);
+    Span k = {total, total};
     if (base < total) {
       const int seen = (int)base + __hip_atomic_load(&P.counters[3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       if (seen < total) {
-        const int c = chunk_items(total - seen, unit);
-        i0 = min((int)base + atomicAdd(&P.counters[3], c), total);
-        i1 = min(i0 + c, total);
+        const int c = chunk_items(total - seen, waves, grid);
+        k = counted_span((int)base, total, atomicAdd(&P.counters[3], c), c);
       }
     }
-    sh[0] = i0;
-    sh[1] = i1;
+    sh[0] = k.i0;
+    sh[1] = k.i1;
   }
   __syncthreads();
-  Chunk k;
+  Span k;
   k.i0 = __builtin_amdgcn_readfirstlane(sh[0]);
   k.i1 = __builtin_amdgcn_readfirstlane(sh[1]);
   return k;
@@ -1039,12 +1014,12 @@ __global__ void __launch_bounds__(GRAM == kSep ? 512 : 256) k_children(Problem P
   WaveLds<L> &S = *reinterpret_cast<WaveLds<L> *>(lds_raw + (size_t)P.close_doubles +
                                                   (size_t)wv * P.lds_wave_doubles);
   __shared__ int next[2];
-  Chunk k = first_chunk(P, 1);
+  Span k = first_chunk(P.counters[2], nw, gridDim.x, blockIdx.x);
   if (k.i0 >= k.i1) return;  // uniform in the workgroup
   build_pidmap<L>(pidmap, podd, threadIdx.x, blockDim.x);
   int loaded = -1;
 #pragma unroll 1
-  for (; k.i0 < k.i1; k = next_chunk(P, 1, next)) {
+  for (; k.i0 < k.i1; k = next_chunk(P, next)) {
   const int i1 = k.i1;
   int s = item_slot(P, k.i0), lo = P.woff[s], hi = P.woff[s + 1];  // current slot, its items
   int w = k.i0 + wv, seg = k.i0;
@@ -1228,21 +1203,21 @@ __device__ inline int row_end(const Problem &P, int s, int e, int i1) {
   return i1;
 }
 
-// How the items are shared out: an eighth of the round's items per XCD (the
-// workgroups b = x mod 8, which the hardware places on XCD x), each workgroup of
-// an XCD a first chunk by its index and then chunks from the XCD's own counter
-// (one counter for all is a queue of thousands of atomics on one address: 50k
-// cycles a wait); within a workgroup the waves take groups of eight items from
-// its range, a run of one parameter row.  A wave that finds the range empty
-// takes the next one for all (the lock), while the others finish their groups:
-// no barrier until another row's table is needed or the items are gone.  (With
-// a barrier at every chunk the waves of one flow scale's rounds spent 37% of
-// their time waiting, 60% in the per-integral mode.)
+// How the items are shared out: a share of the XCD's items per workgroup, by
+// index and then from the XCD's counter (share.h; the hardware places the
+// workgroups b = x mod 8 on XCD x; one counter for all is a queue of thousands of
+// atomics on one address: 50k cycles a wait); within a workgroup the waves take
+// groups of eight items from its range, a run of one parameter row.  A wave that
+// finds the range empty takes the next one for all (the lock), while the others
+// finish their groups: no barrier until another row's table is needed or the
+// items are gone.  (With a barrier at every chunk the waves of one flow scale's
+// rounds spent 37% of their time waiting, 60% in the per-integral mode.)
 struct LpcShare {
-  unsigned long long range;  // end << 32 | next item
+  unsigned long long range;  // range_word
   int lock;
   int mode;                  // 0: run, 1: another row's table, 2: no items left
-  int row, lo, hi;           // the next range and its row (mode 1)
+  int row;                   // the next range and its row (mode 1)
+  Span next;
   int rest, end;             // what is left of the chunk behind the range
   int base, total;           // the XCD's items behind the first chunks
   int group;                 // items per group
@@ -1257,48 +1232,39 @@ struct LpcShare {
 // factors on 8x8 momenta take 666 us with this rule, 684 with twice and 742
 // with four times as many items, 700 without wide groups.  (One momentum: 434
 // -> 381 us.)
-__device__ inline int group_items(const Problem &P, long total) { return total <= P.wide_items ? 1 : lpc::kItems; }
-
-// chunk sizes: half of an even share of the XCD's items left, in whole groups
-__device__ inline int share_items(int left, int group) {
-  const int wgs = ((int)gridDim.x + kXcds - 1) / kXcds;  // (the XCD's workgroups, or one more)
-  if (group == 1) return max(1, (left + wgs - 1) / wgs);
-  return max(group, left / (2 * wgs) / group * group);
-}
+__device__ inline int group_items(const Problem &P, int total) { return total <= P.wide_items ? 1 : lpc::kItems; }
 
 // the next range of this workgroup (one wave): of the present chunk, or of a
 // new one from the counter
 __device__ inline void next_range(const Problem &P, LpcShare &sh, int loaded) {
   const int lane = lane_id();
-  int i0 = sh.rest, i1 = sh.end;
-  if (i0 >= i1) {
+  Span k = {sh.rest, sh.end};
+  if (k.i0 >= k.i1) {
     if (lane == 0 && sh.base < sh.total) {
       int *count = P.xcount + (blockIdx.x % min(kXcds, (int)gridDim.x)) * kXcdStride;
       const int seen = sh.base + __hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       if (seen < sh.total) {
-        const int c = share_items(sh.total - seen, sh.group);
-        i0 = min(sh.base + atomicAdd(count, c), sh.total);
-        i1 = min(i0 + c, sh.total);
+        const int c = share_items(sh.total - seen, sh.group, gridDim.x, kXcds);
+        k = counted_span(sh.base, sh.total, atomicAdd(count, c), c);
       }
     }
-    i0 = __builtin_amdgcn_readfirstlane(i0);
-    i1 = __builtin_amdgcn_readfirstlane(i1);
+    k.i0 = __builtin_amdgcn_readfirstlane(k.i0);
+    k.i1 = __builtin_amdgcn_readfirstlane(k.i1);
   }
-  if (i0 >= i1) {
+  if (k.i0 >= k.i1) {
     if (lane == 0) sh.mode = 2;
     return;
   }
-  const int s = wave_slot(P, i0), e = __builtin_amdgcn_readfirstlane(P.sctr[s].entry);
-  const int hi = row_end(P, s, e, i1);
+  const int s = wave_slot(P, k.i0), e = __builtin_amdgcn_readfirstlane(P.sctr[s].entry);
+  const int hi = row_end(P, s, e, k.i1);
   if (lane == 0) {
     sh.rest = hi;
-    sh.end = i1;
+    sh.end = k.i1;
     if (e == loaded) {
-      atomicExch(&sh.range, ((unsigned long long)hi << 32) | (unsigned)i0);
+      atomicExch(&sh.range, range_word({k.i0, hi}));
     } else {
       sh.row = e;
-      sh.lo = i0;
-      sh.hi = hi;
+      sh.next = {k.i0, hi};
       sh.mode = 1;
     }
   }
@@ -1313,14 +1279,16 @@ __device__ inline int take_group(const Problem &P, LpcShare &sh, int loaded, int
     int mode = 0;
     if (lane == 0) {
       r = __hip_atomic_load(&sh.range, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      if ((unsigned)r < (unsigned)(r >> 32)) r = atomicAdd(&sh.range, (unsigned long long)sh.group);
+      if (!range_empty(r)) r = atomicAdd(&sh.range, (unsigned long long)sh.group);
       mode = __hip_atomic_load(&sh.mode, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
-    const int g = __builtin_amdgcn_readfirstlane((int)(unsigned)r);
-    end = __builtin_amdgcn_readfirstlane((int)(r >> 32));
-    if (g < end) {
-      end = min(end, g + __builtin_amdgcn_readfirstlane(sh.group));
-      return g;
+    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)r);
+    const unsigned long long ru =
+        ((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((unsigned)(r >> 32)) << 32) | lo;
+    if (!range_empty(ru)) {
+      const Span k = range_group(ru, __builtin_amdgcn_readfirstlane(sh.group));
+      end = k.i1;
+      return k.i0;
     }
     if (__builtin_amdgcn_readfirstlane(mode)) return -1;
     int mine = 0;
@@ -1330,7 +1298,7 @@ __device__ inline int take_group(const Problem &P, LpcShare &sh, int loaded, int
       int empty = 0;
       if (lane == 0) {
         const unsigned long long q = __hip_atomic_load(&sh.range, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        empty = (unsigned)q >= (unsigned)(q >> 32) &&
+        empty = range_empty(q) &&
                 __hip_atomic_load(&sh.mode, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == 0;
       }
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
@@ -1937,25 +1905,22 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(3))) k
   __shared__ LpcShare share;
   // (with one parameter row its table is staged before the items are known)
   bool staged = P.one_row && blockDim.x > 64;
-  {  // the first chunk, by index in the XCD's items [x0, x1)
-    // (a grid of fewer workgroups than XCDs: a share per workgroup)
-    const int nx = min(kXcds, (int)gridDim.x), x = blockIdx.x % nx;
-    const int nb = ((int)gridDim.x - x + nx - 1) / nx;  // the XCD's workgroups
-    const long total = P.counters[2];
-    const int x0 = (int)(total * x / nx), x1 = (int)(total * (x + 1) / nx);
-    const int group = group_items(P, total), c = share_items(x1 - x0, group);
-    const int i0 = (int)min((long)x0 + (long)(blockIdx.x / nx) * c, (long)x1), i1 = min(i0 + c, x1);
-    if (i0 >= i1) return;  // uniform in the workgroup
+  {  // the first share, by index among the XCD's workgroups
+    const int total = P.counters[2], group = group_items(P, total);
+    const XcdShare x = xcd_share(total, gridDim.x, blockIdx.x, kXcds);
+    const int c = share_items(x.last - x.first, group, gridDim.x, kXcds);
+    const Span k = first_share(x, c);
+    if (k.i0 >= k.i1) return;  // uniform in the workgroup
     if (wv == 0) {
       if (threadIdx.x == 0) {
-        share.base = (int)min((long)x0 + (long)nb * c, (long)x1);
-        share.total = x1;
+        share.base = share_base(x, c);
+        share.total = x.last;
         share.group = group;
         share.lock = 0;
         share.mode = 0;
         share.range = 0;
-        share.rest = i0;
-        share.end = i1;
+        share.rest = k.i0;
+        share.end = k.i1;
       }
       wave_sync();
       next_range(P, share, staged ? 0 : -1);
@@ -1977,7 +1942,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(3))) k
       copy_table(tabl, P.tab + E0.tab_off, tab_doubles(E0), threadIdx.x, blockDim.x);
       __syncthreads();  // (and has read share.mode)
       if (threadIdx.x == 0) {
-        atomicExch(&share.range, ((unsigned long long)share.hi << 32) | (unsigned)share.lo);
+        atomicExch(&share.range, range_word(share.next));
         atomicExch(&share.mode, 0);
       }
       __syncthreads();
