@@ -13,6 +13,8 @@
 //   sum_{n >= N} w_n^{-2k} = (2 pi T)^{-2k} zeta(2k, N + 1/2)  (Hurwitz zeta).
 #include <math.h>
 
+#include <algorithm>
+
 #include "launch.h"
 
 namespace paid {
@@ -218,12 +220,23 @@ hipError_t launch_tables(TabArgs a, hipStream_t s) {
   econ_matrix(a.econ);
   for (int m = 0; m < kTabPts; ++m) a.cosine[m] = cos(2.0 * kPi * m / kTabPts);
   a.cosine[kTabPts / 4] = a.cosine[3 * kTabPts / 4] = 0.0;
-  hipLaunchKernelGGL(k_zeta, dim3(a.n_entries), dim3(64), 0, s, a.entries, a.n_entries, a.zeta);
   const int b1 = (int)((a.max_points * kTabLanes + 255) / 256);
   const int b2 = (a.max_rows * kRowThreads + 255) / 256;
-  hipLaunchKernelGGL(k_tab_points, dim3((unsigned)a.n_entries * b1), dim3(256), 0, s, a, b1);
-  hipLaunchKernelGGL(k_tab_coef, dim3((unsigned)a.n_entries * b2), dim3(256), 0, s, a, b2);
-  return hipGetLastError();
+  // A launch may have 2^32 threads, which 200,000 rows of 84 workgroups (T = 0.01)
+  // reach: as many rows a launch as stay below half of that.
+  const int most = (int)std::max(1L, (1L << 23) / std::max(b1, b2));
+  for (int left = a.n_entries; left > 0; left -= most) {
+    const int n = std::min(left, most);
+    hipLaunchKernelGGL(k_zeta, dim3(n), dim3(64), 0, s, a.entries, n, a.zeta);
+    hipLaunchKernelGGL(k_tab_points, dim3((unsigned)(n * b1)), dim3(256), 0, s, a, b1);
+    hipLaunchKernelGGL(k_tab_coef, dim3((unsigned)(n * b2)), dim3(256), 0, s, a, b2);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    a.entries += n;
+    a.zeta += (long)n * (kTabKTail + 1);
+    a.svals += (long)n * a.max_points;
+  }
+  return hipSuccess;
 }
 
 // container constants: parameter row, channel, cos/sin of l/2 per axis
