@@ -647,7 +647,11 @@ int paid_integrate(paid_ctx *c, const paid_params *params, int n_params, const d
   } else {
     size_t fr = 0, tot = 0;
     HIPCHK(c, hipMemGetInfo(&fr, &tot));
-    const double avail = (double)(fr + c->code.n + c->key.n + c->Q.n + c->E.n + c->dv.n + c->dep.n);
+    size_t held = 0;  // of an earlier call
+    for (const DevBuf *b : {&c->code, &c->key, &c->Q, &c->E, &c->dv, &c->dep, &c->de, &c->sel, &c->selc, &c->ifill,
+                            &c->upart, &c->errp, &c->itau, &c->slot_d, &c->pyr})
+      held += b->n;
+    const double avail = (double)(fr + held);
     pool_bytes = (size_t)(0.55 * avail);
     rest_bytes = (size_t)(0.35 * avail);
   }
@@ -664,7 +668,7 @@ int paid_integrate(paid_ctx *c, const paid_params *params, int n_params, const d
   if (Ws > n_ctr) Ws = n_ctr;
   if (Wb + Ws > 65536) Ws = 65536 - Wb;
   // the round buffers of every slot (deltas, selections) must fit beside the pool
-  const size_t slot_rest = (size_t)bmax * (8 * ((size_t)MQ + (store_E ? MU : 0)) + 16) + 32 * (size_t)MU;
+  const size_t slot_rest = slot_round_bytes(bmax, MQ, MU, store_E, c->seed_on);
   if (rest_bytes > 0 && (size_t)(Wb + Ws) * slot_rest > rest_bytes) Ws = (long)(rest_bytes / slot_rest) - Wb;
   if (Ws < 1) return fail(c, PAID_ENOMEM, "region pool too small for one container of %ld regions", cap);
   const long W = Wb + Ws;

@@ -210,6 +210,16 @@ __device__ inline bool seed_split(const Problem &P, int s, uint64_t code) {
 hipError_t launch_admit(const Problem &p, hipStream_t s);
 // doubles of the chunk sums of the per-parent deltas (Problem::upart)
 size_t update_scratch_doubles(int W, int MQ, int MU);
+// bytes of one slot's round buffers, with up to bmax splits a round: per split
+// its deltas (dv, dep, de), index, code and fill mark (sel, selc, ifill); per slot
+// its sums (val, err, errp, itau), the deltas' chunk sums (upart), its container
+// (sctr), counts (slot_i, stl, movei) and, with a model, its pyramid (pyr, seedd)
+inline size_t slot_round_bytes(int bmax, int MQ, int MU, bool errors, bool seeded) {
+  const size_t split = 8 * (size_t)MQ + (errors ? 8 * (size_t)MU : 0) + 8 + 4 + 8 + 4;
+  const size_t sums = 8 * ((size_t)MQ + 1) + 8 * (size_t)MU + 4 * (size_t)MU + 8 * update_scratch_doubles(1, MQ, MU);
+  return (size_t)bmax * split + sums + sizeof(Ctr) + 8 * sizeof(int) + 3 * sizeof(long) + 2 * sizeof(int) +
+         (seeded ? 8 * kPyr + sizeof(int) : 0);
+}
 // moves of waiting containers from small to large slots (p.Wb > 0)
 hipError_t launch_move(const Problem &p, hipStream_t s);
 // predicted leaves of every parameter row (sum over its containers and cells
