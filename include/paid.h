@@ -213,7 +213,8 @@ int paid_integrate(struct paid_ctx *ctx, const paid_params *params, int n_params
 
 /* Frequency-summed kernel g = K_j(a, b) of one parameter row at n energy
  * pairs (the closed-form frequency sum of Sec. 2 as the library evaluates
- * it).  channel: PAID_PP or PAID_PH.  a, b, out: [n], n >= 0 (NULL allowed
+ * it, in the form of the kernel that the context's eval_layout selects for the
+ * 9-function box).  channel: PAID_PP or PAID_PH.  a, b, out: [n], n >= 0 (NULL allowed
  * when n = 0); energies beyond the band bound 4|t| + 4|t'| + |mu| are
  * PAID_EINVAL. */
 int paid_kernel_eval(struct paid_ctx *ctx, const paid_params *p, unsigned channel,

@@ -980,7 +980,7 @@ int paid_kernel_eval(paid_ctx *c, const paid_params *p, unsigned channel, const 
   HIPCHK(c, hipMemcpyAsync(da, ha.data(), sizeof(double) * n, hipMemcpyHostToDevice, c->stream));
   HIPCHK(c, hipMemcpyAsync(db, hb.data(), sizeof(double) * n, hipMemcpyHostToDevice, c->stream));
   HIPCHK(c, launch_kernel_eval(c->entries.as<Entry>(), c->tab.as<double>(), channel == PAID_PH ? 1 : 0,
-                               da, db, n, dout, c->stream));
+                               da, db, n, dout, c->cfg.eval_layout == 1, c->stream));
   HIPCHK(c, hipMemcpyAsync(out, dout, sizeof(double) * n, hipMemcpyDefault, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
   tmp.release();

@@ -257,7 +257,7 @@ hipError_t launch_update(const Problem &p, long items, hipStream_t s);
 
 // diagnostics
 hipError_t launch_kernel_eval(const Entry *e, const double *tab, int ch, const double *a,
-                              const double *b, int n, double *out, hipStream_t s);
+                              const double *b, int n, double *out, bool taylor, hipStream_t s);
 
 hipError_t set_rule_constants(const RuleConst &rc);
 

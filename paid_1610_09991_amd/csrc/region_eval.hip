@@ -1965,12 +1965,14 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(3))) k
 }
 
 // ---------------------------------------------------------------- diagnostics
+// taylor: in the form of the one-wave kernel (k_children)
 __global__ void k_kernel_eval(const Entry *e, const double *tab, int ch, const double *a,
-                              const double *b, int n, double *out) {
+                              const double *b, int n, double *out, bool taylor) {
   int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   const Entry E = *e;
-  out[i] = K_eval(E, tab + E.tab_off, ch, a[i], b[i]);
+  const double *t = tab + E.tab_off;
+  out[i] = taylor ? K_taylor(E, t + (long)E.JV * kValStride, ch, a[i], b[i]) : K_eval(E, t, ch, a[i], b[i]);
 }
 
 template <int L, int GRAM>
@@ -2190,10 +2192,10 @@ hipError_t launch_eval(const Problem &p, int grid, hipStream_t s) {
 }
 
 hipError_t launch_kernel_eval(const Entry *e, const double *tab, int ch, const double *a,
-                              const double *b, int n, double *out, hipStream_t s) {
+                              const double *b, int n, double *out, bool taylor, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_kernel_eval, dim3((n + 255) / 256), dim3(256), 0, s, e, tab, ch, a, b, n,
-                     out);
+                     out, taylor);
   return hipGetLastError();
 }
 
