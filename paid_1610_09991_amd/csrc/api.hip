@@ -647,11 +647,10 @@ int paid_integrate(paid_ctx *c, const paid_params *params, int n_params, const d
   } else {
     size_t fr = 0, tot = 0;
     HIPCHK(c, hipMemGetInfo(&fr, &tot));
-    size_t held = 0;  // of an earlier call
-    for (const DevBuf *b : {&c->code, &c->key, &c->Q, &c->E, &c->dv, &c->dep, &c->de, &c->sel, &c->selc, &c->ifill,
-                            &c->upart, &c->errp, &c->itau, &c->slot_d, &c->pyr})
-      held += b->n;
-    const double avail = (double)(fr + held);
+    // (the smaller buffers that an earlier call holds are left out: counted in
+    // full, a later call could come to one slot more by what else has been freed
+    // since, and allocate the whole pool anew, which takes seconds)
+    const double avail = (double)(fr + c->code.n + c->key.n + c->Q.n + c->E.n + c->dv.n + c->dep.n);
     pool_bytes = (size_t)(0.55 * avail);
     rest_bytes = (size_t)(0.35 * avail);
   }

@@ -24,11 +24,13 @@ def test_round_buffers_fit_beside_the_pool():
     filler = torch.empty(free - (16 << 30), dtype=torch.uint8, device="cuda:0")
     try:
         with P.Context(max_regions=2 * 109_375, batch_max=2 * 69_600) as c:
-            for _ in range(2):  # a second call counts what the first one holds as free
+            slots = 3500
+            for _ in range(3):  # no later call asks for a larger pool
                 out, _, st, rc = c.integrate([[1.0, -0.25, -0.95, 0.3, 1.0]], q, W.ff_box(0), 0, P.PH, rtol=1e-2)
                 left, _ = torch.cuda.mem_get_info()
                 assert rc == P.OK and st["containers"] == 4096
-                assert 1000 < st["max_active"] < 3500, st["max_active"]
+                assert 1000 < st["max_active"] <= slots, (st["max_active"], slots)
+                slots = st["max_active"]
                 assert left > 0.08 * (16 << 30), left
     finally:
         del filler
