@@ -69,13 +69,24 @@ PEAK_FP64_TFLOPS = 78.6  # MI355X FP64: vector (256 CUs x 4 SIMD x 16 lanes x 2 
 K_FLOPS_PER_NODE = 72
 COLUMNS_PER_ITEM = 17
 K_FLOPS_PER_COLUMN = 8
+# What the two-lanes kernel itself needs of them (box basis of 9 functions).
+LPC_FLOPS_PER_ITEM = 23700
+
+# What bounds that kernel is LDS bandwidth: per node (324 a parent) a lane
+# reads two table rows of nine doubles and the node row's cosine and sine.  A
+# compute unit's LDS delivers 128 bytes a clock; bank conflicts of the random
+# table rows and the records' staging, which are not counted, keep it busy 83%
+# of the kernel's time (profiles/k_children_c2_counters.md).
+LDS_BYTES_PER_NODE = 160
+LPC_NODES_PER_ITEM = 324
+PEAK_LDS_TBS = 256 * 128 * 2.4e9 / 1e12
 
 # HBM bytes per work item of the region-evaluation kernel, from the
 # FETCH_SIZE / WRITE_SIZE counters scaled by a plain copy's readings
 # (profiles/k_children_c2_counters.md); valid only for the kernel they were
-# taken with, identified by this hash of the two files that define it.
+# taken with, identified by this hash of the files that define it.
 TRAFFIC_BYTES_PER_ITEM = 1490
-TRAFFIC_SOURCES_SHA256 = "6fbda8111e4680fa33073d55f868af18c681f421014982f8cbdd1e0d03b1dc97"
+TRAFFIC_SOURCES_SHA256 = "cdcfa6d3aedddd2a695b0451b1b4b9dedd94acdfee685638145cfb84c6119e7f"
 NODES_PER_ITEM = 289
 
 # Per-workload region budget (max_regions): the smallest power of two that
@@ -98,7 +109,7 @@ def kernel_sources_sha256() -> str:
     import hashlib
     h = hashlib.sha256()
     d = os.path.join(ROOT, "paid_1610_09991_amd", "csrc")
-    for f in ("paid_device.h", "region_eval.hip"):
+    for f in ("paid_device.h", "region_eval.hip", "share.h"):
         with open(os.path.join(d, f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()
@@ -269,11 +280,20 @@ class Runner:
         traffic = None
         if sep and self.M == 9 and kernel_sources_sha256() == TRAFFIC_SOURCES_SHA256:
             traffic = TRAFFIC_BYTES_PER_ITEM * items / max(launches, 1)
-        return {"bound": "alu" if sep else "mfma", "achieved": achieved, "peak": PEAK_FP64_TFLOPS,
-                "unit": "TFLOP/s", "frac": achieved / PEAK_FP64_TFLOPS, "traffic": traffic,
+        alu = {"achieved": achieved, "peak": PEAK_FP64_TFLOPS, "unit": "TFLOP/s",
+               "frac": achieved / PEAK_FP64_TFLOPS}
+        two_lanes = sep and self.cfg["L"] <= 1 and not self.ctx.cfg.eval_layout and not self.ctx.cfg.symmetry
+        lds = LDS_BYTES_PER_NODE * LPC_NODES_PER_ITEM * items / ev_s / 1e12 if ev_s > 0 else 0.0
+        roof = ({"bound": "lds", "achieved": lds, "peak": PEAK_LDS_TBS, "unit": "TB/s",
+                 "frac": lds / PEAK_LDS_TBS, "fp64": alu} if two_lanes else
+                {"bound": "alu" if sep else "mfma", **alu})
+        if two_lanes and self.M == 9:
+            roof["fp64"]["frac_of_needed_flops"] = alu["frac"] * LPC_FLOPS_PER_ITEM / fpi
+        return {**roof, "traffic": traffic,
                 "traffic_unit": "B per launch",
-                "kernel": "k_children (region evaluation, %s projection)" %
-                          ("separable FP64" if sep else "FP64 matrix-core"),
+                "kernel": "%s (region evaluation, %s projection)" %
+                          ("k_children_lpc" if two_lanes else "k_children",
+                           "separable FP64" if sep else "FP64 matrix-core"),
                 "launches": launches, "avg_launch_ms": 1e3 * avg_launch, "flops_per_item": fpi,
                 "items": items, "eval_share_of_step": ev_s / dt}
 

@@ -113,10 +113,10 @@ typedef struct {
   void *stream;         /* hipStream_t to run on, or NULL for a private stream */
   int profile;          /* 1: time the region-evaluation launches with HIP
                            events on the context stream (paid_stats.eval_*) */
-  int graph;            /* 1: capture the device round (seven kernels and the
-                           read-back of three counters, in three parts around
-                           the evaluation launch) as HIP graphs and replay
-                           them every round */
+  int graph;            /* 1: capture the device round in two parts, the
+                           bookkeeping (its last kernel stores the round's
+                           counters to pinned host memory) and the evaluation
+                           launch, as HIP graphs and replay them every round */
   int eval_wg_per_cu;   /* workgroups of the region-evaluation launch per
                            compute unit (0: as many as the kernel's occupancy
                            fits on one); they share the work items of a round

@@ -18,7 +18,8 @@
 // whole matrix's loads issued together, and many waves hide them.  Staging six
 // zero-padded 32 x 32 matrices per wave in LDS (50.7 KB, three waves a compute
 // unit) instead took 210 us for 11,520 momenta of order 9 and 77 us for 1,024
-// of order 25; this takes 18 and 20 us (35 and 37 us a call with its synchronisation, 244 and 89 before).
+// of order 25; this takes 18 us each (33
+// and 32 us a call with its synchronisation, 244 and 90 before).
 #include "launch.h"
 
 namespace paid {

@@ -336,6 +336,7 @@ __device__ inline double pair_close(const Entry &e, const double *tab, unsigned 
 }
 
 // kernel K_j(a, b) of two energies from both tables: ph = S[a,b], pp = -S[a,-b]
+// (the two-lanes kernel's form as one function, for the diagnostic)
 __device__ inline double K_eval(const Entry &e, const double *tab, int ch, double a, double b) {
   double cn = 0.0, sn = 0.0;
   const unsigned sg = ch ? 0u : 0x80000000u;
